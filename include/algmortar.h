@@ -107,15 +107,14 @@ typedef struct {
  * beta (the preconditioner depends on its argument). */
 #define AM_FLAG_INEXACT_IFACE 8u
 /* precision form with BF16 factors (local_prec AM_BF16), the interface
- * solve as its own launches, and either 16 right-hand sides (where the local
- * solves run on the matrix cores) or one right-hand side with every
- * subdomain's band within 64 rows: multiply the BF16 factor tiles by the
- * block vectors rounded to BF16 (round to nearest even), BF16 x BF16
- * products with FP32 accumulation on the matrix cores
- * (v_mfma_f32_16x16x16bf16_1k; one right-hand side takes column 0 of each
- * 16-column tile), instead of the default FP32 x FP32 products of the
- * widened factors (matrix cores with 16 right-hand sides, vector units with
- * one).  The preconditioner then carries 8-bit block vectors into every
+ * solve as its own launches, and either 16 right-hand sides or one right-hand
+ * side with every subdomain's band within 64 rows: multiply the BF16 factor
+ * entries by the block vectors rounded to BF16 (round to nearest even), with
+ * FP32 accumulation (16 right-hand sides: v_mfma_f32_16x16x16bf16_1k on the
+ * matrix cores; one: the vector units, where such a product is exact in
+ * FP32), instead of the default FP32 x FP32 products of the widened factors.
+ * The diagonals of the block inverses stay FP32 and multiply the unrounded
+ * vectors.  The preconditioner then carries 8-bit block vectors into every
  * factor product; the outer PCG is the flexible one, as for every reduced
  * precision.  Ignored in every other case. */
 #define AM_FLAG_BF16_PRODUCTS 16u
@@ -339,8 +338,9 @@ am_status algmortar_export_mbf(am_handle h, int64_t iface, int32_t sub, double* 
 am_status algmortar_time_kernel(am_handle h, int32_t kernel, int32_t nrhs, int32_t reps,
                                 double* avg_ms, double* bytes);
 
-/* Batching form: the wave layout of the local kernel (groups of right-hand
- * sides x column splits of each block pass) is chosen per right-hand-side
+/* Batching form: the layout of the local kernel (block tiles kept in
+ * registers where the band is within 64 rows; groups of right-hand sides x
+ * column splits of each block pass above) is chosen per right-hand-side
  * count by an autotuner that times every candidate layout on this handle's
  * subdomains as a solve runs it (with the PCG dot products, on a freshly
  * initialised PCG state that the next algmortar_pcg initialises again; the
@@ -360,9 +360,9 @@ am_status algmortar_time_kernel(am_handle h, int32_t kernel, int32_t nrhs, int32
  * choice) and read back by later handles and processes, which then use the
  * recorded layout without timing (us holds zeros): the same results as the
  * process that timed it.  16 right-hand sides with the interface solve as
- * its own launches, and one right-hand side under AM_FLAG_BF16_PRODUCTS
- * with every subdomain's band within 64 rows, run matrix-core kernels of a
- * single layout: choice 0, ncand 1, nothing timed. */
+ * its own launches or with every subdomain's band within 64 rows, and one
+ * right-hand side under AM_FLAG_BF16_PRODUCTS with every subdomain's band
+ * within 64 rows, have a single layout: choice 0, ncand 1, nothing timed. */
 am_status algmortar_tile_choice(am_handle h, int32_t nrhs, int32_t* choice, int32_t* ncand,
                                 double* us);
 

@@ -432,6 +432,20 @@ static hipError_t interface_inverse(DeviceState& d, hipStream_t st) {
   return he;
 }
 
+// Set-up arrays of the window-64 band factors of the FP32 / BF16 forms (see
+// DeviceState::Bc), in one allocation t that the caller frees; zeroed as the
+// band kernel writes inside the band only.
+static hipError_t band_alloc(DeviceState& d, const LocalPlan& lp, void** t, hipStream_t st) {
+  if (d.bucket_sub[0].empty()) return hipSuccess;
+  const size_t bytes = (size_t)lp.band_off.back() * (d.prec == AM_FP32 ? 4 : 2);
+  hipError_t e = hipMalloc(t, 2 * bytes + (size_t)lp.roff.back() * 4);
+  if (e != hipSuccess) return e;
+  d.Bc = *t;
+  d.Br = (uint8_t*)*t + bytes;
+  d.Bd = (uint8_t*)*t + 2 * bytes;
+  return hipMemsetAsync(*t, 0, 2 * bytes, st);
+}
+
 // row of S (original numbering) named by a failing pivot of the interface
 // factorization (the nested-dissection form factors a reordered, padded S)
 static int64_t iface_fail_row(const DeviceState& d, int32_t row) {
@@ -529,8 +543,8 @@ static am_status setup_impl(const am_csr* A, const int32_t* part, int32_t nparts
   d.NE = st.n_edges();
   d.ldS = (int32_t)((d.NL + kTile - 1) / kTile * kTile);
   d.max_nrhs = pow2_at_least(opt.max_nrhs);
-  // small interface inverses are applied inside the local kernel (each
-  // subdomain multiplies its own rows; every row is read twice)
+  // small interface inverses: eta in one launch, or inside the local kernel
+  // (each subdomain multiplies its own rows; every row is read twice)
   d.fuse_eta = (d.NL > 0 && (double)d.NL * d.NL * 8.0 <= 64.0 * 1024 * 1024) ? 1 : 0;
   // the tile kernel folds the per-wave partial rows in its second tile buffer
   // (at least 8 KB for every factor precision and window)
@@ -715,6 +729,18 @@ static am_status setup_impl(const am_csr* A, const int32_t* part, int32_t nparts
   SCHK(upload(al, &d.wp, lp.wp, sm));
   SCHK(upload(al, &d.roff, lp.roff, sm));
   SCHK(upload(al, &d.fac_off, lp.fac_off, sm));
+  SCHK(upload(al, &d.cpl_off, lp.cpl_off, sm));
+  SCHK(upload(al, &d.cpl_k, lp.cpl_k, sm));
+  std::vector<SubDesc> desc((size_t)st.m);
+  d.max_np0 = 0;
+  for (int32_t s2 = 0; s2 < st.m; ++s2) {
+    const int32_t np = (int32_t)(lp.roff[s2 + 1] - lp.roff[s2]);
+    desc[s2] = {st.sub_ptr[s2], lp.fac_off[s2], lp.roff[s2], lp.cpl_off[s2], mbf_off[s2],
+                st.isub_ptr[s2], (int32_t)(st.sub_ptr[s2 + 1] - st.sub_ptr[s2]), np / 64,
+                lp.cpl_k[s2], (int32_t)(st.isub_ptr[s2 + 1] - st.isub_ptr[s2])};
+    if (lp.wp[s2] == 64) d.max_np0 = std::max(d.max_np0, np);
+  }
+  SCHK(upload(al, &d.desc, desc, sm));
   for (int bk = 0; bk < 2; ++bk) {
     SCHK(upload(al, &d.d_bucket_sub[bk], d.bucket_sub[bk], sm));
     SCHK(upload(al, &d.d_bucket_pair[bk], d.bucket_pair[bk], sm));
@@ -740,15 +766,32 @@ static am_status setup_impl(const am_csr* A, const int32_t* part, int32_t nparts
   const size_t esz = d.prec == AM_FP64 ? 8 : (d.prec == AM_FP32 ? 4 : 2);
   const size_t isz = d.prec == AM_FP64 ? 8 : 4;
   const size_t nfac = (size_t)lp.fac_off[st.m];
-  uint8_t *Lc = nullptr, *Lr = nullptr, *iv = nullptr;
+  uint8_t *Lc = nullptr, *Lr = nullptr, *iv = nullptr, *cv = nullptr;
   SCHK(dalloc(al, &Lc, nfac * esz));
-  SCHK(dalloc(al, &Lr, nfac * esz));
   SCHK(dalloc(al, &iv, (size_t)lp.roff[st.m] * isz));
+  SCHK(dalloc(al, &cv, (size_t)lp.cpl_off[st.m] * isz));
+  SCHK(dalloc(al, &d.cidx, (size_t)lp.cpl_off[st.m]));
   d.Lc = Lc;
-  d.Lr = Lr;
   d.invd = iv;
-  SCHK(hipMemsetAsync(Lc, 0, nfac * esz, sm));
-  SCHK(hipMemsetAsync(Lr, 0, nfac * esz, sm));
+  d.cpl = cv;
+  d.cpl_kmax = lp.cpl_kmax;
+  d.max_ni = lp.max_ni;
+  // FP32 / BF16: band factors of the window-64 subdomains, for their basis
+  // functions (set-up only)
+  struct Band {  // (freed after a failed set-up has destroyed the handle, too)
+    void* t = nullptr;
+    ~Band() { (void)hipFree(t); }
+  } band;
+  if (d.prec != AM_FP64 && !plain) SCHK(upload(al, &d.band_off, lp.band_off, sm));
+  if (d.prec != AM_FP64 && !plain) SCHK(band_alloc(d, lp, &band.t, sm));
+  // the band factors (window 128) are written inside their band only; the
+  // row layout exists for them alone
+  if (!d.bucket_sub[1].empty()) {
+    SCHK(dalloc(al, &Lr, nfac * esz));
+    d.Lr = Lr;
+    SCHK(hipMemsetAsync(Lc, 0, nfac * esz, sm));
+    SCHK(hipMemsetAsync(Lr, 0, nfac * esz, sm));
+  }
   SCHK(dalloc(al, &d.fail, 4));
   SCHK(hipMemsetAsync(d.fail, 0xFF, 4 * sizeof(int32_t), sm));
   SCHK(dalloc(al, &d.mbf, (size_t)mbf_off[st.m]));
@@ -826,15 +869,15 @@ static am_status setup_impl(const am_csr* A, const int32_t* part, int32_t nparts
          "interface matrix S not SPD at row " + std::to_string(iface_fail_row(d, fl[2])));
     return bail(AM_ERR_NOT_SPD);
   }
-  // free set-up only arrays: the row layout of the factor served the
+  // free set-up only arrays: the row layout of the band factors served the
   // set-up solves of the basis functions only
   for (auto it = d.allocs.begin(); it != d.allocs.end(); ++it)
-    if (*it == d.Lr) {
+    if (d.Lr && *it == d.Lr) {
       (void)hipFree(*it);
       d.allocs.erase(it);
       break;
     }
-  d.Lr = nullptr;
+  d.Lr = d.Bc = d.Br = d.Bd = nullptr;
   mark("checks and frees", nullptr);
   for (const auto& ph : phases) std::fprintf(stderr, "algmortar set-up: %-24s %9.2f ms\n", ph.first, ph.second);
   *out = h;
@@ -870,7 +913,8 @@ static am_status check_vec_args(am_handle h, const void* a, const void* b, int32
 // BF16 products where every subdomain is in the window-64 bucket (the
 // matrix-core kernels in both cases).
 static bool single_layout(const DeviceState& d, int nr) {
-  if (d.fuse_eta) return false;
+  if (nr == 16 && d.bucket_sub[1].empty()) return true;
+  if (eta_inline(d, nr)) return false;
   return nr == 16 || (nr == 1 && d.bf16_ops && d.bucket_sub[1].empty());
 }
 
@@ -878,7 +922,7 @@ static am_status autotune_tiles(am_handle h, int nr) {
   DeviceState& d = h->d;
   const int slot = tile_slot(nr);
   if (d.tile_cand[slot] >= 0) return AM_OK;
-  const int nc = tile_candidates(nr);
+  const int nc = tile_candidates(d, nr);
   // the matrix-core kernels have one layout: nothing to choose
   if (single_layout(d, nr)) {
     d.tile_cand[slot] = 0;
@@ -929,7 +973,7 @@ static am_status autotune_tiles(am_handle h, int nr) {
   // the smoother's block factors without a coarse part (mode 0).  The
   // candidates take turns over three rounds and keep their fastest round,
   // so a clock ramp at the start does not favour the later ones.
-  const int tmode = d.plain ? 0 : (d.fuse_eta ? 1 : 2);
+  const int tmode = d.plain ? 0 : (eta_inline(d, nr) ? 1 : 2);
   if (tmode == 2) HCHK(launch_pcg_init(d, nr, 1e-300, 1 << 30, 0, st));
   for (int c = 0; c < nc; ++c) d.tile_us[slot][c] = 0.f;
   for (int round = 0; round < 3; ++round)
@@ -967,7 +1011,7 @@ am_status algmortar_tile_choice(am_handle h, int32_t nrhs, int32_t* choice, int3
   if (s != AM_OK) return s;
   const int slot = tile_slot(nr);
   *choice = h->d.tile_cand[slot];
-  *ncand = single_layout(h->d, nr) ? 1 : tile_candidates(nr);
+  *ncand = single_layout(h->d, nr) ? 1 : tile_candidates(h->d, nr);
   if (us)
     for (int c = 0; c < *ncand; ++c) us[c] = h->d.tile_us[slot][c];
   return AM_OK;
@@ -1137,10 +1181,15 @@ am_status algmortar_update_values(am_handle h, const am_csr* A, void* stream) {
   const size_t esz = d.prec == AM_FP64 ? 8 : (d.prec == AM_FP32 ? 4 : 2);
   const size_t nfac = (size_t)h->lp.fac_off[h->st.m];
   void* Lr = nullptr;
-  HCHK(hipMalloc(&Lr, nfac * esz));
-  d.Lr = Lr;
-  hipError_t he = hipMemsetAsync(d.Lc, 0, nfac * esz, st);
-  if (he == hipSuccess) he = hipMemsetAsync(Lr, 0, nfac * esz, st);
+  hipError_t he = hipSuccess;
+  void* band = nullptr;
+  if (d.prec != AM_FP64) he = band_alloc(d, h->lp, &band, st);
+  if (he == hipSuccess && !d.bucket_sub[1].empty()) {
+    he = hipMalloc(&Lr, nfac * esz);
+    d.Lr = Lr;
+    if (he == hipSuccess) he = hipMemsetAsync(d.Lc, 0, nfac * esz, st);
+    if (he == hipSuccess) he = hipMemsetAsync(Lr, 0, nfac * esz, st);
+  }
   if (he == hipSuccess) he = hipMemsetAsync(d.fail, 0xFF, 4 * sizeof(int32_t), st);
   if (he == hipSuccess) he = launch_band_factor(d, st);
   if (he == hipSuccess) he = launch_mbf(d, st);
@@ -1150,7 +1199,8 @@ am_status algmortar_update_values(am_handle h, const am_csr* A, void* stream) {
   const hipError_t he3 = hipStreamSynchronize(st);
   if (he == hipSuccess) he = he3;
   (void)hipFree(Lr);
-  d.Lr = nullptr;
+  (void)hipFree(band);
+  d.Lr = d.Bc = d.Br = d.Bd = nullptr;
   HCHK(he);
   int32_t fl[4];
   HCHK(hipMemcpy(fl, d.fail, sizeof(fl), hipMemcpyDeviceToHost));
@@ -1296,7 +1346,7 @@ am_status algmortar_apply(am_handle h, const double* r, double* z, int32_t nrhs,
   } else {
     if (d.NL > 0) {
       HCHK(launch_bpart(d, d.r, nr, st));
-      if (!d.fuse_eta) HCHK(launch_iface_gemv(d, nr, 0, 0, st));
+      if (!eta_inline(d, nr)) HCHK(launch_iface_gemv(d, nr, 0, 0, st));
     }
     HCHK(launch_local_sweep(d, d.r, d.z, d.eta, nr, 1, st));
   }
@@ -1401,7 +1451,7 @@ am_status algmortar_apply_static(am_handle h, const double* r, double* z, int32_
   HCHK(launch_permute_in(d.dperm, d.n, r, ld, d.r, nrhs, st));
   if (d.NL > 0) {
     HCHK(launch_bpart(d, d.r, nr, st));
-    if (!d.fuse_eta) HCHK(launch_iface_gemv(d, nr, 0, 0, st));
+    if (!eta_inline(d, nr)) HCHK(launch_iface_gemv(d, nr, 0, 0, st));
   }
   HCHK(launch_local_sweep(d, d.r, d.z, d.eta, nr, 1, st));
   HCHK(launch_permute_out(d.dperm, d.n, d.z, z, ld, nrhs, st));
@@ -1486,7 +1536,7 @@ static hipError_t profiled_iteration(am_handle h, int nr, int parity, KernelProf
   };
   if ((e = timed(3, [&] { return launch_pcg_spmv(d, nr, parity, st); })) != hipSuccess) return e;
   if ((e = timed(4, [&] { return launch_pcg_update(d, nr, parity, st); })) != hipSuccess) return e;
-  if (!d.fuse_eta && (e = timed(1, [&] { return launch_iface_gemv(d, nr, 1, 0, st); })) != hipSuccess)
+  if (!eta_inline(d, nr) && (e = timed(1, [&] { return launch_iface_gemv(d, nr, 1, 0, st); })) != hipSuccess)
     return e;
   if ((e = timed(0, [&] { return launch_local_sweep(d, d.r, d.z, d.eta, nr, 2, st); })) != hipSuccess)
     return e;
@@ -1820,12 +1870,18 @@ am_status algmortar_time_kernel(am_handle h, int32_t kernel, int32_t nrhs, int32
       const double N = (double)(st.sub_ptr[s2 + 1] - st.sub_ptr[s2]);
       const double NP = (double)(lp.roff[s2 + 1] - lp.roff[s2]);
       const double ns = (double)(st.isub_ptr[s2 + 1] - st.isub_ptr[s2]);
-      by += 2.0 * NP * lp.wp[s2] * esz + 2.0 * NP * isz + 2.0 * N * 8.0 * nr + ns * N * 8.0;
+      // window 64: the packed block inverses, their diagonal and the
+      // couplings once; window 128: the band factor once per sweep
+      if (lp.wp[s2] == 64)
+        by += NP * (32.0 * esz + isz) + 2.0 * NP * lp.cpl_k[s2] * (isz + 1.0);
+      else
+        by += 2.0 * NP * lp.wp[s2] * esz + 2.0 * NP * isz;
+      by += 2.0 * N * 8.0 * nr + ns * N * 8.0;
     }
     by += (double)d.NL * 8.0 * nr;
     // with the interface solve fused in, its operator S^{-1} (once) and the
     // interface partial right-hand sides
-    if (d.fuse_eta) by += (double)d.NL * d.NL * 8.0 + 2.0 * d.NL * 8.0 * nr;
+    if (eta_inline(d, nr)) by += (double)d.NL * d.NL * 8.0 + 2.0 * d.NL * 8.0 * nr;
   } else if (kernel == 1 && d.nd.on) {
     // the block inverses (twice when there are top rows), C^{-1} once, the
     // coupling values and indices, the slots (read by both block passes and

@@ -124,6 +124,15 @@ struct IxDevice {
   IxScalars* sc = nullptr;              // [kMaxNRHS]
 };
 
+// One subdomain as the solve kernels read it (one 64-byte load instead of a
+// chain of them): first row (device position), factor / diagonal / coupling /
+// basis-function offsets, first basis-function slot, rows, 64-row blocks,
+// couplings per row and side, basis functions.
+struct SubDesc {
+  int64_t base, fac, ro, cpl, mbf, i0;
+  int32_t N, NB, kc, ns;
+};
+
 struct DeviceState {
   int device = 0;
   int prec = AM_FP64;
@@ -131,7 +140,7 @@ struct DeviceState {
   int32_t m = 0;
   int64_t NL = 0, NE = 0;
   int32_t ldS = 0;  // padded interface dimension (multiple of kTile)
-  int32_t fuse_eta = 0;  // local kernel computes its own rows of eta = S^{-1} b
+  int32_t fuse_eta = 0;  // small dense S^{-1}: eta in one launch, or in the local kernel (eta_inline)
   int32_t plain = 0;     // factors are the plain diagonal blocks A_ii (block Jacobi)
   int32_t bf16_ops = 0;  // 16-RHS matrix-core sweeps: BF16 x BF16 products (AM_FLAG_BF16_PRODUCTS)
   int32_t max_nrhs = 1;
@@ -163,9 +172,26 @@ struct DeviceState {
   int32_t* wp = nullptr;       // [m]
   int64_t* roff = nullptr;     // [m+1] padded row offsets of the factor blocks
   int64_t* fac_off = nullptr;  // [m+1] element offsets of the factor blocks
-  void* Lc = nullptr;          // band factor, column layout (precision dependent)
-  void* Lr = nullptr;          // band factor, row layout (set-up only; freed after)
-  void* invd = nullptr;        // [n] 1/L_jj (double for FP64, float otherwise)
+  // window 64: packed block inverses (tri_kernels.h); window 128: band factor,
+  // column layout (precision dependent)
+  void* Lc = nullptr;
+  void* Lr = nullptr;          // band factor, row layout (window 128, set-up only; freed after)
+  // FP32 / BF16 factors, set-up only: the band factors of the window-64
+  // subdomains, from which their basis functions are solved (LocalPlan::band_off)
+  void *Bc = nullptr, *Br = nullptr, *Bd = nullptr;
+  int64_t* band_off = nullptr;
+  // per padded row: diagonal of the block inverses (window 64), 1/L_jj^2
+  // (window 128); double for FP64, float otherwise
+  void* invd = nullptr;
+  // couplings between a window-64 subdomain's neighbouring blocks
+  int32_t cpl_kmax = 0;        // most per row and side
+  int32_t max_ni = 0;          // most basis functions on a subdomain
+  int32_t max_np0 = 0;         // largest padded row count in window 64
+  SubDesc* desc = nullptr;     // [m]
+  int64_t* cpl_off = nullptr;  // [m+1] element offsets
+  int32_t* cpl_k = nullptr;    // [m] places per row and side
+  void* cpl = nullptr;         // values (double for FP64, float otherwise)
+  uint8_t* cidx = nullptr;     // column's row within its block
   std::vector<int32_t> bucket_sub[2];  // host: subdomain ids per window width 64/128
   int32_t* d_bucket_sub[2] = {nullptr, nullptr};
   std::vector<int32_t> bucket_pair[2]; // host: (subdomain, slot) pairs per window width
@@ -229,14 +255,22 @@ double* static_scratch_ptr(int device);
 hipError_t launch_band_factor(DeviceState& d, hipStream_t s);
 hipError_t launch_mbf(DeviceState& d, hipStream_t s);
 inline int tile_slot(int nrhs) { return nrhs <= 1 ? 0 : nrhs <= 2 ? 1 : nrhs <= 4 ? 2 : nrhs <= 8 ? 3 : 4; }
-// number of tile-kernel wave layouts the autotuner times for nrhs
-int tile_candidates(int nrhs);
+// number of local-kernel wave layouts the autotuner times for nrhs
+int tile_candidates(const DeviceState& d, int nrhs);
 // replaces the 64 x 64 diagonal blocks of the column layout by their inverses
 hipError_t launch_invert_diag(DeviceState& d, hipStream_t s);
 // z = A_i^{-1} r (+ prolongation with eta when eta != nullptr); dots when dot_out
 hipError_t launch_local_sweep(DeviceState& d, const double* r, double* z, const double* eta,
                               int nrhs, int mode, hipStream_t s);
 hipError_t launch_bpart(DeviceState& d, const double* r, int nrhs, hipStream_t s);
+
+// Whether the local kernel forms its own rows of eta = S^{-1} b: every
+// workgroup then reads max_ni rows of S^{-1} with its few waves, which pays
+// while that is shorter than the launch it saves (about 4 us).
+constexpr int64_t kEtaInline = 4096;  // max_ni * NL * columns
+inline bool eta_inline(const DeviceState& d, int nr) {
+  return d.fuse_eta && d.max_ni * d.NL * nr <= kEtaInline;
+}
 
 // ---- launchers (kernels_iface.hip) ----
 hipError_t launch_assemble_S(DeviceState& d, hipStream_t s);

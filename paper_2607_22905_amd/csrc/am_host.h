@@ -93,7 +93,15 @@ struct LocalPlan {
   std::vector<int32_t> dpos;       // [n] inverse: dpos[old] = new
   std::vector<int32_t> wp;         // [m] window width per subdomain
   std::vector<int64_t> roff;       // [m+1] padded row offsets (rows padded to a multiple of 64)
-  std::vector<int64_t> fac_off;    // [m+1] offsets (elements) of Lc / Lr blocks = roff * wp
+  // [m+1] element offsets of the factors: 2048 per 64-row block (window 64,
+  // packed block inverses), 128 per row (window 128, band)
+  std::vector<int64_t> fac_off;
+  std::vector<int64_t> band_off;   // [m+1] element offsets of the band factors = padded rows * wp
+  // window 64: most couplings of a row to the block before or after its own,
+  // and [m+1] element offsets of the coupling lists (2 * cpl_k * padded rows)
+  std::vector<int32_t> cpl_k;
+  std::vector<int64_t> cpl_off;
+  int32_t cpl_kmax = 0;
   int32_t max_wp = 64;
   int32_t max_ni = 0;              // max |I_i|
   int32_t max_sub = 0;             // max subdomain size

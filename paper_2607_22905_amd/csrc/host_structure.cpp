@@ -498,6 +498,10 @@ am_status plan_local(const HostCSR& A, const Structure& st, LocalPlan& lp, std::
   lp.wp.assign(st.m, 64);
   lp.fac_off.assign(st.m + 1, 0);
   lp.roff.assign(st.m + 1, 0);
+  lp.band_off.assign(st.m + 1, 0);
+  lp.cpl_k.assign(st.m, 0);
+  lp.cpl_off.assign(st.m + 1, 0);
+  lp.cpl_kmax = 0;
   lp.max_wp = 64;
   lp.max_ni = 0;
   lp.max_sub = 0;
@@ -526,6 +530,20 @@ am_status plan_local(const HostCSR& A, const Structure& st, LocalPlan& lp, std::
       }
     }
     bws[s] = bw;
+    if (bw <= 64) {  // couplings per row to the 64-row blocks beside its own
+      int32_t most = 0;
+      for (int32_t t = 0; t < ns; ++t) {
+        int32_t before = 0, after = 0;
+        for (int64_t p = A.rp[chosen[t]]; p < A.rp[chosen[t] + 1]; ++p) {
+          if (part[A.ci[p]] != s) continue;
+          const int32_t cb = loc[A.ci[p]] / 64;
+          before += cb < t / 64;
+          after += cb > t / 64;
+        }
+        most = std::max(most, std::max(before, after));
+      }
+      lp.cpl_k[s] = most;
+    }
     for (int32_t t = 0; t < ns; ++t) {
       lp.dperm[b + t] = chosen[t];
       lp.dpos[chosen[t]] = (int32_t)(b + t);
@@ -546,7 +564,10 @@ am_status plan_local(const HostCSR& A, const Structure& st, LocalPlan& lp, std::
     lp.max_ni = std::max<int32_t>(lp.max_ni, (int32_t)(st.isub_ptr[s + 1] - st.isub_ptr[s]));
     const int64_t np = ((int64_t)ns + 63) / 64 * 64;
     lp.roff[s + 1] = lp.roff[s] + np;
-    lp.fac_off[s + 1] = lp.fac_off[s] + np * wp;
+    lp.fac_off[s + 1] = lp.fac_off[s] + (wp == 64 ? np * 32 : np * wp);
+    lp.band_off[s + 1] = lp.band_off[s] + np * wp;
+    lp.cpl_off[s + 1] = lp.cpl_off[s] + 2 * np * lp.cpl_k[s];
+    lp.cpl_kmax = std::max(lp.cpl_kmax, lp.cpl_k[s]);
   }
   return AM_OK;
 }

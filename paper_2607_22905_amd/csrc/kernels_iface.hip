@@ -15,7 +15,9 @@ namespace am {
 
 // ---------------------------------------------------------------------------
 // One wave per interface row n.  Every write to row n comes from lane 0 of
-// that wave, in a fixed order.
+// that wave, in a fixed order.  The diagonal's -sum a_e is folded into the
+// basis function's values, a_e (phat - 1) / 2 per side (exact differences
+// where phat is near 1, instead of sums that cancel).
 __global__ __launch_bounds__(256) void k_assemble_S(
     int NL, int ldS, const int64_t* __restrict__ iface_ptr, const int32_t* __restrict__ iface_ij,
     const int32_t* __restrict__ e_kloc, const int32_t* __restrict__ e_lloc,
@@ -27,9 +29,6 @@ __global__ __launch_bounds__(256) void k_assemble_S(
   if (n >= NL) return;
   const int i = iface_ij[2 * n], j = iface_ij[2 * n + 1];
   const int64_t e0 = iface_ptr[n], e1 = iface_ptr[n + 1];
-  double sa = 0.0;
-  for (int64_t e = e0 + lane; e < e1; e += 64) sa += e_a[e];
-  sa = wave_sum(sa);
   double* Srow = S + (size_t)n * ldS;
   for (int side = 0; side < 2; ++side) {
     const int sd = side == 0 ? i : j;
@@ -41,12 +40,13 @@ __global__ __launch_bounds__(256) void k_assemble_S(
     for (int q = 0; q < nq; ++q) {
       const int m = isub_list[q0 + q];
       double v = 0.0;
-      for (int64_t e = e0 + lane; e < e1; e += 64) v = fma(e_a[e], P[(size_t)q * Ns + loc[e]], v);
+      const double one = m == n ? 1.0 : 0.0;
+      for (int64_t e = e0 + lane; e < e1; e += 64)
+        v = fma(e_a[e], P[(size_t)q * Ns + loc[e]] - one, v);
       v = wave_sum(v);
       if (lane == 0) Srow[m] += 0.5 * v;
     }
   }
-  if (lane == 0) Srow[n] -= sa;
 }
 
 // (S + S^T)/2 on the N_Lambda block; identity on the padding.
@@ -429,6 +429,142 @@ __global__ __launch_bounds__(256) void k_lauum(const double* Li, double* Sinv, i
   });
 }
 
+// One correction step of the explicit inverse where it is small (applied
+// inside the local kernel): X <- X + X (I - S X).  S has the few entries of
+// the basis functions that share a subdomain, so the residual is sparse rows
+// times X, accumulated in twice the working precision; the product with X is
+// one more dense tile product.  The factorization alone leaves an error of
+// the order of cond(S) eps in z (1e-12 on a 100-cell chain, cond(S) 1.5e5;
+// 5e-14 after the step).  Wave: row n, 64 columns.
+__global__ __launch_bounds__(256) void k_sinv_residual(
+    int NL, int ldS, const int32_t* __restrict__ iface_ij, const int64_t* __restrict__ isub_ptr,
+    const int32_t* __restrict__ isub_list, const double* __restrict__ S,
+    const double* __restrict__ X, double* __restrict__ R) {
+#pragma clang fp contract(off)
+  const int lane = threadIdx.x & 63;
+  const int n = blockIdx.y * 4 + (threadIdx.x >> 6), c = blockIdx.x * 64 + lane;
+  if (n >= ldS) return;
+  double hi = (n < NL && n == c) ? 1.0 : 0.0, lo = 0.0;
+  if (n < NL) {
+    const int i = iface_ij[2 * n], j = iface_ij[2 * n + 1];
+    for (int side = 0; side < 2; ++side) {
+      const int sd = side == 0 ? i : j;
+      for (int64_t t = isub_ptr[sd]; t < isub_ptr[sd + 1]; ++t) {
+        const int m = isub_list[t];
+        // basis functions between the same two subdomains are in both lists
+        if (side == 1 && iface_ij[2 * m] == i && iface_ij[2 * m + 1] == j) continue;
+        const double a = S[(size_t)n * ldS + m], x = X[(size_t)m * ldS + c];
+        const double pr = a * x, u = hi - pr, w = u - hi;
+        lo += (hi - (u - w)) - (pr + w);
+        lo -= fma(a, x, -pr);
+        hi = u;
+      }
+    }
+  }
+  R[(size_t)n * ldS + c] = hi + lo;
+}
+
+// out = X + X R (lower tile half, mirrored)
+__global__ __launch_bounds__(256) void k_sinv_correct(const double* X, const double* R,
+                                                      double* __restrict__ out, int ld, int T) {
+  const int j = blockIdx.x, i = blockIdx.y;
+  if (j > i) return;
+  __shared__ Tile As;
+  __shared__ Tile Bs;
+  MfAcc acc;
+  mf_zero(acc);
+  TileRegs ra, rb;
+  tile_fetch(ra, X + (size_t)i * 64 * ld, ld);
+  tile_fetch(rb, R + (size_t)j * 64, ld);
+  for (int k = 0; k < T; ++k) {
+    tile_put(As, ra, false);
+    tile_put(Bs, rb, false);
+    __syncthreads();
+    if (k + 1 < T) {
+      tile_fetch(ra, X + (size_t)i * 64 * ld + (size_t)(k + 1) * 64, ld);
+      tile_fetch(rb, R + (size_t)(k + 1) * 64 * ld + (size_t)j * 64, ld);
+    }
+    mf_mac(acc, As, Bs);
+    __syncthreads();
+  }
+  mf_each(acc, [&](int r, int c, double v) {
+    const size_t gr = (size_t)i * 64 + r, gc = (size_t)j * 64 + c;
+    if (gr < gc) return;
+    const double x = X[gr * ld + gc] + v;
+    out[gr * ld + gc] = x;
+    out[gc * ld + gr] = x;
+  });
+}
+
+// ---------------------------------------------------------------------------
+// eta = S^{-1} b with a small dense S^{-1} (at most 64 MB, resident in the
+// caches), in one launch: a wave forms RW rows, its lanes striding over the
+// columns with a round's loads all issued before the first is used, and sums
+// them by shuffles.  In a solve one more workgroup takes the stop decision.
+// 64^3 (NL = 1344): 4 us; the same rows formed in the local kernel, by its two
+// waves per subdomain, held every subdomain up for 5.6 us, and the four
+// columns of a bisection part's 23 rows for over 100.
+template <int NR>
+__global__ __launch_bounds__(256) void k_eta_dense(int NL, int ldS, const double* __restrict__ Sinv,
+                                                   const double* __restrict__ bpart,
+                                                   double* __restrict__ eta, int pcg, int init,
+                                                   const double* __restrict__ pb, int npb,
+                                                   PcgScalars* sc, PcgShared* sh) {
+  constexpr int RW = NR <= 2 ? 2 : 4;
+  constexpr int UM = NR == 1 ? 6 : NR <= 4 ? 2 : 1;
+  __shared__ double lds[4 * NR];
+  // a solve that stopped earlier (this launch's last workgroup may be writing
+  // the flag: no barrier below, and a stopped solve reads no eta)
+  if (pcg && !init && all_done(sh)) return;
+  if (pcg && blockIdx.x == gridDim.x - 1) {
+    stop_test_wg<NR>(pb, npb, init, sc, sh, lds);
+    return;
+  }
+  const int lane = threadIdx.x & 63;
+  const int r0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * RW;
+  if (r0 >= NL) return;
+  const double* row[RW];
+#pragma unroll
+  for (int r = 0; r < RW; ++r) row[r] = Sinv + (size_t)min(r0 + r, NL - 1) * ldS;
+  double a[RW][NR];
+#pragma unroll
+  for (int r = 0; r < RW; ++r)
+#pragma unroll
+    for (int k = 0; k < NR; ++k) a[r][k] = 0.0;
+  for (int m0 = lane; m0 < NL; m0 += 64 * UM) {
+    double bm[UM][2][NR], sv[UM][RW];
+#pragma unroll
+    for (int u = 0; u < UM; ++u) {
+      const int m = min(m0 + 64 * u, NL - 1);
+#pragma unroll
+      for (int r = 0; r < RW; ++r) sv[u][r] = row[r][m];
+#pragma unroll
+      for (int k = 0; k < NR; ++k) {
+        bm[u][0][k] = bpart[(size_t)(2 * m) * NR + k];
+        bm[u][1][k] = bpart[(size_t)(2 * m + 1) * NR + k];
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < UM; ++u) {
+      const bool ok = m0 + 64 * u < NL;
+#pragma unroll
+      for (int k = 0; k < NR; ++k) {
+        const double b = ok ? bm[u][0][k] + bm[u][1][k] : 0.0;
+#pragma unroll
+        for (int r = 0; r < RW; ++r) a[r][k] = fma(sv[u][r], b, a[r][k]);
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < RW; ++r)
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {
+      const double t = wave_sum(a[r][k]);
+      if (lane == 0 && r0 + r < NL) eta[(size_t)(r0 + r) * NR + k] = t;
+    }
+}
+
 // ---------------------------------------------------------------------------
 // eta = S^{-1} b, b_m = bpart[2m] + bpart[2m+1], as a sum of outer products
 // over the rows of the symmetric S^{-1}: eta[r] = sum_m S^{-1}[m][r] b_m.
@@ -647,7 +783,12 @@ hipError_t dense_cholesky_inverse(DeviceState& d, double* L, double* Li, double*
     }
   }
   hipLaunchKernelGGL(k_lauum, dim3(T, T), dim3(256), 0, st, Li, d.Sinv, ld, T);
-  return hipGetLastError();
+  if (!d.fuse_eta) return hipGetLastError();
+  hipLaunchKernelGGL(k_sinv_residual, dim3(T, ld / 4), dim3(256), 0, st, (int)d.NL, ld, d.iface_ij,
+                     d.isub_ptr, d.isub_list, d.S, d.Sinv, L);
+  hipLaunchKernelGGL(k_sinv_correct, dim3(T, T), dim3(256), 0, st, d.Sinv, L, Li, ld, T);
+  e = hipMemcpyAsync(d.Sinv, Li, sizeof(double) * (size_t)ld * ld, hipMemcpyDeviceToDevice, st);
+  return e != hipSuccess ? e : hipGetLastError();
 }
 
 hipError_t launch_lauum(const double* Li, double* out, int ld, int T, hipStream_t st) {
@@ -671,7 +812,26 @@ static void gemv_t(DeviceState& d, hipStream_t st, int pcg, int init) {
             d.op_parts, d.eta, pcg, init, d.red.pb, d.m, d.sc, d.shared);
 }
 
+template <int NR>
+static void eta_dense_t(DeviceState& d, hipStream_t st, int pcg, int init) {
+  constexpr int rows = 4 * (NR <= 2 ? 2 : 4);
+  const unsigned nb = (unsigned)((d.NL + rows - 1) / rows) + (pcg ? 1 : 0);
+  am_launch(d, true, true, k_eta_dense<NR>, dim3(nb), dim3(256), st, (int)d.NL, d.ldS, d.Sinv,
+            d.bpart, d.eta, pcg, init, d.red.pb, d.m, d.sc, d.shared);
+}
+
 hipError_t launch_iface_gemv(DeviceState& d, int nr, int pcg, int init, hipStream_t st) {
+  if (d.fuse_eta) {
+    switch (nr) {
+      case 1: eta_dense_t<1>(d, st, pcg, init); break;
+      case 2: eta_dense_t<2>(d, st, pcg, init); break;
+      case 4: eta_dense_t<4>(d, st, pcg, init); break;
+      case 8: eta_dense_t<8>(d, st, pcg, init); break;
+      case 16: eta_dense_t<16>(d, st, pcg, init); break;
+      default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+  }
   if (d.NL == 0 && !pcg) return hipSuccess;
   if (d.nd.on) return launch_nd_solve(d, nr, pcg, init, st);
   if (d.ix.on) return launch_ix_solve(d, nr, pcg, init, st);

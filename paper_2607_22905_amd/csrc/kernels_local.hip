@@ -41,7 +41,10 @@ hipError_t launch_invert_diag(DeviceState& d, hipStream_t st) {
   }
 }
 
-int tile_candidates(int nrhs) {
+int tile_candidates(const DeviceState& d, int nrhs) {
+  // the block-inverse kernels (window 64): three layouts up to four columns
+  // (the third differs from the first beyond nine blocks only), one above
+  if (d.bucket_sub[1].empty()) return nrhs > 4 ? 1 : d.max_np0 > 9 * 64 && nrhs != 2 ? 3 : 2;
   switch (tile_slot(nrhs)) {
     case 0: return TileCands<1>::n;
     case 1: return TileCands<2>::n;

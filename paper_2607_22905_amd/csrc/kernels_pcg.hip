@@ -980,7 +980,7 @@ static hipError_t update_xr(DeviceState& d, int nr, int parity, int init, hipStr
 hipError_t launch_pcg_start(DeviceState& d, int nr, hipStream_t s) {
   hipError_t e = update_xr(d, nr, 0, 1, s);
   if (e != hipSuccess) return e;
-  if (!d.fuse_eta) {
+  if (!eta_inline(d, nr)) {
     e = launch_iface_gemv(d, nr, 1, 1, s);
     if (e != hipSuccess) return e;
   }
@@ -1023,7 +1023,7 @@ hipError_t launch_pcg_iteration(DeviceState& d, int nr, int parity, hipStream_t 
   if (e != hipSuccess) return e;
   e = update_xr(d, nr, parity, 0, s);
   if (e != hipSuccess) return e;
-  if (!d.fuse_eta) {
+  if (!eta_inline(d, nr)) {
     e = launch_iface_gemv(d, nr, 1, 0, s);
     if (e != hipSuccess) return e;
   }

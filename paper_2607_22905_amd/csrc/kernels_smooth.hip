@@ -162,7 +162,7 @@ hipError_t launch_smoothed_apply(DeviceState& d, SmoothDevice& sm, const double*
   SM_TRY(gather(n, sm.to_am, t, nullptr, sm.t_am, nr, s));
   if (d.NL > 0) {
     SM_TRY(launch_bpart(d, sm.t_am, nr, s));
-    if (!d.fuse_eta) SM_TRY(launch_iface_gemv(d, nr, 0, 0, s));
+    if (!eta_inline(d, nr)) SM_TRY(launch_iface_gemv(d, nr, 0, 0, s));
   }
   SM_TRY(launch_local_sweep(d, sm.t_am, sm.w_am, d.eta, nr, 1, s));
   SM_TRY(gather(n, sm.to_bj, sm.w_am, nullptr, w, nr, s));

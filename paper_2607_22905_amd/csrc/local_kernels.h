@@ -1,9 +1,12 @@
 // Subdomain kernels for gfx950: the local operators A_i = A_ii - sum_j D_ij
-// (eq. Dij-def, eq. A_i) factored as banded Cholesky A_i = L_i L_i^T
-// (Algorithm 1), the local solves A_i pbar_i = r_i (eq. def-pbar-local,
-// Algorithm 2), the multiscale basis functions A_i phat = -B_i psi
-// (eq. def-phat-local) and the reconstruction z = pbar + sum eta_m phat^(m)
-// (eq. p-decomposition-alg).
+// (eq. Dij-def, eq. A_i), the local solves A_i pbar_i = r_i (eq.
+// def-pbar-local, Algorithm 2), the multiscale basis functions A_i phat =
+// -B_i psi (eq. def-phat-local) and the reconstruction z = pbar + sum eta_m
+// phat^(m) (eq. p-decomposition-alg).  Subdomains whose band fits 64 rows (in
+// the device order) are in tri_kernels.h; here are those of bands of 65 to 128
+// rows, factored as banded Cholesky A_i = L_i L_i^T (Algorithm 1), and the
+// band sweeps of the set-up solves (also of the FP32 / BF16 basis functions of
+// the narrow ones).
 //
 // Layout.  Inside subdomain s the rows are in the device order (a bandwidth-
 // reducing order, see plan_local), padded to NP = 64*ceil(N/64) rows.  With a
@@ -22,6 +25,8 @@
 #include <type_traits>
 
 #include "am_common.h"
+#include "mf_ops.h"
+#include "tri_kernels.h"
 
 namespace am {
 
@@ -876,344 +881,9 @@ __global__ __launch_bounds__(64 * G * W) void k_localt(
     }
 }
 
-// Tile form for 16 right-hand sides on the matrix cores (window 64, interface
-// solve done before the launch).  Each tile pass is a dense 64 x 64 by
-// 64 x 16 product, so the four waves of the workgroup each take 16 rows of
-// the output block and accumulate all 16 right-hand sides over the 64
-// columns: no partial sums cross waves.  FP64 factors use
-// v_mfma_f64_16x16x4f64; FP32 and BF16 factors (widened to FP32 when the
-// tile is staged) use v_mfma_f32_16x16x4f32 with FP32 block vectors, the
-// arithmetic of the vector-unit kernel for those factors.  Both take lane l's
-// operands as A[l % 16][l / 16] and B[l / 16][l % 16]; the FP64 result is
-// D[l / 16 + 4 v][l % 16], the FP32 one D[4 (l / 16) + v][l % 16] (v < 4).
-// With BF16 factors and BFOP, the products are BF16 x BF16 with FP32
-// accumulation instead (v_mfma_f32_16x16x16bf16_1k, the block vectors
-// rounded to BF16; see mf_pass).  The block vectors (64 rows x 16) live in
-// LDS (two buffers, pitch 17); each tile goes through registers (loaded
-// while the previous one is in use) into one LDS buffer.
-//   forward  y_b = t_b + Nlow_b t_b,   out_b = dinv y_b,
-//            t_{b+1} = r_{b+1} - U_b y_b
-//   backward s_b = out_b - U_b^T x_{b+1},   x_b = s_b + Nlow_b^T s_b,
-//            z_b = x_b + sum_q phat_q eta_q   (mode >= 1), PCG dots (mode 2)
-// with Nlow_b the strictly lower part of tile b (the inverted diagonal
-// block) and U_b its upper part with the diagonal (the coupling to block
-// b + 1).
-typedef double am_mf_d4 __attribute__((ext_vector_type(4)));
-typedef float am_mf_f4 __attribute__((ext_vector_type(4)));
-constexpr int kMfVP = 17;  // LDS pitch of a block-vector row (16 values + 1)
-template <typename AT> struct MfAcc;
-template <> struct MfAcc<double> {
-  using V = am_mf_d4;
-  // row of the 16 x 16 result held in element v of a lane with l / 16 = lk
-  static __device__ __forceinline__ int row(int lk, int v) { return lk + 4 * v; }
-};
-template <> struct MfAcc<float> {
-  using V = am_mf_f4;
-  static __device__ __forceinline__ int row(int lk, int v) { return 4 * lk + v; }
-};
-__device__ __forceinline__ am_mf_d4 mf4(double a, double b, am_mf_d4 c) {
-  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ am_mf_f4 mf4(float a, float b, am_mf_f4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
-
-// acc += sum over the 64 columns jj of A[rows][jj] B[jj][.] for a 16-row
-// strip, afn(c, m) and bfn(c, m) giving this lane's operands at column
-// jj = c + m lk (lk = lane / 16, held by the caller), c and m constants of
-// the unrolled loop.  FP64 / FP32 (16x16x4 products): lane holds column 4 kk + lk of
-// step kk; the 16 operand pairs are read from LDS first, then four
-// independent chains of four products (kk = c mod 4 in chain c) are added in
-// chain order.  BF16 (BFOP, FP32 arithmetic type only): four 16x16x16
-// products, lane holding columns 16 c + 4 lk .. 16 c + 4 lk + 3 of step c,
-// both operands rounded to BF16 (the factor values are BF16 already), two
-// chains added in order.
-__device__ __forceinline__ short am_bf16_rne(float x) {
-  uint32_t u = __builtin_bit_cast(uint32_t, x);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (short)(u >> 16);
-}
-typedef short am_mf_s4 __attribute__((ext_vector_type(4)));
-template <bool BFOP, typename V, typename AF, typename BF>
-__device__ __forceinline__ V mf_pass(V acc, AF&& afn, BF&& bfn) {
-  using AT = decltype(afn(0, 0));
-  if constexpr (BFOP) {
-    static_assert(sizeof(AT) == 4, "BF16 products: FP32 arithmetic type");
-    V c[2];
-    c[0] = acc;
-    c[1] = V{0, 0, 0, 0};
-    am_mf_s4 a[4], b[4];
-#pragma unroll
-    for (int st = 0; st < 4; ++st)
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        a[st][t] = am_bf16_rne(afn(16 * st + t, 4));
-        b[st][t] = am_bf16_rne(bfn(16 * st + t, 4));
-      }
-#pragma unroll
-    for (int st = 0; st < 4; ++st)
-      c[st % 2] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[st], b[st], c[st % 2], 0, 0, 0);
-    return c[0] + c[1];
-  } else {
-    V c[4];
-    c[0] = acc;
-#pragma unroll
-    for (int t = 1; t < 4; ++t) c[t] = V{0, 0, 0, 0};
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {  // two halves of 8 operand pairs (registers)
-      AT a[8], b[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        a[u] = afn(4 * (8 * h + u), 1);
-        b[u] = bfn(4 * (8 * h + u), 1);
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) c[u % 4] = mf4(a[u], b[u], c[u % 4]);
-    }
-    return (c[0] + c[1]) + (c[2] + c[3]);
-  }
-}
-
-template <typename FT, int NT, bool BFOP = false>
-__global__ __launch_bounds__(256) void k_localt_mf(
-    const int32_t* __restrict__ subs, const int64_t* __restrict__ sub_ptr,
-    const int64_t* __restrict__ roff, const int64_t* __restrict__ fac_off,
-    const FT* __restrict__ Lc, const typename AccT<FT>::T* __restrict__ dinv, const double* rin,
-    double* out, int mode, const int64_t* __restrict__ isub_ptr,
-    const int32_t* __restrict__ isub_list, const int64_t* __restrict__ mbf_off,
-    const double* __restrict__ mbf, const double* __restrict__ eta, const double* __restrict__ qv,
-    double* __restrict__ partial, unsigned blk_off, PcgShared* sh, int64_t nrows) {
-  // 16 right-hand sides fill the 16 columns of a matrix-core tile; one
-  // right-hand side takes column 0 (lanes of the other columns carry zeros)
-  static_assert(NT == 16 || NT == 1, "one 16-column matrix-core tile");
-  using AT = typename AccT<FT>::T;  // arithmetic type: FP64, else FP32
-  using V = typename MfAcc<AT>::V;
-  constexpr int PITCH = 65;
-  constexpr int CH = 64 * PITCH;
-  constexpr int NTHR = 256;
-  constexpr int VEC = 16 / (int)sizeof(FT);       // factor elements per 16-byte load
-  constexpr int NLD = 64 * 64 / (VEC * NTHR);     // 16-byte loads per thread per tile
-  constexpr int PD = 1;  // one tile ahead in registers (two workgroups per CU)
-  __shared__ AT tile[CH];  // one buffer: two workgroups fit a CU
-  __shared__ AT vb[2][64 * kMfVP];
-  __shared__ AT eta_s[TileMaxNi<NT>::v * NT];
-  __shared__ double dots[4][2 * NT];
-
-  const int s = subs[blockIdx.x];
-  const int64_t base = sub_ptr[s];
-  const int N = (int)(sub_ptr[s + 1] - base);
-  const int64_t ro = roff[s];
-  const int NP = (int)(roff[s + 1] - ro);
-  const int NB = NP / 64;
-  const FT* lc = Lc + fac_off[s];
-  const AT* dv = dinv + ro;
-  const int lane = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int li = lane % 16, lk = lane / 16;
-  const bool colok = li < NT;  // this lane's column is a right-hand side
-  const int64_t i0 = isub_ptr[s];
-  const int ns = mode >= 1 ? (int)(isub_ptr[s + 1] - i0) : 0;
-  const double* P = mbf + mbf_off[s];
-  auto vi = [&](int row, int k) { return vix<NT>(nrows, base + row, k); };
-
-  uint4 pre[PD][NLD];
-  auto tile_load = [&](int b, int slot) {
-    const uint4* src = reinterpret_cast<const uint4*>(lc + (size_t)64 * b * 64);
-#pragma unroll
-    for (int u = 0; u < NLD; ++u) pre[slot][u] = src[u * NTHR + threadIdx.x];
-  };
-  auto tile_store = [&](int slot) {
-#pragma unroll
-    for (int u = 0; u < NLD; ++u) {
-      const int e0 = (u * NTHR + (int)threadIdx.x) * VEC;  // column e0 / 64, rows e0 % 64 ..
-      AT* dst = tile + (e0 / 64) * PITCH + (e0 % 64);
-      FT v[VEC];
-      __builtin_memcpy(v, &pre[slot][u], 16);
-#pragma unroll
-      for (int t = 0; t < VEC; ++t) dst[t] = (AT)widen_lds(v[t]);
-    }
-  };
-  // rows of this lane's part of the D layout
-  auto drow = [&](int v) { return 16 * w + MfAcc<AT>::row(lk, v); };
-
-  tile_load(0, 0);
-  if (mode == 2 && all_done(sh)) return;
-  for (int t = threadIdx.x; t < ns * NT; t += NTHR)
-    eta_s[t] = (AT)eta[(size_t)isub_list[i0 + t / NT] * NT + (t % NT)];
-  tile_store(0);
-  if (1 < NB) tile_load(1, 0);
-  // t_0 = r of block 0 (columns beyond NT: zero)
-  for (int e = threadIdx.x; e < 64 * 16; e += NTHR) {
-    const int row = e / 16, k = e % 16;
-    vb[0][row * kMfVP + k] = (row < N && k < NT) ? (AT)rin[vi(row, k)] : AT(0);
-  }
-  __syncthreads();
-
-  // ---- forward sweep ----
-  auto fwd_body = [&](const int b, auto parc) {
-    constexpr int par = decltype(parc)::v;  // b & 1
-    const int j0 = 64 * b;
-    AT rn[4], dvl[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int row = j0 + 64 + drow(v);
-      rn[v] = (row < N && colok) ? (AT)rin[vi(row, li)] : AT(0);
-      dvl[v] = dv[j0 + drow(v)];
-    }
-    const AT* T = tile;
-    // pass B: y = t + Nlow t
-    V acc;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) acc[v] = vb[0][drow(v) * kMfVP + li];
-    {
-      const int ii = 16 * w + li;
-      acc = mf_pass<BFOP>(
-          acc, [&](int c, int m) { const int jj = c + m * lk; return ii > jj ? T[jj * PITCH + ii] : AT(0); },
-          [&](int c, int m) { const int jj = c + m * lk; return vb[0][jj * kMfVP + li]; });
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      vb[1][drow(v) * kMfVP + li] = acc[v];
-      const int row = j0 + drow(v);
-      if (row < N && colok) out[vi(row, li)] = (double)(acc[v] * dvl[v]);
-    }
-    __syncthreads();
-    // pass A: t_{b+1} = r_{b+1} - U y
-#pragma unroll
-    for (int v = 0; v < 4; ++v) acc[v] = rn[v];
-    {
-      const int ii = 16 * w + li;
-      acc = mf_pass<BFOP>(
-          acc, [&](int c, int m) { const int jj = c + m * lk; return ii <= jj ? -T[jj * PITCH + ii] : AT(0); },
-          [&](int c, int m) { const int jj = c + m * lk; return vb[1][jj * kMfVP + li]; });
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) vb[0][drow(v) * kMfVP + li] = acc[v];
-    __syncthreads();  // every wave is done with tile b
-    if (b + 1 < NB) {
-      tile_store((par + 1) % PD);
-      if (b + 1 + PD < NB) tile_load(b + 1 + PD, (par + 1) % PD);
-      __syncthreads();
-    }
-  };
-  for (int b = 0; b < NB; b += 2) {
-    fwd_body(b, IC<0>{});
-    if (b + 1 < NB) fwd_body(b + 1, IC<1>{});
-  }
-
-  // ---- backward sweep: tile NB-1 is still in LDS ----
-  if (NB > 1) tile_load(NB - 2, 0);
-  // x_{NB} = 0
-  for (int e = threadIdx.x; e < 64 * 16; e += NTHR) vb[1][(e / 16) * kMfVP + e % 16] = AT(0);
-  __syncthreads();
-  double rz = 0.0, qz = 0.0;  // column li of this lane's rows
-  auto bwd_body = [&](const int b, auto parc) {
-    constexpr int par = decltype(parc)::v;  // b & 1
-    const int j0 = 64 * b;
-    const AT* T = tile;
-    AT vv[4];
-    double rp[4], qp[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int row = j0 + drow(v);
-      const bool ok = row < N && colok;
-      vv[v] = ok ? (AT)out[vi(row, li)] : AT(0);
-      rp[v] = (ok && mode == 2) ? rin[vi(row, li)] : 0.0;
-      qp[v] = (ok && mode == 2) ? qv[vi(row, li)] : 0.0;
-    }
-    // basis-function values of this block for the reconstruction, fetched
-    // before the passes: A[row 16 w + li][slot q0 + lk] of z += phat eta
-    constexpr int NPA = 8;  // slots 0..31 fetched ahead, the rest when used
-    const int ra = j0 + 16 * w + li;
-    AT pa[NPA];
-#pragma unroll
-    for (int c = 0; c < NPA; ++c) {
-      const int q = 4 * c + lk;
-      pa[c] = (q < ns && ra < N) ? (AT)P[(size_t)q * N + ra] : AT(0);
-    }
-    // pass A: s = out_b - U^T x_{b+1}
-    V acc;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) acc[v] = vv[v];
-    {
-      const int ii = 16 * w + li;  // output row ii, tile row jj
-      acc = mf_pass<BFOP>(
-          acc, [&](int c, int m) { const int jj = c + m * lk; return jj <= ii ? -T[ii * PITCH + jj] : AT(0); },
-          [&](int c, int m) { const int jj = c + m * lk; return vb[1][jj * kMfVP + li]; });
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) vb[0][drow(v) * kMfVP + li] = acc[v];
-    __syncthreads();
-    // pass B: x = s + Nlow^T s
-    {
-      const int ii = 16 * w + li;
-      acc = mf_pass<BFOP>(
-          acc, [&](int c, int m) { const int jj = c + m * lk; return jj > ii ? T[ii * PITCH + jj] : AT(0); },
-          [&](int c, int m) { const int jj = c + m * lk; return vb[0][jj * kMfVP + li]; });
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) vb[1][drow(v) * kMfVP + li] = acc[v];
-    // z = x + P_b eta on the matrix cores (slots in chunks of 4)
-#pragma unroll
-    for (int c = 0; c < NPA; ++c) {
-      if (4 * c >= ns) break;  // uniform
-      const int q = 4 * c + lk;
-      const AT e = (q < ns && colok) ? eta_s[q * NT + li] : AT(0);
-      acc = mf4(pa[c], e, acc);
-    }
-    for (int c = NPA; 4 * c < ns; ++c) {
-      const int q = 4 * c + lk;
-      const AT av = (q < ns && ra < N) ? (AT)P[(size_t)q * N + ra] : AT(0);
-      const AT e = (q < ns && colok) ? eta_s[q * NT + li] : AT(0);
-      acc = mf4(av, e, acc);
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int row = j0 + drow(v);
-      if (row < N && colok) {
-        const double zv = (double)acc[v];
-        out[vi(row, li)] = zv;
-        rz = fma(rp[v], zv, rz);
-        qz = fma(qp[v], zv, qz);
-      }
-    }
-    __syncthreads();  // every wave is done with tile b
-    if (b > 0) {
-      tile_store((par + 1) % PD);  // tile b - 1
-      if (b - 1 - PD >= 0) tile_load(b - 1 - PD, (par + 1) % PD);
-      __syncthreads();
-    }
-  };
-  {
-    int b = NB - 1;
-    if (b & 1) bwd_body(b--, IC<1>{});
-    for (; b >= 0; b -= 2) {
-      bwd_body(b, IC<0>{});
-      if (b - 1 >= 0) bwd_body(b - 1, IC<1>{});
-    }
-  }
-
-  if (mode != 2) return;
-  // lanes l, l ^ 16, l ^ 32, l ^ 48 hold the same column
-  rz += __shfl_xor(rz, 16, 64);
-  rz += __shfl_xor(rz, 32, 64);
-  qz += __shfl_xor(qz, 16, 64);
-  qz += __shfl_xor(qz, 32, 64);
-  if (lane < NT) {
-    dots[w][lane] = rz;
-    dots[w][NT + lane] = qz;
-  }
-  __syncthreads();
-  if (threadIdx.x < 2 * NT) {
-    double a = 0.0;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) a += dots[u][threadIdx.x];
-    partial[(size_t)(blk_off + blockIdx.x) * 2 * NT + threadIdx.x] = a;
-  }
-}
-
-// The same for window 128 (a bandwidth of 65-128 rows): a column keeps its
+// 16 right-hand sides on the matrix cores, window 128 (a bandwidth of 65-128
+// rows; four waves, each 16 output rows over all 64 columns; operands and
+// results as in mf_ops.h): a column keeps its
 // 128 band entries in a ring of two 64-row chunks, so that in tile b the
 // chunk b & 1 holds the rows of block b (strictly lower part: the inverted
 // diagonal block; upper part with the diagonal: the coupling L_{b+2,b} to
@@ -1503,57 +1173,67 @@ __global__ __launch_bounds__(256) void k_bpart(int64_t n, const int64_t* __restr
 // ---------------------------------------------------------------------------
 // launcher templates (instantiated once per factor precision)
 
+// local operators of both window buckets: the block inverses and couplings
+// (window 64), the band factors (window 128)
 template <typename FT>
 hipError_t band_factor_t(DeviceState& d, hipStream_t st) {
   using IT = typename AccT<FT>::T;
-  for (int bk = 0; bk < 2; ++bk) {
-    const int nb = (int)d.bucket_sub[bk].size();
-    if (!nb) continue;
-    if (bk == 0)
-      hipLaunchKernelGGL((k_band_factor<FT, 64>), dim3(nb), dim3(256), 0, st,
-                         d.d_bucket_sub[bk], d.sub_ptr, d.roff, d.fac_off, d.prp, d.pci, d.pv,
-                         (FT*)d.Lc, (FT*)d.Lr, (IT*)d.invd, d.fail, d.plain);
-    else
-      hipLaunchKernelGGL((k_band_factor<FT, 128>), dim3(nb), dim3(256), 0, st,
-                         d.d_bucket_sub[bk], d.sub_ptr, d.roff, d.fac_off, d.prp, d.pci, d.pv,
-                         (FT*)d.Lc, (FT*)d.Lr, (IT*)d.invd, d.fail, d.plain);
+  const int nb0 = (int)d.bucket_sub[0].size(), nb1 = (int)d.bucket_sub[1].size();
+  if (nb0) {
+    hipLaunchKernelGGL((k_tri_couplings<FT>), dim3(nb0), dim3(256), 0, st, d.d_bucket_sub[0],
+                       d.sub_ptr, d.roff, d.cpl_off, d.cpl_k, d.prp, d.pci, d.pv, (IT*)d.cpl,
+                       d.cidx);
+    hipLaunchKernelGGL((k_tri_factor<FT>), dim3(nb0), dim3(512), 0, st, d.d_bucket_sub[0],
+                       d.sub_ptr, d.roff, d.fac_off, d.prp, d.pci, d.pv, (FT*)d.Lc, (IT*)d.invd,
+                       d.fail, d.plain);
+    if (d.Bc)
+      hipLaunchKernelGGL((k_band_factor<FT, 64>), dim3(nb0), dim3(256), 0, st, d.d_bucket_sub[0],
+                         d.sub_ptr, d.roff, d.band_off, d.prp, d.pci, d.pv, (FT*)d.Bc, (FT*)d.Br,
+                         (IT*)d.Bd, d.fail, d.plain);
   }
+  if (nb1)
+    hipLaunchKernelGGL((k_band_factor<FT, 128>), dim3(nb1), dim3(256), 0, st, d.d_bucket_sub[1],
+                       d.sub_ptr, d.roff, d.fac_off, d.prp, d.pci, d.pv, (FT*)d.Lc, (FT*)d.Lr,
+                       (IT*)d.invd, d.fail, d.plain);
   return hipGetLastError();
 }
 
 template <typename FT>
 hipError_t mbf_t(DeviceState& d, hipStream_t st) {
   using IT = typename AccT<FT>::T;
-  for (int bk = 0; bk < 2; ++bk) {
-    const int nb = (int)d.bucket_pair[bk].size();
-    if (!nb) continue;
-    if (bk == 0)
-      hipLaunchKernelGGL((k_mbf<FT, 1>), dim3(nb), dim3(64), 0, st, d.d_bucket_pair[bk],
-                         d.mbf_pair_sub, d.mbf_pair_q, d.sub_ptr, d.roff, d.fac_off,
-                         (const FT*)d.Lc, (const FT*)d.Lr, (const IT*)d.invd, d.mbf_off, d.mbf,
+  const int nb0 = (int)d.bucket_pair[0].size(), nb1 = (int)d.bucket_pair[1].size();
+  if (nb0) {
+    if constexpr (sizeof(FT) == 8) {
+      // the vector of a subdomain of up to 4096 rows in LDS
+      const bool chip = d.max_np0 <= 4096;
+      auto kern = chip ? &k_tri_mbf<true> : &k_tri_mbf<false>;
+      hipLaunchKernelGGL(kern, dim3(nb0), dim3(64), chip ? d.max_np0 * sizeof(double) : 0, st,
+                         d.d_bucket_pair[0], d.mbf_pair_sub, d.mbf_pair_q, d.desc, (const FT*)d.Lc,
+                         (const IT*)d.invd, (const IT*)d.cpl, d.cidx, d.prp, d.pci, d.pv, d.mbf,
+                         d.bw_ptr, d.bw_row, d.bw_val, d.plain);
+    } else {
+      // reduced precision: the basis functions define the coarse space, and
+      // those of the band sweeps in FT arithmetic are kept
+      hipLaunchKernelGGL((k_mbf<FT, 1>), dim3(nb0), dim3(64), 0, st, d.d_bucket_pair[0],
+                         d.mbf_pair_sub, d.mbf_pair_q, d.sub_ptr, d.roff, d.band_off,
+                         (const FT*)d.Bc, (const FT*)d.Br, (const IT*)d.Bd, d.mbf_off, d.mbf,
                          d.bw_ptr, d.bw_row, d.bw_val);
-    else
-      hipLaunchKernelGGL((k_mbf<FT, 2>), dim3(nb), dim3(64), 0, st, d.d_bucket_pair[bk],
-                         d.mbf_pair_sub, d.mbf_pair_q, d.sub_ptr, d.roff, d.fac_off,
-                         (const FT*)d.Lc, (const FT*)d.Lr, (const IT*)d.invd, d.mbf_off, d.mbf,
-                         d.bw_ptr, d.bw_row, d.bw_val);
+    }
   }
+  if (nb1)
+    hipLaunchKernelGGL((k_mbf<FT, 2>), dim3(nb1), dim3(64), 0, st, d.d_bucket_pair[1],
+                       d.mbf_pair_sub, d.mbf_pair_q, d.sub_ptr, d.roff, d.fac_off,
+                       (const FT*)d.Lc, (const FT*)d.Lr, (const IT*)d.invd, d.mbf_off, d.mbf,
+                       d.bw_ptr, d.bw_row, d.bw_val);
   return hipGetLastError();
 }
 
 template <typename FT>
 hipError_t invert_diag_t(DeviceState& d, hipStream_t st) {
-  for (int bk = 0; bk < 2; ++bk) {
-    const int nb = (int)d.bucket_sub[bk].size();
-    if (!nb) continue;
-    const dim3 grid(nb, (unsigned)((d.max_np + 63) / 64));
-    if (bk == 0)
-      hipLaunchKernelGGL((k_invert_diag<FT, 1>), grid, dim3(64), 0, st, d.d_bucket_sub[bk], d.roff,
-                         d.fac_off, (FT*)d.Lc);
-    else
-      hipLaunchKernelGGL((k_invert_diag<FT, 2>), grid, dim3(64), 0, st, d.d_bucket_sub[bk], d.roff,
-                         d.fac_off, (FT*)d.Lc);
-  }
+  const int nb1 = (int)d.bucket_sub[1].size();
+  if (nb1)
+    hipLaunchKernelGGL((k_invert_diag<FT, 2>), dim3(nb1, (unsigned)((d.max_np + 63) / 64)),
+                       dim3(64), 0, st, d.d_bucket_sub[1], d.roff, d.fac_off, (FT*)d.Lc);
   return hipGetLastError();
 }
 
@@ -1609,6 +1289,7 @@ template <typename FT, int NT, int I>
 hipError_t localt_shape(DeviceState& d, const double* r, double* z, const double* eta, int mode,
                         int init, hipStream_t st) {
   using IT = typename AccT<FT>::T;
+  const int inl = eta_inline(d, NT);  // eta rows in the local kernel
   const int nb0 = (int)d.bucket_sub[0].size(), nb1 = (int)d.bucket_sub[1].size();
   // With both window buckets populated, the window-128 bucket (few, long
   // workgroups) runs on a second stream beside the window-64 one: a fork and
@@ -1619,58 +1300,64 @@ hipError_t localt_shape(DeviceState& d, const double* r, double* z, const double
   auto launch_bucket = [&](int bk, hipStream_t s, bool first, bool last) {
     const int nb = bk == 0 ? nb0 : nb1;
     const unsigned off = bk == 0 ? 0u : (unsigned)nb0;  // rows of the partials
-    // bucket 0 lists 0 .. m-1 in order when bucket 1 is empty: the kernel
-    // then takes its subdomain from blockIdx.x (one dependent load less)
-    const int32_t* subs_arg = (bk == 0 && nb1 == 0) ? nullptr : d.d_bucket_sub[bk];
-    auto go = [&](auto kern, int threads) {
-      am_launch(d, first, last, kern, dim3(nb), dim3(threads), s,
-                subs_arg, d.sub_ptr, d.roff, d.fac_off, (const FT*)d.Lc,
-                (const IT*)d.invd, r, z, mode, d.isub_ptr, d.isub_list, d.mbf_off, d.mbf, eta,
-                d.q, d.red.pd, off, d.fuse_eta, d.Sinv, (int)d.NL, d.ldS, d.bpart, d.red.pb, d.m,
-                init, d.sc, d.shared, d.n);
-    };
-    // the matrix-core kernels of 16 columns (BF16 x BF16 products on request)
-    auto go_mf = [&](auto kern) {
-      am_launch(d, first, last, kern, dim3(nb), dim3(256), s, d.d_bucket_sub[bk], d.sub_ptr,
-                d.roff, d.fac_off, (const FT*)d.Lc, (const IT*)d.invd, r, z, mode, d.isub_ptr,
-                d.isub_list, d.mbf_off, d.mbf, eta, d.q, d.red.pd, off, d.shared, d.n);
-    };
     constexpr bool kBf = std::is_same<FT, bf16_t>::value;
     if (bk == 0) {
-      using S = TileAt<FT, 1, NT, I>;
-      bool mf = false;
-      if constexpr (NT == 16) {
-        if (!d.fuse_eta) {
-          mf = true;
-          if (kBf && d.bf16_ops)
-            go_mf(k_localt_mf<FT, 16, kBf>);
-          else
-            go_mf(k_localt_mf<FT, 16, false>);
+      // bucket 0 lists 0 .. m-1 in order when bucket 1 is empty: the kernel
+      // then takes its subdomain from blockIdx.x (one dependent load less)
+      const int32_t* subs_arg = nb1 == 0 ? nullptr : d.d_bucket_sub[0];
+      auto go = [&](auto kern, int threads, size_t lds, auto... tail) {
+        am_launch_shm(d, first, last, kern, dim3(nb), dim3(threads), lds, s, subs_arg, d.desc,
+                      (const FT*)d.Lc, (const IT*)d.invd, (const IT*)d.cpl, d.cidx, r, z, mode,
+                      d.isub_list, d.mbf, eta, d.q, d.red.pd, off, inl, d.Sinv, (int)d.NL, d.ldS,
+                      d.bpart, d.red.pb, d.m, init, d.sc, d.shared, tail...);
+      };
+      if constexpr (NT >= 8) {
+        const size_t lds = (size_t)d.max_ni * NT * sizeof(double);
+        static_assert(tri_mf_lds<IT>() + 64 * NT * 8 <= 80 * 1024, "two workgroups per CU");
+        if (kBf && NT == 16 && !inl && d.bf16_ops)
+          go(k_tri_mf<FT, NT, kBf>, 256, lds);
+        else
+          go(k_tri_mf<FT, NT, false>, 256, lds);
+      } else {
+        // tiles per half kept in registers: candidate 0 four (subdomains of
+        // up to nine blocks whole), 1 two (more workgroups per CU, the outer
+        // tiles read twice), 2 six (up to thirteen blocks)
+        constexpr int HT = I == 1 ? 2 : I == 2 ? 6 : 4;
+        // one right-hand side with BF16 x BF16 products, where every
+        // subdomain is in this bucket
+        if constexpr (NT == 1 && kBf && I == 0) {
+          if (!inl && d.bf16_ops && nb1 == 0) {
+            go(k_tri_solve<FT, 1, HT, true>, 128, 0);
+            return;
+          }
         }
+        go(k_tri_solve<FT, NT, HT>, 128, 0);
       }
-      // one right-hand side with BF16 x BF16 products: column 0 of the
-      // matrix-core tiles, where every subdomain is in the window-64 bucket
-      if constexpr (NT == 1 && kBf) {
-        if (!d.fuse_eta && d.bf16_ops && nb1 == 0) {
-          mf = true;
-          go_mf(k_localt_mf<FT, 1, true>);
-        }
-      }
-      if (!mf) go(k_localt<FT, 1, NT, S::G, S::W>, 64 * S::G * S::W);
-    } else {
-      using S = TileAt<FT, 2, NT, I>;
-      bool mf = false;
-      if constexpr (NT == 16) {
-        if (!d.fuse_eta) {
-          mf = true;
-          if (kBf && d.bf16_ops)
-            go_mf(k_localt_mf2<FT, 16, kBf>);
-          else
-            go_mf(k_localt_mf2<FT, 16, false>);
-        }
-      }
-      if (!mf) go(k_localt<FT, 2, NT, S::G, S::W>, 64 * S::G * S::W);
+      return;
     }
+    auto go = [&](auto kern, int threads) {
+      am_launch(d, first, last, kern, dim3(nb), dim3(threads), s, d.d_bucket_sub[1], d.sub_ptr,
+                d.roff, d.fac_off, (const FT*)d.Lc, (const IT*)d.invd, r, z, mode, d.isub_ptr,
+                d.isub_list, d.mbf_off, d.mbf, eta, d.q, d.red.pd, off, inl, d.Sinv,
+                (int)d.NL, d.ldS, d.bpart, d.red.pb, d.m, init, d.sc, d.shared, d.n);
+    };
+    using S = TileAt<FT, 2, NT, I>;
+    // the matrix-core kernel of 16 columns (BF16 x BF16 products on request)
+    if constexpr (NT == 16) {
+      if (!inl) {
+        auto go_mf = [&](auto kern) {
+          am_launch(d, first, last, kern, dim3(nb), dim3(256), s, d.d_bucket_sub[1], d.sub_ptr,
+                    d.roff, d.fac_off, (const FT*)d.Lc, (const IT*)d.invd, r, z, mode, d.isub_ptr,
+                    d.isub_list, d.mbf_off, d.mbf, eta, d.q, d.red.pd, off, d.shared, d.n);
+        };
+        if (kBf && d.bf16_ops)
+          go_mf(k_localt_mf2<FT, 16, kBf>);
+        else
+          go_mf(k_localt_mf2<FT, 16, false>);
+        return;
+      }
+    }
+    go(k_localt<FT, 2, NT, S::G, S::W>, 64 * S::G * S::W);
   };
   if (fork) {
     const hipEvent_t p0 = d.prof_ev[0], p1 = d.prof_ev[1];
