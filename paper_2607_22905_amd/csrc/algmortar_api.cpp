@@ -267,20 +267,23 @@ static hipError_t nd_upload(DeviceState& d, const IfaceND& ndh, hipStream_t sm) 
   nd.nrows = ndh.nrows;
   nd.R = (int32_t)ndh.ntop;
   nd.ldC = (int32_t)((ndh.ntop + 63) / 64 * 64);
-  nd.ldp = (int32_t)ndh.ld;
   nd.h_blk_off = ndh.blk_off;
   nd.h_pad_off = ndh.pad_off;
   // padded position -> basis function
-  nd.h_src.assign((size_t)nd.ldp, -1);
+  nd.h_src.assign((size_t)ndh.ld, -1);
   for (int b = 0; b < nd.nblk; ++b)
     for (int64_t r = ndh.blk_off[b]; r < ndh.blk_off[b + 1]; ++r)
       nd.h_src[ndh.pad_off[b] + (r - ndh.blk_off[b])] = ndh.order[r];
   for (int64_t t = 0; t < ndh.ntop; ++t) nd.h_src[ndh.pad_off[nd.nblk] + t] = ndh.order[nd.nrows + t];
   std::vector<int64_t> inv_off(nd.nblk + 1, 0);
-  std::vector<int32_t> wg_blk, wg_row0;
+  std::vector<int64_t> moff(nd.nblk + 1, 0);
+  std::vector<int32_t> wg_blk, wg_row0, tiles;
   for (int b = 0; b < nd.nblk; ++b) {
-    const int64_t sb = ndh.blk_off[b + 1] - ndh.blk_off[b];
+    const int64_t sb = ndh.blk_off[b + 1] - ndh.blk_off[b], pb = (sb + 63) / 64 * 64;
     inv_off[b + 1] = inv_off[b] + sb * sb;
+    moff[b + 1] = moff[b] + pb * pb;
+    tiles.push_back((int32_t)(pb / 64));
+    nd.tmax = std::max(nd.tmax, tiles.back());
     nd.smax = std::max(nd.smax, sb);
     for (int64_t r0 = 0; r0 < sb; r0 += 64) {
       wg_blk.push_back(b);
@@ -288,6 +291,7 @@ static hipError_t nd_upload(DeviceState& d, const IfaceND& ndh, hipStream_t sm) 
     }
   }
   nd.nwg = (int32_t)wg_blk.size();
+  nd.mrows = moff[nd.nblk];
   // row parts of the top product: about 2048 waves, at most what the
   // kernels keep in LDS
   const int64_t cap = nd_max_rows(d.max_nrhs);
@@ -308,6 +312,10 @@ static hipError_t nd_upload(DeviceState& d, const IfaceND& ndh, hipStream_t sm) 
   std::vector<int32_t> t_pos(ndh.t_pos.begin(), ndh.t_pos.end());
   std::vector<int32_t> b_top(ndh.b_top.begin(), ndh.b_top.end());
   std::vector<int32_t> t_ri(t_pos.size()), t_ci(t_pos.size()), b_ri(b_top.size()), b_ci(b_top.size());
+  std::vector<int32_t> t_blk(t_pos.size());
+  for (size_t q = 0; q < t_pos.size(); ++q)
+    t_blk[q] = (int32_t)(std::upper_bound(ndh.blk_off.begin(), ndh.blk_off.end(), (int64_t)t_pos[q]) -
+                         ndh.blk_off.begin() - 1);
   for (int64_t t = 0; t < ndh.ntop; ++t)
     for (int64_t q = ndh.t_ptr[t]; q < ndh.t_ptr[t + 1]; ++q) {
       t_ri[q] = ord[nd.nrows + t];
@@ -324,14 +332,16 @@ static hipError_t nd_upload(DeviceState& d, const IfaceND& ndh, hipStream_t sm) 
 #define NDUP(p, v)                              \
   if ((e = upload(al, &(p), (v), sm)) != hipSuccess) return e
   NDUP(nd.ord, ord);
-  NDUP(nd.src, nd.h_src);
   NDUP(nd.blk_off, ndh.blk_off);
   NDUP(nd.pad_off, ndh.pad_off);
   NDUP(nd.inv_off, inv_off);
+  NDUP(nd.moff, moff);
+  NDUP(nd.tiles, tiles);
   NDUP(nd.wg_blk, wg_blk);
   NDUP(nd.wg_row0, wg_row0);
   NDUP(nd.t_ptr, ndh.t_ptr);
   NDUP(nd.t_pos, t_pos);
+  NDUP(nd.t_blk, t_blk);
   NDUP(nd.t_ri, t_ri);
   NDUP(nd.t_ci, t_ci);
   NDUP(nd.b_ptr, ndh.b_ptr);
@@ -411,24 +421,17 @@ static hipError_t ix_upload(DeviceState& d, const Structure& st, hipStream_t sm)
 // the temporaries are allocated and freed here.  Synchronizes `st`.
 static hipError_t interface_inverse(DeviceState& d, hipStream_t st) {
   if (d.NL <= 0) return hipSuccess;
-  const int64_t ld = d.nd.on ? d.nd.ldp : d.ldS;
-  const size_t nS = (size_t)ld * ld;
-  const int64_t ptiles = trtri_part_tiles((int)(ld / 64));
-  double *L = nullptr, *Li = nullptr, *part = nullptr, *Sp = nullptr;
-  hipError_t he = hipMalloc((void**)&L, nS * sizeof(double));
-  if (he == hipSuccess) he = hipMalloc((void**)&Li, nS * sizeof(double));
-  if (he == hipSuccess && ptiles > 0) he = hipMalloc((void**)&part, (size_t)ptiles * 4096 * sizeof(double));
-  if (he == hipSuccess && (d.nd.on || d.ix.on)) he = hipMalloc((void**)&Sp, nS * sizeof(double));
+  const int64_t nS = (int64_t)d.ldS * d.ldS;
+  const int64_t cnt = d.nd.on ? nd_scratch(d.nd) : (d.ix.on ? 3 : 2) * nS + 8192;
+  double* t = nullptr;
+  hipError_t he = hipMalloc((void**)&t, (size_t)cnt * sizeof(double));
   if (he == hipSuccess)
-    he = d.nd.on   ? nd_numeric(d, Sp, L, Li, part, st)
-         : d.ix.on ? ix_numeric(d, Sp, L, Li, part, st)
-                   : dense_cholesky_inverse(d, L, Li, part, st);
+    he = d.nd.on   ? nd_numeric(d, t, st)
+         : d.ix.on ? ix_numeric(d, t + 2 * nS + 8192, t, t + nS, t + 2 * nS, st)
+                   : dense_inverse(d, d.S, t, t + nS, t + 2 * nS, d.Sinv, st);
   const hipError_t he2 = hipStreamSynchronize(st);
   if (he == hipSuccess) he = he2;
-  (void)hipFree(L);
-  (void)hipFree(Li);
-  (void)hipFree(part);
-  (void)hipFree(Sp);
+  (void)hipFree(t);
   return he;
 }
 
@@ -799,7 +802,6 @@ static am_status setup_impl(const am_csr* A, const int32_t* part, int32_t nparts
   SCHK(dalloc(al, &d.S, nS));
   if (use_nd) {
     SCHK(nd_upload(d, ndh, sm));
-    SCHK(dalloc(al, &d.Sinv, (size_t)d.nd.ldp * d.nd.ldp));  // reordered S^{-1}
   } else {
     SCHK(dalloc(al, &d.Sinv, nS));
   }
@@ -1804,15 +1806,17 @@ am_status algmortar_export_interface(am_handle h, int32_t which, double* out) {
   DeviceState& d = h->d;
   if (d.NL == 0) return AM_OK;
   HCHK(hipSetDevice(d.device));
-  if (which == 1 && d.nd.on) {  // the reordered inverse of the dissection form
-    const int64_t ldp = d.nd.ldp;
-    std::vector<double> tmp((size_t)ldp * ldp);
-    HCHK(hipMemcpy(tmp.data(), d.Sinv, sizeof(double) * tmp.size(), hipMemcpyDeviceToHost));
-    std::vector<int64_t> pos((size_t)d.NL);
-    for (int64_t a = 0; a < ldp; ++a)
-      if (d.nd.h_src[a] >= 0) pos[d.nd.h_src[a]] = a;
-    for (int64_t i = 0; i < d.NL; ++i)
-      for (int64_t j = 0; j < d.NL; ++j) out[i * d.NL + j] = tmp[(size_t)pos[i] * ldp + pos[j]];
+  const int64_t nS = (int64_t)d.ldS * d.ldS;
+  if (which == 1 && d.nd.on) {  // not kept by the dissection form: formed here
+    double* t = nullptr;
+    HCHK(hipMalloc((void**)&t, (size_t)(3 * nS + 8192) * sizeof(double)));
+    hipError_t he = dense_inverse(d, d.S, t + nS, t + 2 * nS, t + 3 * nS, t, h->own);
+    if (he == hipSuccess) he = hipStreamSynchronize(h->own);
+    if (he == hipSuccess)
+      he = hipMemcpy2D(out, sizeof(double) * d.NL, t, sizeof(double) * d.ldS, sizeof(double) * d.NL,
+                       d.NL, hipMemcpyDeviceToHost);
+    (void)hipFree(t);
+    HCHK(he);
     return AM_OK;
   }
   const double* src = which == 0 ? d.S : d.Sinv;

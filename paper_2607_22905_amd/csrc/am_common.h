@@ -323,4 +323,56 @@ __device__ __forceinline__ void bpart_sub(int s, int64_t n, const int64_t* __res
   }
 }
 
+// ---------------------------------------------------------------------------
+// Inverse of a symmetric positive definite 64 x 64 block by the symmetric sweep
+// over its 64 pivots (row and column k divided by the pivot, the rest reduced
+// by the rank-one product): 256 threads (tid), each with the 4 x 4 piece at
+// (4 (tid / 16), 4 (tid % 16)) in x, which ends as minus the inverse.  The
+// pivot row goes through one of two LDS rows prow: one barrier per pivot,
+// taken by every thread of the workgroup, act or not (act: whether this group
+// of 256 has a block).  bad(k) is called by one thread for a pivot that is not
+// positive (taken as 1).  Bound by the chain of 64 barriers and divisions,
+// about 25 us.
+template <typename F>
+__device__ __forceinline__ void sweep_inverse_64(double (&x)[4][4], double (*prow)[64], int tid,
+                                                 bool act, F&& bad) {
+  const int i0 = 4 * (tid / 16), j0 = 4 * (tid % 16);
+  if (act && i0 == 0)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) prow[0][j0 + c] = x[0][c];
+  __syncthreads();
+  for (int k4 = 0; k4 < 64; k4 += 4) {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      const int k = k4 + kk;
+      if (act) {
+        const double* pr = prow[kk & 1];
+        const double d = pr[k];
+        const bool no = !(d > 0.0) || !(d < 1.0e300);
+        const double rd = no ? 1.0 : 1.0 / d;
+        if (tid == 0 && no) bad(k);
+        double pi[4], pj[4];
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+          pi[a] = pr[i0 + a];
+          pj[a] = pr[j0 + a];
+        }
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            const bool ik = i0 + a == k, jk = j0 + c == k;
+            const double gen = fma(-(pi[a] * rd), pj[c], x[a][c]);
+            x[a][c] = ik ? (jk ? -rd : pj[c] * rd) : (jk ? pi[a] * rd : gen);
+          }
+        // the next pivot row, from the threads that hold it
+        if (k + 1 < 64 && i0 == ((k + 1) & ~3))
+#pragma unroll
+          for (int c = 0; c < 4; ++c) prow[(kk + 1) & 1][j0 + c] = x[(kk + 1) & 3][c];
+      }
+      __syncthreads();
+    }
+  }
+}
+
 }  // namespace am

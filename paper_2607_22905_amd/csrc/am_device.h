@@ -66,18 +66,20 @@ struct NdDevice {
   int64_t nrows = 0;       // rows in blocks
   int32_t R = 0;           // top rows
   int32_t ldC = 0;         // leading dimension of C^{-1} (R rounded up to 64)
-  int32_t ldp = 0;         // padded dimension of the reordered S
   int32_t nwg = 0;         // workgroups of k_nd_blocks
   int64_t smax = 0;        // rows of the largest block
   int32_t P = 1, per = 1;  // row parts of k_nd_top and rows per part
   int64_t nt_pairs = 0, nb_pairs = 0;
   std::vector<int64_t> h_blk_off, h_pad_off;  // host copies
-  std::vector<int32_t> h_src;
+  std::vector<int32_t> h_src;  // padded position -> basis function, -1 on padding
   int32_t* ord = nullptr;      // [NL] ND position -> basis function (top rows last)
-  int32_t* src = nullptr;      // [ldp] padded position -> basis function, -1 on padding
   int64_t* blk_off = nullptr;  // [nblk+1]
-  int64_t* pad_off = nullptr;  // [nblk+1]
+  int64_t* pad_off = nullptr;  // [nblk+1] their first padded positions (64-row aligned)
   int64_t* inv_off = nullptr;  // [nblk+1] offsets of the block inverses (full squares)
+  int64_t mrows = 0;           // doubles of the padded block matrices (set-up)
+  int32_t tmax = 0;            // tiles a side of the largest block
+  int64_t* moff = nullptr;     // [nblk+1] their offsets
+  int32_t* tiles = nullptr;    // [nblk] tiles a side
   int32_t* wg_blk = nullptr;   // [nwg] block of each workgroup ..
   int32_t* wg_row0 = nullptr;  // .. and its first row
   double* binv = nullptr;      // block inverses
@@ -86,6 +88,7 @@ struct NdDevice {
   int32_t* t_pos = nullptr;    //   ND positions of those rows
   double* t_val = nullptr;     //   S values
   int32_t *t_ri = nullptr, *t_ci = nullptr;  // (row, column) of each value in S (set-up)
+  int32_t* t_blk = nullptr;    //   blocks of those rows (set-up)
   int64_t* b_ptr = nullptr;    // [nrows+1] block row -> couplings to top rows
   int32_t* b_top = nullptr;    //   top indices
   double* b_val = nullptr;
@@ -274,34 +277,43 @@ inline bool eta_inline(const DeviceState& d, int nr) {
 
 // ---- launchers (kernels_iface.hip) ----
 hipError_t launch_assemble_S(DeviceState& d, hipStream_t s);
-// S^{-1} through the tiled Cholesky factor L and its inverse Linv (both
-// ldS x ldS scratch); part: trtri_part_tiles(ldS / 64) tiles of 64 x 64
-// scratch for the split launches of the inverse (may be null if that is 0)
-int64_t trtri_part_tiles(int T);
-hipError_t dense_cholesky_inverse(DeviceState& d, double* L, double* Linv, double* part,
-                                  hipStream_t s);
+// Minus the inverses of nmat symmetric positive definite matrices of T[z] 64 x
+// 64 tiles a side, at m0 + moff[z] (nmat 1: moff, T null, Tmax tiles), lower
+// tiles, left in m0 (T even) or m1 (T odd); Dbuf: 8192 doubles per matrix.  A
+// pivot that is not positive is recorded in fail[0] as row rowbase[z] + r (the
+// smallest).
+hipError_t sweep_inverse(double* m0, double* m1, const int64_t* moff, const int32_t* T, int nmat,
+                         int Tmax, double* Dbuf, const int64_t* rowbase, int64_t rowbase0,
+                         int32_t* fail, hipStream_t s);
+// the full symmetric inverses from it: matrix z to out + ooff[z], its first
+// nrow_off[z + 1] - nrow_off[z] rows and columns (one matrix: nrow0 rows of
+// leading dimension ldo0, zero beyond nrow0 columns)
+hipError_t sweep_output(const double* m0, const double* m1, const int64_t* moff, const int32_t* T,
+                        int nmat, int Tmax, double* out, const int64_t* ooff,
+                        const int64_t* nrow_off, int nrow0, int ldo0, hipStream_t s);
+// out = S^{-1} for a matrix of the size of d.S (m0, m1: ldS x ldS scratch),
+// corrected once where it is applied as a small dense matrix (fuse_eta)
+hipError_t dense_inverse(DeviceState& d, const double* S, double* m0, double* m1, double* Dbuf,
+                         double* out, hipStream_t s);
 // eta = S^{-1} b; in PCG mode (pcg != 0) the launch first applies the stop
 // test to the ||r||^2 partials (init: records ||b||^2)
 hipError_t launch_iface_gemv(DeviceState& d, int nrhs, int pcg, int init, hipStream_t s);
-// out = Li^T Li over a T x T tile block (Li lower triangular, leading
-// dimension ld; both pointers at the block's first entry)
-hipError_t launch_lauum(const double* Li, double* out, int ld, int T, hipStream_t s);
-
 // ---- launchers (kernels_nd.hip) ----
 // largest block (rows) the nested-dissection kernels take for nr_max columns
 int64_t nd_max_rows(int nr_max);
 // eta = S^{-1} b by the nested-dissection block elimination (same contract
 // as launch_iface_gemv)
 hipError_t launch_nd_solve(DeviceState& d, int nrhs, int pcg, int init, hipStream_t s);
-// set-up: block inverses, C^{-1} and coupling values from d.S (see kernels_nd.hip)
-hipError_t nd_numeric(DeviceState& d, double* Sp, double* L, double* Li, double* part,
-                      hipStream_t s);
+// set-up: block inverses, C^{-1} and coupling values from d.S (see
+// kernels_nd.hip); scratch of nd_scratch(d.nd) doubles
+int64_t nd_scratch(const NdDevice& nd);
+hipError_t nd_numeric(DeviceState& d, double* scratch, hipStream_t s);
 
 // ---- launchers (kernels_inexact.hip) ----
 // eta ~ S^{-1} b by block-Jacobi PCG (same contract as launch_iface_gemv)
 hipError_t launch_ix_solve(DeviceState& d, int nrhs, int pcg, int init, hipStream_t s);
 // set-up: block inverses and the ELL values of S (see kernels_inexact.hip)
-hipError_t ix_numeric(DeviceState& d, double* Sbd, double* L, double* Li, double* part,
+hipError_t ix_numeric(DeviceState& d, double* Sbd, double* m0, double* m1, double* Dbuf,
                       hipStream_t s);
 
 // ---- launchers (kernels_pcg.hip) ----

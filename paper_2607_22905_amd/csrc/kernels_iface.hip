@@ -1,8 +1,8 @@
 // Interface kernels for gfx950: assembly of the interface matrix
 //   S[n, m] = -delta_nm sum_{e in E_n} a_e + sum_{e in E_n} a_e (phat^(m)_k + phat^(m)_l)/2
 // (eq. interface-problem-alg with the sign of Corollary eq. k-schur), its
-// symmetrisation, an FP64 tiled Cholesky S = L L^T followed by the explicit
-// inverse S^{-1} = L^{-T} L^{-1}, and the per-apply interface solve
+// symmetrisation, explicit inverses by a tiled symmetric sweep, and the
+// per-apply interface solve
 // eta = S^{-1} b as a dense GEMV/GEMM (Algorithm 2).
 //
 // Dense tiles are 64 x 64, row-major with leading dimension ldS (a multiple
@@ -69,16 +69,6 @@ __global__ __launch_bounds__(256) void k_symmetrize(int NL, int ldS, double* S) 
 // dense tile helpers (64 x 64, 256 threads, 4 x 4 outputs per thread)
 typedef double Tile[64][65];
 
-__device__ __forceinline__ void load_tile(Tile& T, const double* p, int ld, bool trans) {
-  for (int t = threadIdx.x; t < 4096; t += blockDim.x) {
-    const int r = t >> 6, c = t & 63;
-    if (trans)
-      T[c][r] = p[(size_t)r * ld + c];
-    else
-      T[r][c] = p[(size_t)r * ld + c];
-  }
-}
-
 // A tile through registers, for 256-thread workgroups: tile_fetch issues all
 // 16 loads of the thread before any is used (one memory round trip per tile
 // instead of one per row of threads), tile_put stores them to LDS.
@@ -143,290 +133,160 @@ __device__ __forceinline__ void mf_each(const MfAcc& acc, F&& f) {
     for (int v = 0; v < 4; ++v) f(16 * w + lk + 4 * v, 16 * t + li, acc.t[t][v]);
 }
 
-// Cholesky of the diagonal tile (b, b), in place (lower; upper zeroed), by
-// symmetric elimination on unscaled columns: step k takes the pivot
-// d_k = a_kk and updates a_ij -= a_ik (a_jk / d_k) for k < j <= i.  Thread
-// (column j = tid % 64, rows tid / 64 + 4 u) keeps its 16 entries in
-// registers for the whole factorization; the owners of column k + 1 publish
-// it (after their step-k update) to one of two LDS column buffers, so each
-// step is one barrier.  At the end l_jj = sqrt(d_j) and l_ij = a_ij / l_jj.
-// A pivot <= 0 is recorded in fail (and taken as 1).
-__global__ __launch_bounds__(256) void k_potrf_diag(double* A, int ld, int b, int32_t* fail) {
-  __shared__ double col[2][64];
-  __shared__ double sq[64];
-  const int tid = threadIdx.x, jj = tid & 63, r0 = tid >> 6;
-  double* p = A + (size_t)b * 64 * ld + (size_t)b * 64;
-  double v[16];
+// Explicit inverse of symmetric positive definite matrices in 64 x 64 tiles,
+// by the symmetric sweep over tile pivots: with D = A_kk^{-1}, step k is
+//   A_ij <- A_ij - (A_ik D) A_jk^T,   A_ik <- A_ik D,   A_kk <- -D
+// for i, j != k, and after the last step the matrix is -A^{-1}.  Lower tiles
+// only (i >= j), read from src and written to dst, which change places from
+// step to step (no tile is read after it was overwritten); A_ik with i < k is
+// tile (k, i) transposed.  The workgroup of tile (k + 1, k + 1) inverts it at
+// the end of its step, beside the others' products, so a step is one launch
+// and the chain one tile inverse (25 us) and two tile products a step.  (A
+// tiled Cholesky, triangular inverse and L^{-T} L^{-1} took five launches and
+// 115 us a step for half the products.)  blockIdx.z: matrix, at moff[z] with
+// T[z] tiles a side (batch of one: moff null, T0); its row r is rowbase[z] + r
+// in fail, which keeps the smallest row (-1, the largest unsigned, for none).
+__global__ __launch_bounds__(256) void k_sweep_first(const double* src, const int64_t* moff,
+                                                     const int32_t* T, int T0, double* Dbuf,
+                                                     const int64_t* rowbase, int64_t rowbase0,
+                                                     int32_t* fail) {
+  const int z = blockIdx.x, ld = 64 * (moff ? T[z] : T0), tid = threadIdx.x;
+  const double* A = src + (moff ? moff[z] : 0);
+  const int64_t rb = rowbase ? rowbase[z] : rowbase0;
+  __shared__ double prow[2][64];
+  const int i0 = 4 * (tid / 16), j0 = 4 * (tid % 16);
+  double x[4][4];
 #pragma unroll
-  for (int u = 0; u < 16; ++u) v[u] = p[(size_t)(r0 + 4 * u) * ld + jj];
-  if (jj == 0)
+  for (int a = 0; a < 4; ++a)
 #pragma unroll
-    for (int u = 0; u < 16; ++u) col[0][r0 + 4 * u] = v[u];
-  __syncthreads();
-  for (int k = 0; k < 64; ++k) {
-    const double* ck = col[k & 1];
-    double d = ck[k];
-    if (!(d > 0.0)) {
-      d = 1.0;
-      if (tid == 0 && atomicCAS(fail, -1, b * 64 + k) == -1) fail[1] = b * 64 + k;
-    }
-    if (tid == 0) sq[k] = sqrt(d);
-    const double ajk = ck[jj] * (1.0 / d);  // a_jk / d_k for this thread's column
-    if (jj > k)
+    for (int c = 0; c < 4; ++c) x[a][c] = A[(size_t)(i0 + a) * ld + j0 + c];
+  sweep_inverse_64(x, prow, tid, true, [&](int k) {
+    atomicMin((unsigned*)fail, (unsigned)(rb + k));
+  });
+  double* D = Dbuf + (size_t)z * 2 * 4096;
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int i = r0 + 4 * u;
-        if (i >= jj) v[u] -= ck[i] * ajk;
-      }
-    if (jj == k + 1)
+  for (int a = 0; a < 4; ++a)
 #pragma unroll
-      for (int u = 0; u < 16; ++u) col[(k + 1) & 1][r0 + 4 * u] = v[u];
-    __syncthreads();
+    for (int c = 0; c < 4; ++c) D[(i0 + a) * 64 + j0 + c] = -x[a][c];
+}
+
+__global__ __launch_bounds__(256) void k_sweep_step(const double* __restrict__ src,
+                                                    double* __restrict__ dst, const int64_t* moff,
+                                                    const int32_t* Tz, int T0, int k, double* Dbuf,
+                                                    const int64_t* rowbase, int64_t rowbase0,
+                                                    int32_t* fail) {
+  const int z = blockIdx.z, T = moff ? Tz[z] : T0, ld = 64 * T;
+  const int j = blockIdx.x, i = blockIdx.y;
+  if (k >= T || i >= T || j > i) return;
+  const double* A = src + (moff ? moff[z] : 0);
+  double* B = dst + (moff ? moff[z] : 0);
+  const double* D = Dbuf + ((size_t)z * 2 + (k & 1)) * 4096;
+  double* out = B + (size_t)i * 64 * ld + (size_t)j * 64;
+  if (i == k && j == k) {
+    for (int t = threadIdx.x; t < 4096; t += 256) out[(size_t)(t >> 6) * ld + (t & 63)] = -D[t];
+    return;
   }
+  __shared__ Tile As;
+  __shared__ Tile Bs;
+  TileRegs ra, rb;
+  MfAcc acc;
+  mf_zero(acc);
+  // tile (r, k) of the symmetric matrix: stored at (k, r), transposed, above
+  auto fetch = [&](TileRegs& R, int r) {
+    if (r > k)
+      tile_fetch(R, A + (size_t)r * 64 * ld + (size_t)k * 64, ld);
+    else
+      tile_fetch(R, A + (size_t)k * 64 * ld + (size_t)r * 64, ld);
+  };
+  if (i == k) {  // row k: D A_kj
+    tile_fetch(ra, D, 64);
+    tile_fetch(rb, A + (size_t)k * 64 * ld + (size_t)j * 64, ld);
+    tile_put(As, ra, false);
+    tile_put(Bs, rb, false);
+    __syncthreads();
+    mf_mac(acc, As, Bs);
+    mf_each(acc, [&](int r, int c, double v) { out[(size_t)r * ld + c] = v; });
+    return;
+  }
+  fetch(ra, i);
+  tile_fetch(rb, D, 64);
+  tile_put(As, ra, i < k);
+  tile_put(Bs, rb, false);
+  __syncthreads();
+  if (j != k) fetch(rb, j);  // in flight during the first product
+  mf_mac(acc, As, Bs);       // A_ik D
+  if (j == k) {
+    mf_each(acc, [&](int r, int c, double v) { out[(size_t)r * ld + c] = v; });
+    return;
+  }
+  __syncthreads();
+  mf_each(acc, [&](int r, int c, double v) { As[r][c] = v; });
+  tile_put(Bs, rb, j > k);  // A_jk^T
+  tile_fetch(ra, A + (size_t)i * 64 * ld + (size_t)j * 64, ld);
+  __syncthreads();
+  mf_zero(acc);
+  mf_mac(acc, As, Bs);
+  __syncthreads();
+  mf_each(acc, [&](int r, int c, double v) { As[r][c] = v; });
+  __syncthreads();
 #pragma unroll
   for (int u = 0; u < 16; ++u) {
-    const int i = r0 + 4 * u;
-    p[(size_t)i * ld + jj] = jj < i ? v[u] / sq[jj] : (jj == i ? sq[jj] : 0.0);
+    const int r = (threadIdx.x >> 6) + 4 * u, c = threadIdx.x & 63;
+    const double v = ra.v[u] - As[r][c];
+    out[(size_t)r * ld + c] = v;
+    Bs[r][c] = v;
   }
-}
-
-// Panel: A_ib <- A_ib L_bb^{-T} for i = b+1.. (one tile per workgroup):
-// X L^T = A by columns, x_j = (a_j - sum_{c < j} x_c l_jc) (1 / l_jj) with
-// the terms in increasing c.  Thread (column j = tid % 64, rows tid / 64 + 4 u)
-// keeps its 16 entries in registers; finished column c goes to one of two
-// LDS buffers for the others, so each step is one barrier.
-__global__ __launch_bounds__(256) void k_trsm_panel(double* A, int ld, int b) {
-  __shared__ Tile L;
-  __shared__ double col[2][64];
-  const int i = b + 1 + blockIdx.x;
-  const int tid = threadIdx.x, jj = tid & 63, r0 = tid >> 6;
-  const double* pl = A + (size_t)b * 64 * ld + (size_t)b * 64;
-  double* pa = A + (size_t)i * 64 * ld + (size_t)b * 64;
-  {
-    TileRegs rl;
-    tile_fetch(rl, pl, ld);
-    tile_put(L, rl, false);
-  }
-  double v[16];
-#pragma unroll
-  for (int u = 0; u < 16; ++u) v[u] = pa[(size_t)(r0 + 4 * u) * ld + jj];
+  if (i != k + 1 || j != k + 1) return;
+  // the next pivot
   __syncthreads();
-  const double rjj = 1.0 / L[jj][jj];
-  if (jj == 0)
+  const int tid = threadIdx.x, i0 = 4 * (tid / 16), j0 = 4 * (tid % 16);
+  double x[4][4];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      v[u] *= rjj;
-      col[0][r0 + 4 * u] = v[u];
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {  // the lower half defines both halves
+      const int r = i0 + a, q = j0 + c;
+      x[a][c] = r >= q ? Bs[r][q] : Bs[q][r];
     }
+  const int64_t base = (rowbase ? rowbase[z] : rowbase0) + 64 * (k + 1);
   __syncthreads();
-  for (int c = 0; c < 63; ++c) {
-    const double* xc = col[c & 1];
-    const double ljc = L[jj][c];
-    if (jj > c)
-#pragma unroll
-      for (int u = 0; u < 16; ++u) v[u] -= xc[r0 + 4 * u] * ljc;
-    if (jj == c + 1)
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        v[u] *= rjj;
-        col[(c + 1) & 1][r0 + 4 * u] = v[u];
-      }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int u = 0; u < 16; ++u) pa[(size_t)(r0 + 4 * u) * ld + jj] = v[u];
-}
-
-// Trailing update A_ij -= A_ib A_jb^T for b < j <= i.
-__global__ __launch_bounds__(256) void k_syrk_update(double* A, int ld, int b) {
-  const int j = b + 1 + blockIdx.x, i = b + 1 + blockIdx.y;
-  if (j > i) return;
-  __shared__ Tile Ai;
-  __shared__ Tile Bj;
-  TileRegs ra, rb;
-  tile_fetch(ra, A + (size_t)i * 64 * ld + (size_t)b * 64, ld);
-  tile_fetch(rb, A + (size_t)j * 64 * ld + (size_t)b * 64, ld);
-  tile_put(Ai, ra, false);
-  tile_put(Bj, rb, true);
-  __syncthreads();
-  MfAcc acc;
-  mf_zero(acc);
-  mf_mac(acc, Ai, Bj);
-  double* pc = A + (size_t)i * 64 * ld + (size_t)j * 64;
-  mf_each(acc, [&](int r, int c, double v) { pc[(size_t)r * ld + c] -= v; });
-}
-
-// Inverse of each diagonal tile of L (lower), one column per thread.
-__global__ __launch_bounds__(64) void k_trtri_diag(const double* L, double* Li, int ld) {
-  __shared__ Tile T;
-  __shared__ Tile X;
-  const int b = blockIdx.x;
-  load_tile(T, L + (size_t)b * 64 * ld + (size_t)b * 64, ld, false);
-  __syncthreads();
-  const int c = threadIdx.x;
-  for (int r = 0; r < 64; ++r) {
-    double v = (r == c) ? 1.0 : 0.0;
-    if (r < c) {
-      X[r][c] = 0.0;
-      continue;
-    }
-    for (int k = c; k < r; ++k) v -= T[r][k] * X[k][c];
-    X[r][c] = v / T[r][r];
-  }
-  __syncthreads();
-  double* p = Li + (size_t)b * 64 * ld + (size_t)b * 64;
-  for (int t = threadIdx.x; t < 4096; t += blockDim.x) {
-    const int r = t >> 6, cc = t & 63;
-    p[(size_t)r * ld + cc] = X[r][cc];
-  }
-}
-
-// Trailing update with two panels, A_ij -= A_ib A_jb^T + A_i,b+1 A_j,b+1^T
-// for b+2 <= j <= i: one read-modify-write of the output tile for two
-// panels (the second pair of tiles is fetched while the first is multiplied).
-__global__ __launch_bounds__(256) void k_syrk_update2(double* A, int ld, int b) {
-  const int j = b + 2 + blockIdx.x, i = b + 2 + blockIdx.y;
-  if (j > i) return;
-  __shared__ Tile Ai;
-  __shared__ Tile Bj;
-  TileRegs ra, rb;
-  tile_fetch(ra, A + (size_t)i * 64 * ld + (size_t)b * 64, ld);
-  tile_fetch(rb, A + (size_t)j * 64 * ld + (size_t)b * 64, ld);
-  tile_put(Ai, ra, false);
-  tile_put(Bj, rb, true);
-  __syncthreads();
-  tile_fetch(ra, A + (size_t)i * 64 * ld + (size_t)(b + 1) * 64, ld);
-  tile_fetch(rb, A + (size_t)j * 64 * ld + (size_t)(b + 1) * 64, ld);
-  MfAcc acc;
-  mf_zero(acc);
-  mf_mac(acc, Ai, Bj);
-  __syncthreads();
-  tile_put(Ai, ra, false);
-  tile_put(Bj, rb, true);
-  __syncthreads();
-  mf_mac(acc, Ai, Bj);
-  double* pc = A + (size_t)i * 64 * ld + (size_t)j * 64;
-  mf_each(acc, [&](int r, int c, double v) { pc[(size_t)r * ld + c] -= v; });
-}
-
-// Off-diagonal tiles of L^{-1} at distance d: Li_ij = -Li_ii sum_{k=j}^{i-1} L_ik Li_kj.
-__global__ __launch_bounds__(256) void k_trtri_off(const double* L, double* Li, int ld, int d) {
-  const int i = d + blockIdx.x, j = blockIdx.x;
-  __shared__ Tile As;
-  __shared__ Tile Bs;
-  MfAcc acc;
-  mf_zero(acc);
-  // the tiles of step k + 1 are in flight while step k runs on the matrix cores
-  TileRegs ra, rb;
-  tile_fetch(ra, L + (size_t)i * 64 * ld + (size_t)j * 64, ld);
-  tile_fetch(rb, Li + (size_t)j * 64 * ld + (size_t)j * 64, ld);
-  for (int k = j; k < i; ++k) {
-    tile_put(As, ra, false);
-    tile_put(Bs, rb, false);
-    __syncthreads();
-    if (k + 1 < i) {
-      tile_fetch(ra, L + (size_t)i * 64 * ld + (size_t)(k + 1) * 64, ld);
-      tile_fetch(rb, Li + (size_t)(k + 1) * 64 * ld + (size_t)j * 64, ld);
-    } else {
-      tile_fetch(ra, Li + (size_t)i * 64 * ld + (size_t)i * 64, ld);
-    }
-    mf_mac(acc, As, Bs);
-    __syncthreads();
-  }
-  mf_each(acc, [&](int r, int c, double v) { Bs[r][c] = v; });
-  tile_put(As, ra, false);
-  __syncthreads();
-  mf_zero(acc);
-  mf_mac(acc, As, Bs);
-  double* p = Li + (size_t)i * 64 * ld + (size_t)j * 64;
-  mf_each(acc, [&](int r, int c, double v) { p[(size_t)r * ld + c] = -v; });
-}
-
-// The sum of k_trtri_off split over nchunk workgroups per tile, for the
-// launches with few tiles: workgroup (j, c) forms the share
-//   part[j nchunk + c] = sum_{k = k0}^{k1 - 1} L_ik Li_kj,
-// k0 = j + c d / nchunk, k1 = j + (c + 1) d / nchunk, as a row-major 64 x 64
-// block (nchunk <= d, so no share is empty).
-__global__ __launch_bounds__(256) void k_trtri_part(const double* L, const double* Li, int ld,
-                                                    int d, int nchunk, double* part) {
-  const int j = blockIdx.x / nchunk, c = blockIdx.x % nchunk, i = j + d;
-  const int k0 = j + (int)((int64_t)c * d / nchunk);
-  const int k1 = j + (int)((int64_t)(c + 1) * d / nchunk);
-  __shared__ Tile As;
-  __shared__ Tile Bs;
-  MfAcc acc;
-  mf_zero(acc);
-  TileRegs ra, rb;
-  tile_fetch(ra, L + (size_t)i * 64 * ld + (size_t)k0 * 64, ld);
-  tile_fetch(rb, Li + (size_t)k0 * 64 * ld + (size_t)j * 64, ld);
-  for (int k = k0; k < k1; ++k) {
-    tile_put(As, ra, false);
-    tile_put(Bs, rb, false);
-    __syncthreads();
-    if (k + 1 < k1) {
-      tile_fetch(ra, L + (size_t)i * 64 * ld + (size_t)(k + 1) * 64, ld);
-      tile_fetch(rb, Li + (size_t)(k + 1) * 64 * ld + (size_t)j * 64, ld);
-    }
-    mf_mac(acc, As, Bs);
-    __syncthreads();
-  }
-  double* p = part + (size_t)blockIdx.x * 4096;
-  mf_each(acc, [&](int r, int cc, double v) { p[r * 64 + cc] = v; });
-}
-
-// Li_ij = -Li_ii sum_c part[j nchunk + c], the shares added in order c = 0, 1, ..
-__global__ __launch_bounds__(256) void k_trtri_fin(double* Li, int ld, int d, int nchunk,
-                                                   const double* part) {
-  const int j = blockIdx.x, i = j + d;
-  __shared__ Tile As;
-  __shared__ Tile Bs;
-  TileRegs sum, t;
-  tile_fetch(sum, part + (size_t)j * nchunk * 4096, 64);
-  for (int c = 1; c < nchunk; ++c) {
-    tile_fetch(t, part + ((size_t)j * nchunk + c) * 4096, 64);
-#pragma unroll
-    for (int u = 0; u < 16; ++u) sum.v[u] += t.v[u];
-  }
-  tile_put(Bs, sum, false);
-  tile_fetch(t, Li + (size_t)i * 64 * ld + (size_t)i * 64, ld);
-  tile_put(As, t, false);
-  __syncthreads();
-  MfAcc acc;
-  mf_zero(acc);
-  mf_mac(acc, As, Bs);
-  double* p = Li + (size_t)i * 64 * ld + (size_t)j * 64;
-  mf_each(acc, [&](int r, int c, double v) { p[(size_t)r * ld + c] = -v; });
-}
-
-// S^{-1}_ij = sum_{k >= max(i,j)} Li_ki^T Li_kj for i >= j, mirrored.
-__global__ __launch_bounds__(256) void k_lauum(const double* Li, double* Sinv, int ld, int T) {
-  const int j = blockIdx.x, i = blockIdx.y;
-  if (j > i) return;
-  __shared__ Tile As;
-  __shared__ Tile Bs;
-  MfAcc acc;
-  mf_zero(acc);
-  // the tiles of step k + 1 are in flight while step k runs on the matrix cores
-  TileRegs ra, rb;
-  tile_fetch(ra, Li + (size_t)i * 64 * ld + (size_t)i * 64, ld);
-  tile_fetch(rb, Li + (size_t)i * 64 * ld + (size_t)j * 64, ld);
-  for (int k = i; k < T; ++k) {
-    tile_put(As, ra, true);
-    tile_put(Bs, rb, false);
-    __syncthreads();
-    if (k + 1 < T) {
-      tile_fetch(ra, Li + (size_t)(k + 1) * 64 * ld + (size_t)i * 64, ld);
-      tile_fetch(rb, Li + (size_t)(k + 1) * 64 * ld + (size_t)j * 64, ld);
-    }
-    mf_mac(acc, As, Bs);
-    __syncthreads();
-  }
-  mf_each(acc, [&](int r, int c, double v) {
-    const size_t gr = (size_t)i * 64 + r, gc = (size_t)j * 64 + c;
-    if (gr < gc) return;  // diagonal tile: the lower half defines both halves
-    Sinv[gr * ld + gc] = v;
-    Sinv[gc * ld + gr] = v;
+  sweep_inverse_64(x, reinterpret_cast<double(*)[64]>(&As[0][0]), tid, true, [&](int q) {
+    atomicMin((unsigned*)fail, (unsigned)(base + q));
   });
+  double* Dn = Dbuf + ((size_t)z * 2 + ((k + 1) & 1)) * 4096;
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) Dn[(i0 + a) * 64 + j0 + c] = -x[a][c];
+}
+
+// out = the symmetric inverse from a finished sweep (sign changed, the lower
+// half mirrored): nrow x ldo, row-major, columns from ncol on zero.
+// Workgroups over 64 x 64 tiles (blockIdx.x, y); blockIdx.z: matrix.
+__global__ __launch_bounds__(256) void k_sweep_out(const double* m0, const double* m1,
+                                                   const int64_t* moff, const int32_t* Tz, int T0,
+                                                   double* out, const int64_t* ooff,
+                                                   const int64_t* nrow_off, int nrow0, int ldo0) {
+  const int z = blockIdx.z, T = moff ? Tz[z] : T0, ld = 64 * T;
+  if ((int)blockIdx.x >= T || (int)blockIdx.y >= T) return;
+  const double* M = (T & 1 ? m1 : m0) + (moff ? moff[z] : 0);
+  const int nr = nrow_off ? (int)(nrow_off[z + 1] - nrow_off[z]) : nrow0;
+  const int ldo = nrow_off ? nr : ldo0;
+  double* o = out + (ooff ? ooff[z] : 0);
+  __shared__ Tile S;
+  const int bi = max((int)blockIdx.x, (int)blockIdx.y), bj = min((int)blockIdx.x, (int)blockIdx.y);
+  TileRegs r;
+  tile_fetch(r, M + (size_t)bi * 64 * ld + (size_t)bj * 64, ld);
+  tile_put(S, r, false);
+  __syncthreads();
+  const bool up = blockIdx.x > blockIdx.y;  // column tile beyond the row tile
+  for (int t = threadIdx.x; t < 4096; t += 256) {
+    const int a = t >> 6, c = t & 63;
+    const int gr = blockIdx.y * 64 + a, gc = blockIdx.x * 64 + c;
+    if (gr >= nr || gc >= ldo) continue;
+    const double v = up || (bi == bj && c > a) ? S[c][a] : S[a][c];
+    o[(size_t)gr * ldo + gc] = gc < nr ? -v : 0.0;
+  }
 }
 
 // One correction step of the explicit inverse where it is small (applied
@@ -729,72 +589,43 @@ hipError_t launch_assemble_S(DeviceState& d, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Shares per tile of the distance-d launch of the triangular inverse: enough
-// workgroups for two per CU, at most 16 shares, none empty.
-int trtri_chunks(int T, int d) {
-  const int nb = T - d;
-  return std::max(1, std::min(std::min(16, d), 512 / nb));
+hipError_t sweep_inverse(double* m0, double* m1, const int64_t* moff, const int32_t* T, int nmat,
+                         int Tmax, double* Dbuf, const int64_t* rowbase, int64_t rowbase0,
+                         int32_t* fail, hipStream_t st) {
+  if (nmat < 1 || Tmax < 1) return hipSuccess;
+  hipLaunchKernelGGL(k_sweep_first, dim3(nmat), dim3(256), 0, st, m0, moff, T, Tmax, Dbuf, rowbase,
+                     rowbase0, fail);
+  for (int k = 0; k < Tmax; ++k)
+    hipLaunchKernelGGL(k_sweep_step, dim3(Tmax, Tmax, nmat), dim3(256), 0, st, k & 1 ? m1 : m0,
+                       k & 1 ? m0 : m1, moff, T, Tmax, k, Dbuf, rowbase, rowbase0, fail);
+  return hipGetLastError();
 }
 
-// Scratch tiles the split launches need (0 if none is split).
-int64_t trtri_part_tiles(int T) {
-  int64_t mx = 0;
-  for (int dd = 1; dd < T; ++dd) {
-    const int c = trtri_chunks(T, dd);
-    if (c > 1) mx = std::max<int64_t>(mx, (int64_t)(T - dd) * c);
-  }
-  return mx;
+hipError_t sweep_output(const double* m0, const double* m1, const int64_t* moff, const int32_t* T,
+                        int nmat, int Tmax, double* out, const int64_t* ooff,
+                        const int64_t* nrow_off, int nrow0, int ldo0, hipStream_t st) {
+  if (nmat < 1 || Tmax < 1) return hipSuccess;
+  hipLaunchKernelGGL(k_sweep_out, dim3(Tmax, Tmax, nmat), dim3(256), 0, st, m0, m1, moff, T, Tmax,
+                     out, ooff, nrow_off, nrow0, ldo0);
+  return hipGetLastError();
 }
 
-hipError_t dense_cholesky_inverse(DeviceState& d, double* L, double* Li, double* part,
-                                  hipStream_t st) {
+hipError_t dense_inverse(DeviceState& d, const double* S, double* m0, double* m1, double* Dbuf,
+                         double* out, hipStream_t st) {
   const int ld = d.ldS, T = ld / 64;
   if (T == 0) return hipSuccess;
-  hipError_t e = hipMemcpyAsync(L, d.S, sizeof(double) * (size_t)ld * ld, hipMemcpyDeviceToDevice, st);
-  if (e != hipSuccess) return e;
-  e = hipMemsetAsync(Li, 0, sizeof(double) * (size_t)ld * ld, st);
-  if (e != hipSuccess) return e;
-  // right-looking tiled Cholesky with a look-ahead of one panel: after panel
-  // b, only column b+1 is updated; panel b+1 is factored; then panels b and
-  // b+1 update the rest of the trailing matrix together
-  for (int b = 0; b < T;) {
-    hipLaunchKernelGGL(k_potrf_diag, dim3(1), dim3(256), 0, st, L, ld, b, d.fail + 2);
-    if (b + 1 == T) break;
-    hipLaunchKernelGGL(k_trsm_panel, dim3(T - b - 1), dim3(256), 0, st, L, ld, b);
-    if (b + 2 == T) {  // one tile left
-      hipLaunchKernelGGL(k_syrk_update, dim3(1, 1), dim3(256), 0, st, L, ld, b);
-      b += 1;
-      continue;
-    }
-    hipLaunchKernelGGL(k_syrk_update, dim3(1, T - b - 1), dim3(256), 0, st, L, ld, b);
-    hipLaunchKernelGGL(k_potrf_diag, dim3(1), dim3(256), 0, st, L, ld, b + 1, d.fail + 2);
-    hipLaunchKernelGGL(k_trsm_panel, dim3(T - b - 2), dim3(256), 0, st, L, ld, b + 1);
-    hipLaunchKernelGGL(k_syrk_update2, dim3(T - b - 2, T - b - 2), dim3(256), 0, st, L, ld, b);
-    b += 2;
-  }
-  hipLaunchKernelGGL(k_trtri_diag, dim3(T), dim3(64), 0, st, L, Li, ld);
-  for (int dd = 1; dd < T; ++dd) {
-    const int c = trtri_chunks(T, dd);
-    if (c == 1) {
-      hipLaunchKernelGGL(k_trtri_off, dim3(T - dd), dim3(256), 0, st, L, Li, ld, dd);
-    } else {
-      hipLaunchKernelGGL(k_trtri_part, dim3((T - dd) * c), dim3(256), 0, st, L, Li, ld, dd, c, part);
-      hipLaunchKernelGGL(k_trtri_fin, dim3(T - dd), dim3(256), 0, st, Li, ld, dd, c, part);
-    }
-  }
-  hipLaunchKernelGGL(k_lauum, dim3(T, T), dim3(256), 0, st, Li, d.Sinv, ld, T);
-  if (!d.fuse_eta) return hipGetLastError();
+  const size_t bytes = sizeof(double) * (size_t)ld * ld;
+  hipError_t e = hipMemcpyAsync(m0, S, bytes, hipMemcpyDeviceToDevice, st);
+  if (e == hipSuccess)
+    e = sweep_inverse(m0, m1, nullptr, nullptr, 1, T, Dbuf, nullptr, 0, d.fail + 2, st);
+  if (e == hipSuccess)
+    e = sweep_output(m0, m1, nullptr, nullptr, 1, T, out, nullptr, nullptr, ld, ld, st);
+  if (e != hipSuccess || !d.fuse_eta) return e;
   hipLaunchKernelGGL(k_sinv_residual, dim3(T, ld / 4), dim3(256), 0, st, (int)d.NL, ld, d.iface_ij,
-                     d.isub_ptr, d.isub_list, d.S, d.Sinv, L);
-  hipLaunchKernelGGL(k_sinv_correct, dim3(T, T), dim3(256), 0, st, d.Sinv, L, Li, ld, T);
-  e = hipMemcpyAsync(d.Sinv, Li, sizeof(double) * (size_t)ld * ld, hipMemcpyDeviceToDevice, st);
+                     d.isub_ptr, d.isub_list, d.S, out, m0);
+  hipLaunchKernelGGL(k_sinv_correct, dim3(T, T), dim3(256), 0, st, out, m0, m1, ld, T);
+  e = hipMemcpyAsync(out, m1, bytes, hipMemcpyDeviceToDevice, st);
   return e != hipSuccess ? e : hipGetLastError();
-}
-
-hipError_t launch_lauum(const double* Li, double* out, int ld, int T, hipStream_t st) {
-  if (T <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_lauum, dim3(T, T), dim3(256), 0, st, Li, out, ld, T);
-  return hipGetLastError();
 }
 
 template <int NR>

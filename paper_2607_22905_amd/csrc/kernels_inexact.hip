@@ -287,8 +287,8 @@ __global__ __launch_bounds__(256) void k_ix_ell(const double* __restrict__ S, in
 }
 
 // block inverses and the ELL values from the handle's S (original order).
-// Sbd, L, Li: ldS x ldS scratch; part: trtri_part_tiles(ldS / 64) tiles.
-hipError_t ix_numeric(DeviceState& d, double* Sbd, double* L, double* Li, double* part,
+// Sbd, m0, m1: ldS x ldS scratch; Dbuf: 8192 doubles.
+hipError_t ix_numeric(DeviceState& d, double* Sbd, double* m0, double* m1, double* Dbuf,
                       hipStream_t st) {
   IxDevice& ix = d.ix;
   const int64_t tot = (int64_t)d.ldS * d.ldS;
@@ -296,10 +296,7 @@ hipError_t ix_numeric(DeviceState& d, double* Sbd, double* L, double* Li, double
                      d.ldS, (int)d.NL, ix.bs, Sbd);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  double* S0 = d.S;
-  d.S = Sbd;
-  e = dense_cholesky_inverse(d, L, Li, part, st);  // d.Sinv = Sbd^{-1}
-  d.S = S0;
+  e = dense_inverse(d, Sbd, m0, m1, Dbuf, d.Sinv, st);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_ix_extract, dim3(64, ix.nblk), dim3(256), 0, st, d.Sinv, d.ldS, (int)d.NL,
                      ix.bs, ix.inv_off, ix.binv);
