@@ -93,10 +93,36 @@ __device__ __forceinline__ void st_fac(bf16_t* p, double v) {
   *p = (bf16_t)(u >> 16);
 }
 
+// v[lane] + v[lane ^ 32] and v[lane] + v[lane ^ 16] by register swaps
+__device__ __forceinline__ double add_xor32(double v) {
+  const int2 a = __builtin_bit_cast(int2, v);
+  const auto x = __builtin_amdgcn_permlane32_swap(a.x, a.x, false, false);
+  const auto y = __builtin_amdgcn_permlane32_swap(a.y, a.y, false, false);
+  return __builtin_bit_cast(double, make_int2(x[0], y[0])) +
+         __builtin_bit_cast(double, make_int2(x[1], y[1]));
+}
+__device__ __forceinline__ double add_xor16(double v) {
+  const int2 a = __builtin_bit_cast(int2, v);
+  const auto x = __builtin_amdgcn_permlane16_swap(a.x, a.x, false, false);
+  const auto y = __builtin_amdgcn_permlane16_swap(a.y, a.y, false, false);
+  return __builtin_bit_cast(double, make_int2(x[0], y[0])) +
+         __builtin_bit_cast(double, make_int2(x[1], y[1]));
+}
+// v + v of the lane N places on in the row of 16
+template <int N> __device__ __forceinline__ double add_ror(double v) {
+  const int2 a = __builtin_bit_cast(int2, v);
+  return v + __builtin_bit_cast(
+                 double, make_int2(__builtin_amdgcn_update_dpp(0, a.x, 0x120 + N, 0xF, 0xF, true),
+                                   __builtin_amdgcn_update_dpp(0, a.y, 0x120 + N, 0xF, 0xF, true)));
+}
+// Sum over the 64 lanes, in every lane (all lanes active): the butterfly over
+// lane ^ 32, 16, .. 1, in registers.  (After the first steps the values repeat
+// every 16, 8, 4, 2 lanes, so a rotation within the row of 16 reaches the
+// partner.  __shfl_xor, the same sums through the LDS crossbar, took a round
+// trip of some 130 cycles for each of the six steps.)
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
+  v = add_xor16(add_xor32(v));
+  return add_ror<1>(add_ror<2>(add_ror<4>(add_ror<8>(v))));
 }
 
 // Sum of v[k] over the block (fixed tree); result valid in every thread.
@@ -117,6 +143,23 @@ __device__ __forceinline__ void block_sum(double (&v)[NR], double* lds) {
     v[k] = s;
   }
   __syncthreads();
+}
+
+// The same sums, each in one thread: thread t < NR returns that of v[t].
+template <int NR>
+__device__ __forceinline__ double block_sum_spread(const double (&v)[NR], double* lds) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+#pragma unroll
+  for (int k = 0; k < NR; ++k) {
+    const double t = wave_sum(v[k]);
+    if (lane == 0) lds[w * NR + k] = t;
+  }
+  __syncthreads();
+  double s = 0.0;
+  if (threadIdx.x < NR)
+    for (int i = 0; i < nw; ++i) s += lds[i * NR + threadIdx.x];
+  __syncthreads();
+  return s;
 }
 
 // Publish this block's sums and tell whether it is the last block of the

@@ -1110,10 +1110,8 @@ __global__ __launch_bounds__(256) void k_localt_mf2(
   }
 
   if (mode != 2) return;
-  rz += __shfl_xor(rz, 16, 64);
-  rz += __shfl_xor(rz, 32, 64);
-  qz += __shfl_xor(qz, 16, 64);
-  qz += __shfl_xor(qz, 32, 64);
+  rz = add_xor32(add_xor16(rz));
+  qz = add_xor32(add_xor16(qz));
   if (lane < 16) {
     dots[w][lane] = rz;
     dots[w][NT + lane] = qz;

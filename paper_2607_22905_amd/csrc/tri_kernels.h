@@ -1364,10 +1364,8 @@ __global__ __launch_bounds__(256, 2) void k_tri_mf(
 
   if (mode != 2) return;
   // lanes l, l ^ 16, l ^ 32, l ^ 48 hold the same column
-  rz += __shfl_xor(rz, 16, 64);
-  rz += __shfl_xor(rz, 32, 64);
-  qz += __shfl_xor(qz, 16, 64);
-  qz += __shfl_xor(qz, 32, 64);
+  rz = add_xor32(add_xor16(rz));
+  qz = add_xor32(add_xor16(qz));
   double* dots = reinterpret_cast<double*>(&tile[0][0]);  // [4][2 NT]
   if (lane < NT) {
     dots[wave * 2 * NT + lane] = rz;
