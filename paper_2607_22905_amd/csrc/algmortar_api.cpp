@@ -277,7 +277,8 @@ static hipError_t nd_upload(DeviceState& d, const IfaceND& ndh, hipStream_t sm) 
   for (int64_t t = 0; t < ndh.ntop; ++t) nd.h_src[ndh.pad_off[nd.nblk] + t] = ndh.order[nd.nrows + t];
   std::vector<int64_t> inv_off(nd.nblk + 1, 0);
   std::vector<int64_t> moff(nd.nblk + 1, 0);
-  std::vector<int32_t> wg_blk, wg_row0, tiles;
+  std::vector<NdWg> wg;
+  std::vector<int32_t> tiles;
   for (int b = 0; b < nd.nblk; ++b) {
     const int64_t sb = ndh.blk_off[b + 1] - ndh.blk_off[b], pb = (sb + 63) / 64 * 64;
     inv_off[b + 1] = inv_off[b] + sb * sb;
@@ -285,12 +286,10 @@ static hipError_t nd_upload(DeviceState& d, const IfaceND& ndh, hipStream_t sm) 
     tiles.push_back((int32_t)(pb / 64));
     nd.tmax = std::max(nd.tmax, tiles.back());
     nd.smax = std::max(nd.smax, sb);
-    for (int64_t r0 = 0; r0 < sb; r0 += 64) {
-      wg_blk.push_back(b);
-      wg_row0.push_back((int32_t)r0);
-    }
+    for (int64_t r0 = 0; r0 < sb; r0 += 64)
+      wg.push_back({ndh.blk_off[b], inv_off[b], (int32_t)sb, (int32_t)r0});
   }
-  nd.nwg = (int32_t)wg_blk.size();
+  nd.nwg = (int32_t)wg.size();
   nd.mrows = moff[nd.nblk];
   // row parts of the top product: about 2048 waves, at most what the
   // kernels keep in LDS
@@ -337,8 +336,7 @@ static hipError_t nd_upload(DeviceState& d, const IfaceND& ndh, hipStream_t sm) 
   NDUP(nd.inv_off, inv_off);
   NDUP(nd.moff, moff);
   NDUP(nd.tiles, tiles);
-  NDUP(nd.wg_blk, wg_blk);
-  NDUP(nd.wg_row0, wg_row0);
+  NDUP(nd.wg, wg);
   NDUP(nd.t_ptr, ndh.t_ptr);
   NDUP(nd.t_pos, t_pos);
   NDUP(nd.t_blk, t_blk);
@@ -652,7 +650,12 @@ static am_status setup_impl(const am_csr* A, const int32_t* part, int32_t nparts
   const int64_t npair = 2 * NL;
   std::vector<int32_t> pair_sub(npair), pair_q(npair);
   std::vector<int64_t> bidx(npair);  // (interface, side) -> pair
-  std::vector<int64_t> bdst(npair);  // pair -> (interface, side) slot 2n + side
+  std::vector<int64_t> bdst(npair);  // pair -> its slot of bpart (DeviceState::bdst)
+  std::vector<int32_t> ndpos;
+  if (use_nd) {
+    ndpos.resize(NL);
+    for (int64_t p = 0; p < NL; ++p) ndpos[ndh.order[p]] = (int32_t)p;
+  }
   for (int32_t s2 = 0; s2 < st.m; ++s2)
     for (int64_t pi = st.isub_ptr[s2]; pi < st.isub_ptr[s2 + 1]; ++pi) {
       pair_sub[pi] = s2;
@@ -660,7 +663,7 @@ static am_status setup_impl(const am_csr* A, const int32_t* part, int32_t nparts
       const int32_t nidx = st.isub_list[pi];
       const int side = st.iface_ij[2 * nidx] == s2 ? 0 : 1;
       bidx[2 * nidx + side] = pi;
-      bdst[pi] = 2 * (int64_t)nidx + side;
+      bdst[pi] = 2 * (int64_t)(use_nd ? ndpos[nidx] : nidx) + side;
     }
   for (int bk = 0; bk < 2; ++bk) d.bucket_pair[bk].clear();
   for (int64_t pi = 0; pi < npair; ++pi)

@@ -108,13 +108,18 @@ __device__ __forceinline__ double add_xor16(double v) {
   return __builtin_bit_cast(double, make_int2(x[0], y[0])) +
          __builtin_bit_cast(double, make_int2(x[1], y[1]));
 }
-// v + v of the lane N places on in the row of 16
-template <int N> __device__ __forceinline__ double add_ror(double v) {
+// v + v of another lane of the row of 16 (a data-parallel primitive control)
+template <int CTRL> __device__ __forceinline__ double add_dpp(double v) {
   const int2 a = __builtin_bit_cast(int2, v);
   return v + __builtin_bit_cast(
-                 double, make_int2(__builtin_amdgcn_update_dpp(0, a.x, 0x120 + N, 0xF, 0xF, true),
-                                   __builtin_amdgcn_update_dpp(0, a.y, 0x120 + N, 0xF, 0xF, true)));
+                 double, make_int2(__builtin_amdgcn_update_dpp(0, a.x, CTRL, 0xF, 0xF, true),
+                                   __builtin_amdgcn_update_dpp(0, a.y, CTRL, 0xF, 0xF, true)));
 }
+template <int N> __device__ __forceinline__ double add_ror(double v) { return add_dpp<0x120 + N>(v); }
+__device__ __forceinline__ double add_xor1(double v) { return add_dpp<0xB1>(v); }
+__device__ __forceinline__ double add_xor2(double v) { return add_dpp<0x4E>(v); }
+// lane 7 - l of each eight (lane ^ 4 where the values repeat in fours)
+__device__ __forceinline__ double add_mirror(double v) { return add_dpp<0x141>(v); }
 // Sum over the 64 lanes, in every lane (all lanes active): the butterfly over
 // lane ^ 32, 16, .. 1, in registers.  (After the first steps the values repeat
 // every 16, 8, 4, 2 lanes, so a rotation within the row of 16 reaches the
@@ -214,6 +219,15 @@ __device__ __forceinline__ void reduce_partials(double (&tot)[NR], const double*
   for (int k = 0; k < NR; ++k) tot[k] = 0.0;
   fold_rows<NR>(partial, (int)nblocks, threadIdx.x, blockDim.x, tot);
   block_sum<NR>(tot, lds);
+}
+
+// Part of the rows that workgroup b of nb takes where it reads neighbours'
+// rows: the workgroups go to the eight XCDs in turn, so those of one XCD
+// (b % 8) take consecutive parts, and most neighbours' lines are then in the
+// XCD's own L2.
+__device__ __forceinline__ int xcd_part(int b, int nb) {
+  const int x = b & 7, per = nb >> 3, rem = nb & 7;
+  return x * per + min(x, rem) + (b >> 3);
 }
 
 // Node vectors with NT right-hand sides: value (row, k) at row * NT + k, the

@@ -60,6 +60,12 @@ struct Reduce {
 
 // Nested-dissection interface solve (kernels_nd.hip, layout from
 // build_iface_nd): device arrays, owned through DeviceState::allocs.
+// 64 rows row0 .. of one block: its first ND position o, the offset of its
+// inverse and its rows s
+struct NdWg {
+  int64_t o, inv;
+  int32_t s, row0;
+};
 struct NdDevice {
   int32_t on = 0;          // the interface solve uses this form
   int32_t nblk = 0;
@@ -80,8 +86,7 @@ struct NdDevice {
   int32_t tmax = 0;            // tiles a side of the largest block
   int64_t* moff = nullptr;     // [nblk+1] their offsets
   int32_t* tiles = nullptr;    // [nblk] tiles a side
-  int32_t* wg_blk = nullptr;   // [nwg] block of each workgroup ..
-  int32_t* wg_row0 = nullptr;  // .. and its first row
+  NdWg* wg = nullptr;          // [nwg] the rows of each workgroup of k_nd_blocks
   double* binv = nullptr;      // block inverses
   double* cinv = nullptr;      // [R][ldC] C^{-1}
   int64_t* t_ptr = nullptr;    // [R+1] top row -> couplings to block rows
@@ -216,7 +221,9 @@ struct DeviceState {
   int32_t* e_kloc = nullptr;     // [NE] local row of k in subdomain i
   int32_t* e_lloc = nullptr;     // [NE] local row of l in subdomain j
   double* e_a = nullptr;         // [NE]
-  int64_t* bdst = nullptr;       // [2 NL] (subdomain, slot) pair -> slot 2n + side of bpart
+  // [2 NL] (subdomain, slot) pair -> slot 2n + side of bpart (dissection form:
+  // 2p + side, p the ND position of n)
+  int64_t* bdst = nullptr;
   double* S = nullptr;           // [ldS * ldS] symmetrised interface matrix
   double* Sinv = nullptr;        // [ldS * ldS]
   int32_t op_parts = 1;          // row parts of the interface product (k_iface_op)
@@ -230,7 +237,7 @@ struct DeviceState {
   double* z = nullptr;
   double* p[2] = {nullptr, nullptr};
   double* q = nullptr;
-  double* bpart = nullptr;  // [2 NL][nrhs], slot 2n + side
+  double* bpart = nullptr;  // [2 NL][nrhs], slots as in bdst
   double* eta = nullptr;    // [ldS][nrhs]
   PcgScalars* sc = nullptr; // [kMaxNRHS]
   PcgShared* shared = nullptr;

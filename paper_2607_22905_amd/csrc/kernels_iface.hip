@@ -49,20 +49,34 @@ __global__ __launch_bounds__(256) void k_assemble_S(
   }
 }
 
-// (S + S^T)/2 on the N_Lambda block; identity on the padding.
-__global__ __launch_bounds__(256) void k_symmetrize(int NL, int ldS, double* S) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t tot = (int64_t)ldS * ldS;
-  if (t >= tot) return;
-  const int r = (int)(t / ldS), c = (int)(t % ldS);
-  if (r >= NL || c >= NL) {
-    if (r == c) S[t] = 1.0;
+// (S + S^T)/2, identity on the padding.  S couples a basis function n to those
+// of its two subdomains only: wave n takes its couplings m < n, and writes
+// both entries.  (Over the whole square: 2.5 ms at 128^3, NL = 11904.)
+__global__ __launch_bounds__(256) void k_symmetrize(int NL, int ldS,
+                                                    const int32_t* __restrict__ iface_ij,
+                                                    const int64_t* __restrict__ isub_ptr,
+                                                    const int32_t* __restrict__ isub_list,
+                                                    double* S) {
+  const int lane = threadIdx.x & 63;
+  const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (n >= ldS) return;
+  if (n >= NL) {
+    if (lane == 0) S[(size_t)n * ldS + n] = 1.0;
     return;
   }
-  if (r <= c) return;
-  const double v = 0.5 * (S[(size_t)r * ldS + c] + S[(size_t)c * ldS + r]);
-  S[(size_t)r * ldS + c] = v;
-  S[(size_t)c * ldS + r] = v;
+  const int i = iface_ij[2 * n], j = iface_ij[2 * n + 1];
+  for (int side = 0; side < 2; ++side) {
+    const int sd = side == 0 ? i : j;
+    for (int64_t t = isub_ptr[sd] + lane; t < isub_ptr[sd + 1]; t += 64) {
+      const int m = isub_list[t];
+      if (m >= n) continue;
+      // basis functions between the same two subdomains are in both lists
+      if (side == 1 && iface_ij[2 * m] == i && iface_ij[2 * m + 1] == j) continue;
+      const double v = 0.5 * (S[(size_t)n * ldS + m] + S[(size_t)m * ldS + n]);
+      S[(size_t)n * ldS + m] = v;
+      S[(size_t)m * ldS + n] = v;
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -358,40 +372,43 @@ __global__ __launch_bounds__(256) void k_sinv_correct(const double* X, const dou
 
 // ---------------------------------------------------------------------------
 // eta = S^{-1} b with a small dense S^{-1} (at most 64 MB, resident in the
-// caches), in one launch: a wave forms RW rows, its lanes striding over the
-// columns with a round's loads all issued before the first is used, and sums
-// them by shuffles.  In a solve one more workgroup takes the stop decision.
-// 64^3 (NL = 1344): 4 us; the same rows formed in the local kernel, by its two
-// waves per subdomain, held every subdomain up for 5.6 us, and the four
-// columns of a bisection part's 23 rows for over 100.
+// caches), in one launch: a workgroup forms RW rows, its four waves a quarter
+// of the columns each, with a round's loads all issued before the first is
+// used (and before the stop flag is looked at).  In a solve one more workgroup
+// takes the stop decision.  Bound by the round trips: 64^3 (NL = 1344) one
+// round, 5.5 us (two rows a wave over all columns, four rounds: 5.8 us); the
+// same rows formed in the local kernel, by its two waves per subdomain, held
+// every subdomain up for 5.6 us, and the four columns of a bisection part's 23
+// rows for over 100.
+template <int NR>
+constexpr int eta_rows() { return NR == 1 ? 8 : 4; }
 template <int NR>
 __global__ __launch_bounds__(256) void k_eta_dense(int NL, int ldS, const double* __restrict__ Sinv,
                                                    const double* __restrict__ bpart,
                                                    double* __restrict__ eta, int pcg, int init,
                                                    const double* __restrict__ pb, int npb,
                                                    PcgScalars* sc, PcgShared* sh) {
-  constexpr int RW = NR <= 2 ? 2 : 4;
+  constexpr int RW = eta_rows<NR>();
   constexpr int UM = NR == 1 ? 6 : NR <= 4 ? 2 : 1;
-  __shared__ double lds[4 * NR];
+  __shared__ double lds[4 * RW * NR];
   // a solve that stopped earlier (this launch's last workgroup may be writing
-  // the flag: no barrier below, and a stopped solve reads no eta)
-  if (pcg && !init && all_done(sh)) return;
+  // the flag: threads that read it late leave with the same outcome, as a
+  // stopped solve reads no eta)
+  const int stopped = pcg && !init ? (int)all_done(sh) : 0;
   if (pcg && blockIdx.x == gridDim.x - 1) {
-    stop_test_wg<NR>(pb, npb, init, sc, sh, lds);
+    if (!stopped) stop_test_wg<NR>(pb, npb, init, sc, sh, lds);
     return;
   }
-  const int lane = threadIdx.x & 63;
-  const int r0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * RW;
-  if (r0 >= NL) return;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int r0 = blockIdx.x * RW;
+  const int per = (NL + 3) / 4, me = min(NL, (w + 1) * per);
   const double* row[RW];
 #pragma unroll
   for (int r = 0; r < RW; ++r) row[r] = Sinv + (size_t)min(r0 + r, NL - 1) * ldS;
-  double a[RW][NR];
+  double a[RW * NR];
 #pragma unroll
-  for (int r = 0; r < RW; ++r)
-#pragma unroll
-    for (int k = 0; k < NR; ++k) a[r][k] = 0.0;
-  for (int m0 = lane; m0 < NL; m0 += 64 * UM) {
+  for (int r = 0; r < RW * NR; ++r) a[r] = 0.0;
+  for (int m0 = w * per + lane; m0 < me + lane; m0 += 64 * UM) {
     double bm[UM][2][NR], sv[UM][RW];
 #pragma unroll
     for (int u = 0; u < UM; ++u) {
@@ -405,24 +422,21 @@ __global__ __launch_bounds__(256) void k_eta_dense(int NL, int ldS, const double
       }
     }
     __builtin_amdgcn_sched_barrier(0);
+    if (stopped) break;
 #pragma unroll
     for (int u = 0; u < UM; ++u) {
-      const bool ok = m0 + 64 * u < NL;
+      const bool ok = m0 + 64 * u < me;
 #pragma unroll
       for (int k = 0; k < NR; ++k) {
         const double b = ok ? bm[u][0][k] + bm[u][1][k] : 0.0;
 #pragma unroll
-        for (int r = 0; r < RW; ++r) a[r][k] = fma(sv[u][r], b, a[r][k]);
+        for (int r = 0; r < RW; ++r) a[r * NR + k] = fma(sv[u][r], b, a[r * NR + k]);
       }
     }
   }
-#pragma unroll
-  for (int r = 0; r < RW; ++r)
-#pragma unroll
-    for (int k = 0; k < NR; ++k) {
-      const double t = wave_sum(a[r][k]);
-      if (lane == 0 && r0 + r < NL) eta[(size_t)(r0 + r) * NR + k] = t;
-    }
+  const double t = block_sum_spread<RW * NR>(a, lds);
+  const int r = r0 + (int)threadIdx.x / NR;
+  if ((int)threadIdx.x < RW * NR && r < NL && !stopped) eta[(size_t)r * NR + threadIdx.x % NR] = t;
 }
 
 // ---------------------------------------------------------------------------
@@ -583,9 +597,8 @@ hipError_t launch_assemble_S(DeviceState& d, hipStream_t st) {
   hipLaunchKernelGGL(k_assemble_S, dim3((unsigned)((d.NL + 3) / 4)), dim3(256), 0, st, (int)d.NL,
                      d.ldS, d.iface_ptr, d.iface_ij, d.e_kloc, d.e_lloc, d.e_a, d.sub_ptr,
                      d.isub_ptr, d.isub_list, d.mbf_off, d.mbf, d.S);
-  const int64_t tot = (int64_t)d.ldS * d.ldS;
-  hipLaunchKernelGGL(k_symmetrize, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st,
-                     (int)d.NL, d.ldS, d.S);
+  hipLaunchKernelGGL(k_symmetrize, dim3((unsigned)((d.ldS + 3) / 4)), dim3(256), 0, st,
+                     (int)d.NL, d.ldS, d.iface_ij, d.isub_ptr, d.isub_list, d.S);
   return hipGetLastError();
 }
 
@@ -645,8 +658,7 @@ static void gemv_t(DeviceState& d, hipStream_t st, int pcg, int init) {
 
 template <int NR>
 static void eta_dense_t(DeviceState& d, hipStream_t st, int pcg, int init) {
-  constexpr int rows = 4 * (NR <= 2 ? 2 : 4);
-  const unsigned nb = (unsigned)((d.NL + rows - 1) / rows) + (pcg ? 1 : 0);
+  const unsigned nb = (unsigned)((d.NL + eta_rows<NR>() - 1) / eta_rows<NR>()) + (pcg ? 1 : 0);
   am_launch(d, true, true, k_eta_dense<NR>, dim3(nb), dim3(256), st, (int)d.NL, d.ldS, d.Sinv,
             d.bpart, d.eta, pcg, init, d.red.pb, d.m, d.sc, d.shared);
 }

@@ -56,7 +56,9 @@ __device__ __forceinline__ void ix_precond(const double* __restrict__ inv, int s
                                            double* __restrict__ pb_out, double* red) {
   const int w = threadIdx.x >> 6;
   nd_d4 acc[4];
-  nd_wave_product<NR, false>(inv, s, 64 * w, s, 0, s, rl, 0, acc);
+  NdRows<NR, false> f;
+  f.load(inv, s, 64 * w, s, 0, s);
+  nd_wave_product<NR, false>(inv, s, 64 * w, s, 0, s, rl, 0, f, acc);
   double part[2 * NR];
 #pragma unroll
   for (int c = 0; c < 2 * NR; ++c) part[c] = 0.0;

@@ -13,8 +13,8 @@
 // together, forms C from the sparse couplings and inverts it, with the tiled
 // sweep of kernels_iface.hip on matrices padded to 64-row tiles.
 //
-// Right-hand sides b_n = bpart[2n] + bpart[2n+1] (interface slots, see
-// bpart_sub); eta is written in the original basis-function order, [n][NR].
+// Right-hand sides b = bpart[2p] + bpart[2p+1] at ND position p (the slots are
+// numbered by it in this form, see DeviceState::bdst); eta is written in the original basis-function order, [n][NR].
 #include <algorithm>
 
 #include "am_common.h"
@@ -76,9 +76,7 @@ __device__ __forceinline__ double nd_sub_couplings(double x, int64_t qb, int64_t
 
 template <int NR>
 __global__ __launch_bounds__(64 * NdWaves<NR>::v) void k_nd_blocks(
-    int pass, int from_y1, int nwg, const int32_t* __restrict__ wg_blk,
-    const int32_t* __restrict__ wg_row0, const int64_t* __restrict__ blk_off,
-    const int64_t* __restrict__ inv_off, const double* __restrict__ binv,
+    int pass, int from_y1, int nwg, const NdWg* __restrict__ wg, const double* __restrict__ binv,
     const int32_t* __restrict__ ord, const double* __restrict__ bpart,
     const int64_t* __restrict__ b_ptr, const int32_t* __restrict__ b_top,
     const double* __restrict__ b_val, const double* __restrict__ eta2, double* __restrict__ y1,
@@ -88,6 +86,7 @@ __global__ __launch_bounds__(64 * NdWaves<NR>::v) void k_nd_blocks(
   extern __shared__ double rhs[];
   __shared__ int skip;
   __shared__ double red[NW * NR];
+  const NdWg W = (int)blockIdx.x < nwg ? wg[blockIdx.x] : NdWg{};  // with the stop flag
   if (threadIdx.x == 0) skip = (pcg && !init && all_done(sh)) ? 1 : 0;
   __syncthreads();
   if (skip) return;  // uniform: one read for the whole workgroup
@@ -99,28 +98,29 @@ __global__ __launch_bounds__(64 * NdWaves<NR>::v) void k_nd_blocks(
     stop_test_wg<NR>(opb, npb, init, sc, sh, red);
     return;
   }
-  const int b = wg_blk[blockIdx.x];
-  const int row0 = wg_row0[blockIdx.x];
-  const int64_t o = blk_off[b];
-  const int s = (int)(blk_off[b + 1] - o);
+  const int64_t o = W.o;
+  const int s = W.s, row0 = W.row0;
+  const int w = threadIdx.x >> 6;
+  const int per = (s + NW - 1) / NW;
+  const int jb = min(s, w * per), je = min(s, jb + per);
+  // the first rows of the inverse, on their way while the right-hand side is
+  // formed
+  NdRows<NR, false> f;
+  f.load(binv + W.inv, s, row0, s, jb, je);
   if (from_y1) {  // pass 1: b_B - S_BT eta_T, formed by k_nd_rb
     for (int t = threadIdx.x; t < s * NR; t += blockDim.x) rhs[t] = y1[(size_t)o * NR + t];
   } else {
     for (int t = threadIdx.x; t < s * NR; t += blockDim.x) {
       const int j = t / NR, k = t % NR;
-      const int64_t n = ord[o + j];
-      double v = bpart[(size_t)(2 * n) * NR + k] + bpart[(size_t)(2 * n + 1) * NR + k];
+      double v = bpart[(size_t)(2 * (o + j)) * NR + k] + bpart[(size_t)(2 * (o + j) + 1) * NR + k];
       if (pass)
         v = nd_sub_couplings<NR>(v, b_ptr[o + j], b_ptr[o + j + 1], b_top, b_val, eta2, k);
       rhs[t] = v;
     }
   }
   __syncthreads();
-  const int w = threadIdx.x >> 6;
-  const int per = (s + NW - 1) / NW;
-  const int jb = min(s, w * per), je = min(s, jb + per);
   nd_d4 acc[4];
-  nd_wave_product<NR, false>(binv + inv_off[b], s, row0, s, jb, je, rhs, 0, acc);
+  nd_wave_product<NR, false>(binv + W.inv, s, row0, s, jb, je, rhs, 0, f, acc);
   __syncthreads();  // every wave is done with rhs
   double* part = rhs;  // [NW][64][NR]
   nd_wave_each<NR>(acc, [&](int l, int k, double v) { part[(w * 64 + l) * NR + k] = v; });
@@ -148,10 +148,10 @@ __global__ __launch_bounds__(64 * NdWaves<NR>::v) void k_nd_blocks(
 template <int NR, bool PRE>
 __global__ __launch_bounds__(256) void k_nd_top(
     int R, int ldC, const double* __restrict__ cinv, int P, int per, int nrb,
-    const int32_t* __restrict__ ord_top, const double* __restrict__ bpart,
-    const int64_t* __restrict__ t_ptr, const int32_t* __restrict__ t_pos,
-    const double* __restrict__ t_val, const double* __restrict__ y1,
-    const double* __restrict__ eta2, double* __restrict__ ypart, int pcg, int init,
+    const double* __restrict__ btop, const int64_t* __restrict__ t_ptr,
+    const int32_t* __restrict__ t_pos, const double* __restrict__ t_val,
+    const double* __restrict__ y1, const double* __restrict__ eta2, double* __restrict__ ypart,
+    int pcg, int init,
     const PcgShared* sh) {
   extern __shared__ double r2[];
   __shared__ int skip;
@@ -160,6 +160,10 @@ __global__ __launch_bounds__(256) void k_nd_top(
   if (skip) return;
   const int p = blockIdx.x % P, g = blockIdx.x / P;
   const int jb = min(R, p * per), je = min(R, jb + per);
+  const int w = threadIdx.x >> 6;
+  const int rb = 4 * g + w;
+  NdRows<NR, true> f;  // the first rows of C^{-1}, as in k_nd_blocks
+  f.load(cinv, ldC, 64 * min(rb, nrb - 1), ldC, jb, je);
   const double* v = r2;  // the part's rows of r_T
   int vbase = jb;
   if (PRE) {  // formed by k_nd_rt (held in eta2 until k_nd_fold)
@@ -168,17 +172,14 @@ __global__ __launch_bounds__(256) void k_nd_top(
   } else {
     for (int t = threadIdx.x; t < (je - jb) * NR; t += blockDim.x) {
       const int j = jb + t / NR, k = t % NR;
-      const int64_t n = ord_top[j];
-      double x = bpart[(size_t)(2 * n) * NR + k] + bpart[(size_t)(2 * n + 1) * NR + k];
+      double x = btop[(size_t)(2 * j) * NR + k] + btop[(size_t)(2 * j + 1) * NR + k];
       r2[t] = nd_sub_couplings<NR>(x, t_ptr[j], t_ptr[j + 1], t_pos, t_val, y1, k);
     }
     __syncthreads();
   }
-  const int w = threadIdx.x >> 6;
-  const int rb = 4 * g + w;
   if (rb >= nrb) return;
   nd_d4 acc[4];
-  nd_wave_product<NR, true>(cinv, ldC, 64 * rb, ldC, jb, je, v, vbase, acc);
+  nd_wave_product<NR, true>(cinv, ldC, 64 * rb, ldC, jb, je, v, vbase, f, acc);
   double* out = ypart + (size_t)p * ldC * NR;
   nd_wave_each<NR>(acc, [&](int l, int k, double v) { out[(size_t)(64 * rb + l) * NR + k] = v; });
 }
@@ -206,8 +207,8 @@ __global__ __launch_bounds__(256) void k_nd_fold(int R, int ldC, int P,
   double v = 0.0;
 #pragma unroll 8
   for (int p = u; p < P; p += kNdFoldLanes) v += ypart[((size_t)p * ldC + r) * NR + k];
-#pragma unroll
-  for (int off = 1; off < kNdFoldLanes; off <<= 1) v += __shfl_xor(v, off, 64);
+  static_assert(kNdFoldLanes == 8, "three steps");
+  v = add_mirror(add_xor2(add_xor1(v)));
   if (ok && u == 0) {
     eta2[r * NR + k] = v;
     eta[(size_t)ord_top[r] * NR + k] = v;
@@ -217,8 +218,7 @@ __global__ __launch_bounds__(256) void k_nd_fold(int R, int ldC, int P,
 // r_T = b_T - S_TB y_B, one thread per (top row, column), into eta2 (which
 // holds eta_T only from k_nd_fold on)
 template <int NR>
-__global__ __launch_bounds__(256) void k_nd_rt(int R, const int32_t* __restrict__ ord_top,
-                                               const double* __restrict__ bpart,
+__global__ __launch_bounds__(256) void k_nd_rt(int R, const double* __restrict__ btop,
                                                const int64_t* __restrict__ t_ptr,
                                                const int32_t* __restrict__ t_pos,
                                                const double* __restrict__ t_val,
@@ -230,16 +230,14 @@ __global__ __launch_bounds__(256) void k_nd_rt(int R, const int32_t* __restrict_
   if (t >= (int64_t)R * NR) return;
   const int64_t j = t / NR;
   const int k = (int)(t % NR);
-  const int64_t n = ord_top[j];
-  double x = bpart[(size_t)(2 * n) * NR + k] + bpart[(size_t)(2 * n + 1) * NR + k];
+  double x = btop[(size_t)(2 * j) * NR + k] + btop[(size_t)(2 * j + 1) * NR + k];
   rt[t] = nd_sub_couplings<NR>(x, t_ptr[j], t_ptr[j + 1], t_pos, t_val, y1, k);
 }
 
 // b_B - S_BT eta_T, one thread per (block row, column), into y1 (y_B is no
 // longer needed once r_T is formed)
 template <int NR>
-__global__ __launch_bounds__(256) void k_nd_rb(int64_t nrows, const int32_t* __restrict__ ord,
-                                               const double* __restrict__ bpart,
+__global__ __launch_bounds__(256) void k_nd_rb(int64_t nrows, const double* __restrict__ bpart,
                                                const int64_t* __restrict__ b_ptr,
                                                const int32_t* __restrict__ b_top,
                                                const double* __restrict__ b_val,
@@ -251,8 +249,7 @@ __global__ __launch_bounds__(256) void k_nd_rb(int64_t nrows, const int32_t* __r
   if (t >= nrows * NR) return;
   const int64_t j = t / NR;
   const int k = (int)(t % NR);
-  const int64_t n = ord[j];
-  double x = bpart[(size_t)(2 * n) * NR + k] + bpart[(size_t)(2 * n + 1) * NR + k];
+  double x = bpart[(size_t)(2 * j) * NR + k] + bpart[(size_t)(2 * j + 1) * NR + k];
   rb[t] = nd_sub_couplings<NR>(x, b_ptr[j], b_ptr[j + 1], b_top, b_val, eta2, k);
 }
 
@@ -269,19 +266,20 @@ static void nd_solve_t(DeviceState& d, hipStream_t st, int pcg, int init) {
   const size_t shb = (size_t)std::max<int64_t>(nd.smax, 64 * NW) * NR * sizeof(double);
   // the PCG stop test rides in one extra workgroup of the first launch
   const unsigned extra = pcg ? 1u : 0u;
+  const double* btop = d.bpart + (size_t)2 * nd.nrows * NR;  // the top rows' slots
   if (nd.R > 0) {
     am_launch_shm(d, true, false, k_nd_blocks<NR>, dim3(nd.nwg + extra), dim3(64 * NW), shb, st,
-                  0, 0, nd.nwg, nd.wg_blk, nd.wg_row0, nd.blk_off, nd.inv_off, nd.binv, nd.ord,
-                  d.bpart, nd.b_ptr, nd.b_top, nd.b_val, nd.eta2, nd.y1, d.eta, pcg, init,
+                  0, 0, nd.nwg, nd.wg, nd.binv, nd.ord, d.bpart,
+                  nd.b_ptr, nd.b_top, nd.b_val, nd.eta2, nd.y1, d.eta, pcg, init,
                   d.red.pb, d.m, d.sc, d.shared);
     if (PRE)
       am_launch(d, false, false, k_nd_rt<NR>, dim3((unsigned)((nd.R * NR + 255) / 256)),
-                dim3(256), st, nd.R, nd.ord + nd.nrows, d.bpart, nd.t_ptr, nd.t_pos, nd.t_val,
+                dim3(256), st, nd.R, btop, nd.t_ptr, nd.t_pos, nd.t_val,
                 nd.y1, nd.eta2, pcg, init, d.shared);
     const int nrb = (nd.ldC + 63) / 64;
     am_launch_shm(d, false, false, k_nd_top<NR, PRE>, dim3(nd.P * ((nrb + 3) / 4)), dim3(256),
                   PRE ? 0 : (size_t)nd.per * NR * sizeof(double), st, nd.R, nd.ldC, nd.cinv, nd.P,
-                  nd.per, nrb, nd.ord + nd.nrows, d.bpart, nd.t_ptr, nd.t_pos, nd.t_val, nd.y1,
+                  nd.per, nrb, btop, nd.t_ptr, nd.t_pos, nd.t_val, nd.y1,
                   nd.eta2, nd.ypart, pcg, init, d.shared);
   }
   const unsigned nb =
@@ -291,13 +289,12 @@ static void nd_solve_t(DeviceState& d, hipStream_t st, int pcg, int init) {
               nd.ypart, nd.ord + nd.nrows, nd.eta2, d.eta, pcg, init, d.shared);
   if (PRE && nd.R > 0)
     am_launch(d, false, false, k_nd_rb<NR>, dim3((unsigned)((nd.nrows * NR + 255) / 256)),
-              dim3(256), st, nd.nrows, nd.ord, d.bpart, nd.b_ptr, nd.b_top, nd.b_val, nd.eta2,
+              dim3(256), st, nd.nrows, d.bpart, nd.b_ptr, nd.b_top, nd.b_val, nd.eta2,
               nd.y1, pcg, init, d.shared);
   // with no top rows this is the only launch (it then carries the stop test)
   const unsigned extra1 = nd.R > 0 ? 0u : extra;
   am_launch_shm(d, nd.R == 0, true, k_nd_blocks<NR>, dim3(nd.nwg + extra1), dim3(64 * NW), shb,
-                st, 1, (PRE && nd.R > 0) ? 1 : 0, nd.nwg, nd.wg_blk, nd.wg_row0, nd.blk_off,
-                nd.inv_off, nd.binv, nd.ord, d.bpart, nd.b_ptr, nd.b_top, nd.b_val, nd.eta2, nd.y1,
+                st, 1, (PRE && nd.R > 0) ? 1 : 0, nd.nwg, nd.wg, nd.binv, nd.ord, d.bpart, nd.b_ptr, nd.b_top, nd.b_val, nd.eta2, nd.y1,
                 d.eta, pcg, init, d.red.pb, d.m, d.sc, d.shared);
 }
 
