@@ -95,8 +95,8 @@ __global__ __launch_bounds__(256) void k_spmv_p(int64_t n, int w, const int32_t*
   static_assert(NT <= 4, "8 and 16 columns: k_spmv_sub");
   constexpr int KG = KGroup<NT>::v, TR = NT / KG;
   __shared__ double lds[8 * KG];
-  const int blk = blockIdx.x / TR, g = blockIdx.x % TR, k0 = g * KG;
-  const int nblk = gridDim.x / TR;
+  static_assert(TR == 1, "one group of columns");
+  const int g = 0, k0 = 0, nblk = gridDim.x, blk = xcd_part(blockIdx.x, nblk);
   auto vi = [&](int64_t row, int k) { return ((size_t)g * n + row) * KG + k; };  // vix<NT>(n, row, k0 + k)
   const int done_flag = *(volatile const int32_t*)&sh->all_done;
   const int nrhs = sh->nrhs, flexible = sh->flexible;
@@ -112,7 +112,6 @@ __global__ __launch_bounds__(256) void k_spmv_p(int64_t n, int w, const int32_t*
   double rzq[2 * KG];
 #pragma unroll
   for (int k = 0; k < 2 * KG; ++k) rzq[k] = 0.0;
-  static_assert(TR == 1, "one group of columns");
   fold_rows<2 * NT>(pd, npd, threadIdx.x, blockDim.x, rzq);  // rows of pd: (r, z) then (q, z)
   double pq[KG];
 #pragma unroll
@@ -864,29 +863,34 @@ __global__ __launch_bounds__(256) void k_update_rows(
 }
 
 // ||b - A x||^2 per column (device positions).
-template <int NR>
+template <int NR, int MAXW>
 __global__ __launch_bounds__(256) void k_true_res(int64_t n, int w, const int32_t* __restrict__ ec,
                                                   const double* __restrict__ ev,
                                                   const double* __restrict__ b,
                                                   const double* __restrict__ x, double* partial,
                                                   unsigned* counter, double* out) {
   __shared__ double lds[4 * NR];
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   double v[NR];
 #pragma unroll
   for (int k = 0; k < NR; ++k) v[k] = 0.0;
-  if (i < n) {
-    double acc[NR];
+  const int64_t i0 = (int64_t)xcd_part(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
+  for (int64_t i = i0; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    int64_t col[MAXW];
+    double a[MAXW], acc[NR];
 #pragma unroll
-    for (int k = 0; k < NR; ++k) acc[k] = b[vix<NR>(n, i, k)];
-    for (int c = 0; c < w; ++c) {
-      const int64_t col = ec[(int64_t)c * n + i];
-      const double a = ev[(int64_t)c * n + i];
-#pragma unroll
-      for (int k = 0; k < NR; ++k) acc[k] = fma(-a, x[vix<NR>(n, col, k)], acc[k]);
+    for (int c = 0; c < MAXW; ++c) {
+      col[c] = c < w ? ec[(int64_t)c * n + i] : i;
+      a[c] = c < w ? ev[(int64_t)c * n + i] : 0.0;
     }
 #pragma unroll
-    for (int k = 0; k < NR; ++k) v[k] = acc[k] * acc[k];
+    for (int k = 0; k < NR; ++k) acc[k] = b[vix<NR>(n, i, k)];
+#pragma unroll
+    for (int c = 0; c < MAXW; ++c)
+      if (c < w)
+#pragma unroll
+        for (int k = 0; k < NR; ++k) acc[k] = fma(-a[c], x[vix<NR>(n, col[c], k)], acc[k]);
+#pragma unroll
+    for (int k = 0; k < NR; ++k) v[k] = fma(acc[k], acc[k], v[k]);
   }
   block_sum<NR>(v, lds);
   if (!publish_partial<NR>(v, partial, counter, gridDim.x)) return;
@@ -1027,9 +1031,19 @@ hipError_t launch_pcg_iteration(DeviceState& d, int nr, int parity, hipStream_t 
 
 hipError_t launch_true_residual(DeviceState& d, const double* bperm, int nr, double* out2,
                                 hipStream_t s) {
-  AM_NR_SWITCH(nr, hipLaunchKernelGGL(k_true_res<NR>, dim3(nblk(d.n)), dim3(256), 0, s, d.n,
-                                      d.ell_w, d.ell_col, d.ell_val, bperm, d.x, d.red.partial,
-                                      d.red.counter + 3, out2));
+  // few enough workgroups that their turns at the counter cost nothing (128^3:
+  // 8192 of them 277 us, 1024 80 us)
+  const unsigned g = std::min(nblk(d.n), 1024u);
+  auto go = [&](auto maxw) -> hipError_t {
+    constexpr int MW = decltype(maxw)::value;
+    AM_NR_SWITCH(nr, hipLaunchKernelGGL((k_true_res<NR, MW>), dim3(g), dim3(256), 0, s, d.n,
+                                        d.ell_w, d.ell_col, d.ell_val, bperm, d.x, d.red.partial,
+                                        d.red.counter + 3, out2));
+    return hipSuccess;
+  };
+  const hipError_t e = d.ell_w <= 8 ? go(std::integral_constant<int, 8>{})
+                                    : go(std::integral_constant<int, 32>{});
+  if (e != hipSuccess) return e;
   return hipGetLastError();
 }
 

@@ -41,7 +41,7 @@ __global__ __launch_bounds__(256) void k_sres(int64_t n, int w, const int32_t* _
                                               const double* __restrict__ zin,
                                               const double* __restrict__ win,
                                               double* __restrict__ zout, double* __restrict__ t) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t i = (int64_t)xcd_part(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
   if (i >= n) return;
   int64_t col[MAXW];
   double v[MAXW];
