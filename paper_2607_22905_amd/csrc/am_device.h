@@ -201,6 +201,7 @@ struct DeviceState {
   void* cpl = nullptr;         // values (double for FP64, float otherwise)
   uint8_t* cidx = nullptr;     // column's row within its block
   std::vector<int32_t> bucket_sub[2];  // host: subdomain ids per window width 64/128
+  int32_t sub_order = 0;               // bucket_sub[0] is not in ascending order
   int32_t* d_bucket_sub[2] = {nullptr, nullptr};
   std::vector<int32_t> bucket_pair[2]; // host: (subdomain, slot) pairs per window width
   int32_t* d_bucket_pair[2] = {nullptr, nullptr};

@@ -1300,9 +1300,9 @@ hipError_t localt_shape(DeviceState& d, const double* r, double* z, const double
     const unsigned off = bk == 0 ? 0u : (unsigned)nb0;  // rows of the partials
     constexpr bool kBf = std::is_same<FT, bf16_t>::value;
     if (bk == 0) {
-      // bucket 0 lists 0 .. m-1 in order when bucket 1 is empty: the kernel
-      // then takes its subdomain from blockIdx.x (one dependent load less)
-      const int32_t* subs_arg = nb1 == 0 ? nullptr : d.d_bucket_sub[0];
+      // where bucket 0 lists 0 .. m-1 in order the kernel takes its subdomain
+      // from blockIdx.x (one dependent load less)
+      const int32_t* subs_arg = nb1 == 0 && !d.sub_order ? nullptr : d.d_bucket_sub[0];
       auto go = [&](auto kern, int threads, size_t lds, auto... tail) {
         am_launch_shm(d, first, last, kern, dim3(nb), dim3(threads), lds, s, subs_arg, d.desc,
                       (const FT*)d.Lc, (const IT*)d.invd, (const IT*)d.cpl, d.cidx, r, z, mode,

@@ -659,9 +659,9 @@ __device__ __forceinline__ bool local_prologue(int mode, int ns, int64_t i0,
 // barrier and a round of partial sums per step: 1.0 us a step with four waves
 // against 0.45.)  Blocks further out than HT are read again on the way back.
 // x goes to LDS, and all threads form z = x + sum eta phat and the PCG dots
-// over the rows at the end.  128^3 (4096 boxes), FP64: 178 us for 0.74 GB, the
+// over the rows at the end.  128^3 (4096 boxes), FP64: 158 us for 0.74 GB, the
 // loads of one workgroup beside the chain of the other on its CU (band tiles
-// read once per sweep, 32 barriers: 342 us for 2.1 GB); FP32 98 us; 64^3 21 us
+// read once per sweep, 32 barriers: 342 us for 2.1 GB); FP32 94 us; 64^3 21 us
 // (52 us with the interface rows formed inside).
 template <typename FT, int NT, int HT> constexpr int tri_waves() {
   constexpr int regs = (2 * HT + 1) * 4 * (int)sizeof(FT) + 16 * NT + 72;
@@ -978,6 +978,18 @@ __global__ __launch_bounds__(128, (tri_waves<FT, NT, HT>())) void k_tri_solve(
       out[(size_t)(base + row) * NT + k] = z[k];
     }
   };
+  // the resident rows are finished RB at a time with their loads together;
+  // the first ones' loads go out before the way back (after it, their round
+  // trip stands alone at the end of the workgroup)
+  const int rows = min(r_n, T.N - r_lo);
+  constexpr int RB = NT == 1 ? 4 : NT == 2 ? 2 : 1;
+  RowIn ri[RB];
+  auto load_first = [&]() AM_INLINE {
+#pragma unroll
+    for (int u = 0; u < RB; ++u) load_in(r_lo + min((int)threadIdx.x + NTHR * u, rows - 1), ri[u]);
+  };
+  constexpr bool kEarly = NT == 1 && HT == 4;  // (elsewhere the registers don't allow it)
+  if constexpr (kEarly) load_first();
 #pragma unroll
   for (int j = HT - 1; j >= 0; --j) {
     const int k = off + j;
@@ -1017,12 +1029,7 @@ __global__ __launch_bounds__(128, (tri_waves<FT, NT, HT>())) void k_tri_solve(
       finish(64 * b + lane, y, ri);
     }
   }
-  // the resident rows, RB at a time with their loads together
-  const int rows = min(r_n, T.N - r_lo);
-  constexpr int RB = NT == 1 ? 4 : NT == 2 ? 2 : 1;
-  RowIn ri[RB];
-#pragma unroll
-  for (int u = 0; u < RB; ++u) load_in(r_lo + min((int)threadIdx.x + NTHR * u, rows - 1), ri[u]);
+  if constexpr (!kEarly) load_first();
   __syncthreads();
   for (int i0r = 0; i0r < rows; i0r += RB * NTHR) {
     if (i0r > 0)
@@ -1104,7 +1111,7 @@ __device__ __forceinline__ void tri_mf_pass(V (&acc)[2], AF&& afn, BF&& bfn) {
 // groups form the middle block's x themselves: no exchange on the way back.
 // Bound by the LDS and memory latencies of a step (about 5 us with two
 // workgroups on the CU, 0.5 of it the product): 1721 subdomains of 200-800
-// cells, 16 columns, FP64: 366 us (band tiles, four products a step: 458).
+// cells, 16 columns, FP64: 347 us (band tiles, four products a step: 458).
 // Eight waves of 128 registers spilled, and their scratch loads waited behind
 // the tile loads: 885 us.
 constexpr int kTriTP = 66;
