@@ -468,6 +468,7 @@ static am_status setup_impl(const am_csr* A, const int32_t* part, int32_t nparts
     return fail(nullptr, AM_ERR_ARG, "invalid options");
   am_handle h = new am_handle_s();
   h->opt = opt;
+  HostTeam team;
   auto bail = [&](am_status s) {
     std::string msg = h->err;
     algmortar_destroy(h);

@@ -6,7 +6,10 @@
 #include <algorithm>
 
 #include <atomic>
+#include <condition_variable>
 #include <cstdint>
+#include <functional>
+#include <mutex>
 #include <string>
 #include <thread>
 #include <vector>
@@ -18,6 +21,76 @@ namespace am {
 // Host threads for the set-up loops: ALGMORTAR_HOST_THREADS if set, else the
 // hardware threads, at most 16.
 int host_threads();
+
+// The threads of one set-up call: made at its first parallel loop, waiting
+// between the loops, joined with the call.  (A set-up has a dozen loops of
+// 0.1-0.5 ms; 15 new threads for each of them took about as long again.)  The
+// object lives on the caller's stack and belongs to the calling thread, so
+// set-ups on several threads have a team each; a loop inside a loop, or
+// without a team, makes its own threads.
+class HostTeam {
+ public:
+  HostTeam() : prev_(current()) { current() = this; }
+  ~HostTeam() {
+    current() = prev_;
+    {
+      std::lock_guard<std::mutex> l(m_);
+      stop_ = true;
+    }
+    wake_.notify_all();
+    for (auto& th : pool_) th.join();
+  }
+  HostTeam(const HostTeam&) = delete;
+  HostTeam& operator=(const HostTeam&) = delete;
+  static HostTeam*& current() {
+    static thread_local HostTeam* t = nullptr;
+    return t;
+  }
+  // work() on the caller and up to nt - 1 of the team's threads; returns when
+  // every call of it has returned (false: not run, a loop is under way)
+  bool run(const std::function<void()>& work, int nt) {
+    {
+      std::lock_guard<std::mutex> l(m_);
+      if (job_) return false;
+      job_ = &work;
+      seats_ = nt - 1;
+      ++epoch_;
+    }
+    while ((int)pool_.size() < nt - 1) pool_.emplace_back([this] { serve(); });
+    wake_.notify_all();
+    work();
+    std::unique_lock<std::mutex> l(m_);
+    job_ = nullptr;  // a thread that wakes from now on finds nothing to do
+    done_.wait(l, [this] { return active_ == 0; });
+    return true;
+  }
+
+ private:
+  void serve() {
+    uint64_t seen = 0;
+    std::unique_lock<std::mutex> l(m_);
+    for (;;) {
+      wake_.wait(l, [&] { return stop_ || (job_ && epoch_ != seen && seats_ > 0); });
+      if (stop_) return;
+      seen = epoch_;
+      --seats_;
+      ++active_;
+      const std::function<void()>* w = job_;
+      l.unlock();
+      (*w)();
+      l.lock();
+      if (--active_ == 0) done_.notify_one();
+    }
+  }
+  std::mutex m_;
+  std::condition_variable wake_, done_;
+  std::vector<std::thread> pool_;
+  const std::function<void()>* job_ = nullptr;
+  uint64_t epoch_ = 0;
+  int seats_ = 0, active_ = 0;
+  bool stop_ = false;
+  HostTeam* prev_;
+};
 
 // Runs f(i) for every i in [0, n) on up to host_threads() threads (the
 // caller's included), handing out chunks of `grain` indices in increasing
@@ -39,6 +112,7 @@ void parallel_for(int64_t n, int64_t grain, F&& f) {
       for (int64_t i = lo; i < hi; ++i) f(i);
     }
   };
+  if (HostTeam* t = HostTeam::current(); t && t->run(work, nt)) return;
   std::vector<std::thread> pool;
   pool.reserve(nt - 1);
   for (int t = 1; t < nt; ++t) pool.emplace_back(work);
