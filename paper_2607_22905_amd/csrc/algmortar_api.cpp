@@ -1363,7 +1363,7 @@ am_status algmortar_apply(am_handle h, const double* r, double* z, int32_t nrhs,
   }
   HCHK(launch_permute_in(d.dperm, d.n, r, ld, d.r, nrhs, st));
   if (h->sm.steps > 0) {
-    HCHK(launch_smoothed_apply(d, h->sm, d.r, d.z, nr, st));
+    HCHK(launch_smoothed_apply(d, h->sm, d.r, d.z, false, nr, st));
   } else {
     if (d.NL > 0) {
       HCHK(launch_bpart(d, d.r, nr, st));
@@ -1494,14 +1494,13 @@ am_status algmortar_local_solve(am_handle h, const double* r, double* pbar, void
 static constexpr int kChunk = 8;  // iterations per captured graph (even: p ping-pong)
 
 // One PCG iteration of the smoothed preconditioner: the smoothed apply (some
-// 4 nu + 10 launches), the (r, z), (q, z) partials, the SpMV, the update and
+// 4 nu + 8 launches) with the (r, z), (q, z) partials, the SpMV, the update and
 // the stop test.  After the stop, the apply and the partials still run (on
 // the stopped r, into z and the partials, which nothing reads any more);
 // the SpMV, update and stop test return at once.
 static hipError_t smoothed_iteration(DeviceState& d, SmoothDevice& sm, int nr, int parity,
                                      hipStream_t st) {
-  hipError_t e = launch_smoothed_apply(d, sm, d.r, d.z, nr, st);
-  if (e == hipSuccess) e = launch_smooth_dots(d, nr, st);
+  hipError_t e = launch_smoothed_apply(d, sm, d.r, d.z, true, nr, st);
   if (e == hipSuccess) e = launch_pcg_spmv(d, nr, parity, st);
   if (e == hipSuccess) e = launch_pcg_update(d, nr, parity, st);
   if (e == hipSuccess) e = launch_stop_test(d, nr, 0, st);

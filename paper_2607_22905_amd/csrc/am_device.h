@@ -375,11 +375,10 @@ struct SmoothDevice {
   double* t_am = nullptr;           // [n * max_nrhs] correction input, AlgMortar order
   double* w_am = nullptr;           // [n * max_nrhs] correction output
 };
-// z_am = M^{-1} r_am (both in d's device order, node vectors of nr columns)
+// z_am = M^{-1} r_am (both in d's device order, node vectors of nr columns); dots:
+// with the (r, z), (q, z) partials of d's PCG vectors in d.red.pd (m workgroups)
 hipError_t launch_smoothed_apply(DeviceState& d, SmoothDevice& sm, const double* r_am,
-                                 double* z_am, int nr, hipStream_t s);
-// (r, z) and (q, z) partials of d's PCG vectors into d.red.pd (m workgroups)
-hipError_t launch_smooth_dots(DeviceState& d, int nrhs, hipStream_t s);
+                                 double* z_am, bool dots, int nr, hipStream_t s);
 
 // ---- launchers (kernels_tpfa.hip) ----
 struct TpfaDevice {

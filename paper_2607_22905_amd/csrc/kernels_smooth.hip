@@ -33,16 +33,20 @@ __global__ __launch_bounds__(256) void k_gather(int64_t n, const int32_t* __rest
 }
 
 // u = zin (+ win); zout[i] = u[i] when zout is set; t[i] = r[i] - (A u)[i]
-// (ELL, column-major, padded entries point at the row itself with value 0)
+// (ELL, column-major, padded entries point at the row itself with value 0),
+// stored at tmap[i] when tmap is set (the other device order: a gather launch
+// less)
 template <int NT, int MAXW>
 __global__ __launch_bounds__(256) void k_sres(int64_t n, int w, const int32_t* __restrict__ ec,
                                               const double* __restrict__ ev,
                                               const double* __restrict__ r,
                                               const double* __restrict__ zin,
                                               const double* __restrict__ win,
-                                              double* __restrict__ zout, double* __restrict__ t) {
+                                              double* __restrict__ zout, double* __restrict__ t,
+                                              const int32_t* __restrict__ tmap) {
   const int64_t i = (int64_t)xcd_part(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
   if (i >= n) return;
+  const int64_t it = tmap ? tmap[i] : i;
   int64_t col[MAXW];
   double v[MAXW];
 #pragma unroll
@@ -67,31 +71,40 @@ __global__ __launch_bounds__(256) void k_sres(int64_t n, int w, const int32_t* _
       if (win) u += win[o];
       zout[o] = u;
     }
-    t[o] = acc;
+    t[vix<NT>(n, it, k)] = acc;
   }
 }
 
-// (r, z) and (q, z) partials of workgroup b over rows [b n / m, (b+1) n / m),
-// in the layout the PCG SpMV launch folds: pd[b][0..NT) and pd[b][NT..2NT).
+// z[i] = a[map[i]] (+ b[map[i]]) and the (r, z) and (q, z) partials of
+// workgroup b over rows [b n / m, (b+1) n / m), in the layout the PCG SpMV
+// launch folds: pd[b][0..NT) and pd[b][NT..2NT).
 template <int NT>
-__global__ __launch_bounds__(256) void k_dots(int64_t n, int m, const double* __restrict__ r,
-                                              const double* __restrict__ z,
-                                              const double* __restrict__ q,
-                                              double* __restrict__ pd) {
+__global__ __launch_bounds__(256) void k_gather_dots(int64_t n, int m,
+                                                     const int32_t* __restrict__ map,
+                                                     const double* __restrict__ a,
+                                                     const double* __restrict__ b2,
+                                                     const double* __restrict__ r,
+                                                     const double* __restrict__ q,
+                                                     double* __restrict__ z,
+                                                     double* __restrict__ pd) {
   __shared__ double lds[4 * 2 * NT];
   const int b = blockIdx.x;
   const int64_t r0 = n * b / m, r1 = n * (b + 1) / m;
   double v[2 * NT];
 #pragma unroll
   for (int t = 0; t < 2 * NT; ++t) v[t] = 0.0;
-  for (int64_t i = r0 + threadIdx.x; i < r1; i += blockDim.x)
+  for (int64_t i = r0 + threadIdx.x; i < r1; i += blockDim.x) {
+    const int64_t j = map[i];
 #pragma unroll
     for (int k = 0; k < NT; ++k) {
-      const size_t o = vix<NT>(n, i, k);
-      const double zv = z[o];
+      const size_t o = vix<NT>(n, i, k), oj = vix<NT>(n, j, k);
+      double zv = a[oj];
+      if (b2) zv += b2[oj];
+      z[o] = zv;
       v[k] = fma(r[o], zv, v[k]);
       v[NT + k] = fma(q[o], zv, v[NT + k]);
     }
+  }
   block_sum<2 * NT>(v, lds);
   if (threadIdx.x == 0)
 #pragma unroll
@@ -118,13 +131,14 @@ static hipError_t gather(int64_t n, const int32_t* map, const double* a, const d
 }
 
 static hipError_t sres(const DeviceState& D, const double* r, const double* zin, const double* win,
-                       double* zout, double* t, int nr, hipStream_t s) {
+                       double* zout, double* t, int nr, hipStream_t s,
+                       const int32_t* tmap = nullptr) {
   if (D.ell_w <= 8) {
     AM_NR_SWITCH(nr, hipLaunchKernelGGL((k_sres<NR, 8>), dim3(nblk(D.n)), dim3(256), 0, s, D.n,
-                                        D.ell_w, D.ell_col, D.ell_val, r, zin, win, zout, t));
+                                        D.ell_w, D.ell_col, D.ell_val, r, zin, win, zout, t, tmap));
   } else {
     AM_NR_SWITCH(nr, hipLaunchKernelGGL((k_sres<NR, 32>), dim3(nblk(D.n)), dim3(256), 0, s, D.n,
-                                        D.ell_w, D.ell_col, D.ell_val, r, zin, win, zout, t));
+                                        D.ell_w, D.ell_col, D.ell_val, r, zin, win, zout, t, tmap));
   }
   return hipGetLastError();
 }
@@ -136,7 +150,7 @@ static hipError_t sres(const DeviceState& D, const double* r, const double* zin,
   } while (0)
 
 hipError_t launch_smoothed_apply(DeviceState& d, SmoothDevice& sm, const double* r_am,
-                                 double* z_am, int nr, hipStream_t s) {
+                                 double* z_am, bool dots, int nr, hipStream_t s) {
   DeviceState& D = *sm.bj;
   if (sm.steps < 1 || D.n != d.n || nr > D.max_nrhs || nr > d.max_nrhs)
     return hipErrorInvalidValue;
@@ -157,9 +171,8 @@ hipError_t launch_smoothed_apply(DeviceState& d, SmoothDevice& sm, const double*
     pend = w;
   }
   // the AlgMortar correction of r - A z, in its own device order
-  SM_TRY(sres(D, rb, zc, pend, zn, t, nr, s));
+  SM_TRY(sres(D, rb, zc, pend, zn, sm.t_am, nr, s, sm.to_bj));
   std::swap(zc, zn);
-  SM_TRY(gather(n, sm.to_am, t, nullptr, sm.t_am, nr, s));
   if (d.NL > 0) {
     SM_TRY(launch_bpart(d, sm.t_am, nr, s));
     if (!eta_inline(d, nr)) SM_TRY(launch_iface_gemv(d, nr, 0, 0, s));
@@ -174,13 +187,10 @@ hipError_t launch_smoothed_apply(DeviceState& d, SmoothDevice& sm, const double*
     SM_TRY(launch_local_sweep(D, t, w, D.eta, nr, 0, s));
     pend = w;
   }
-  return gather(n, sm.to_am, zc, pend, z_am, nr, s);
-}
-
-hipError_t launch_smooth_dots(DeviceState& d, int nr, hipStream_t s) {
+  if (!dots) return gather(n, sm.to_am, zc, pend, z_am, nr, s);
   if (d.m < 1) return hipErrorInvalidValue;
-  AM_NR_SWITCH(nr, hipLaunchKernelGGL(k_dots<NR>, dim3((unsigned)d.m), dim3(256), 0, s, d.n, d.m,
-                                      d.r, d.z, d.q, d.red.pd));
+  AM_NR_SWITCH(nr, hipLaunchKernelGGL(k_gather_dots<NR>, dim3((unsigned)d.m), dim3(256), 0, s, n,
+                                      d.m, sm.to_am, zc, pend, d.r, d.q, z_am, d.red.pd));
   return hipGetLastError();
 }
 
