@@ -1361,12 +1361,13 @@ am_status algmortar_apply(am_handle h, const double* r, double* z, int32_t nrhs,
     am_status ts = autotune_tiles(h->bj, nr);
     if (ts != AM_OK) return fail(h, ts, h->bj->err);
   }
-  HCHK(launch_permute_in(d.dperm, d.n, r, ld, d.r, nrhs, st));
+  const bool coarse = d.NL > 0 && h->sm.steps == 0;
+  if (!coarse) HCHK(launch_permute_in(d.dperm, d.n, r, ld, d.r, nrhs, st));
   if (h->sm.steps > 0) {
     HCHK(launch_smoothed_apply(d, h->sm, d.r, d.z, false, nr, st));
   } else {
-    if (d.NL > 0) {
-      HCHK(launch_bpart(d, d.r, nr, st));
+    if (coarse) {
+      HCHK(launch_bpart_in(d, r, ld, nrhs, nr, st));
       if (!eta_inline(d, nr)) HCHK(launch_iface_gemv(d, nr, 0, 0, st));
     }
     HCHK(launch_local_sweep(d, d.r, d.z, d.eta, nr, 1, st));
@@ -1466,13 +1467,14 @@ am_status algmortar_apply_static(am_handle h, const double* r, double* z, int32_
       d.ypart = sy;
     }
   }
-  // columns nrhs .. nr-1 of the padded block: zeros (the array keeps the last
-  // call's contents)
-  if (nrhs < nr) HCHK(launch_fill(d.r, d.n * nr, 0.0, st));
-  HCHK(launch_permute_in(d.dperm, d.n, r, ld, d.r, nrhs, st));
   if (d.NL > 0) {
-    HCHK(launch_bpart(d, d.r, nr, st));
+    HCHK(launch_bpart_in(d, r, ld, nrhs, nr, st));
     if (!eta_inline(d, nr)) HCHK(launch_iface_gemv(d, nr, 0, 0, st));
+  } else {
+    // columns nrhs .. nr-1 of the padded block: zeros (the array keeps the
+    // last call's contents)
+    if (nrhs < nr) HCHK(launch_fill(d.r, d.n * nr, 0.0, st));
+    HCHK(launch_permute_in(d.dperm, d.n, r, ld, d.r, nrhs, st));
   }
   HCHK(launch_local_sweep(d, d.r, d.z, d.eta, nr, 1, st));
   HCHK(launch_permute_out(d.dperm, d.n, d.z, z, ld, nrhs, st));

@@ -340,28 +340,45 @@ __device__ __forceinline__ void stop_test_wg(const double* __restrict__ pb, int 
 // b_n = bpart[2n] + bpart[2n+1] = -sum_{e in E_n} a_e (pbar_k + pbar_l)/2.
 // (A_s is symmetric and phat^(n)_s = A_s^{-1}(-B_s psi_n) = 4 A_s^{-1} w with
 // w_k = -sum a_e / 2 the weights of the edge average.)
-template <int NR>
+// GATHER: r (device order, nrhs columns and zeros) is first formed from src (the
+// caller's order, column k at k ld) and stored, which saves an application the
+// launch and the pass of a permutation.
+template <int NR, bool GATHER>
 __device__ __forceinline__ void bpart_sub(int s, int64_t n, const int64_t* __restrict__ sub_ptr,
                                           const int64_t* __restrict__ isub_ptr,
                                           const int64_t* __restrict__ mbf_off,
                                           const double* __restrict__ mbf,
-                                          const int64_t* __restrict__ bdst, const double* r,
-                                          double* bpart, double* lds) {
-  constexpr int QB = NR <= 2 ? 8 : (NR <= 4 ? 4 : (NR <= 8 ? 2 : 1));  // slots per round
+                                          const int64_t* __restrict__ bdst,
+                                          const int32_t* __restrict__ dperm, const double* src,
+                                          int64_t ld, int nrhs, double* r, double* bpart,
+                                          double* lds) {
+  constexpr int QB = NR <= 4 ? 8 : NR <= 8 ? 2 : 1;  // slots per round
   const int64_t base = sub_ptr[s];
   const int N = (int)(sub_ptr[s + 1] - base);
   const int64_t i0 = isub_ptr[s];
   const int ns = (int)(isub_ptr[s + 1] - i0);
   const double* P = mbf + mbf_off[s];
-  for (int q0 = 0; q0 < ns; q0 += QB) {
+  const int tid = threadIdx.x, tq = tid / NR;  // the slot whose sum this thread will hold
+  int q0 = 0;
+  do {
+    const bool mine = tq < QB && q0 + tq < ns;
+    const int64_t bd = mine ? bdst[i0 + q0 + tq] : 0;
     double v[QB * NR];
 #pragma unroll
     for (int t = 0; t < QB * NR; ++t) v[t] = 0.0;
 #pragma unroll 2
-    for (int row = threadIdx.x; row < N; row += blockDim.x) {
+    for (int row = tid; row < N; row += blockDim.x) {
       double rv[NR];
+      if (GATHER && q0 == 0) {
+        const int64_t o = dperm[base + row];
 #pragma unroll
-      for (int k = 0; k < NR; ++k) rv[k] = r[vix<NR>(n, base + row, k)];
+        for (int k = 0; k < NR; ++k) rv[k] = k < nrhs ? src[k * ld + o] : 0.0;
+#pragma unroll
+        for (int k = 0; k < NR; ++k) r[vix<NR>(n, base + row, k)] = rv[k];
+      } else {
+#pragma unroll
+        for (int k = 0; k < NR; ++k) rv[k] = r[vix<NR>(n, base + row, k)];
+      }
 #pragma unroll
       for (int qq = 0; qq < QB; ++qq) {
         const double ph = (q0 + qq < ns) ? P[(size_t)(q0 + qq) * N + row] : 0.0;
@@ -369,15 +386,10 @@ __device__ __forceinline__ void bpart_sub(int s, int64_t n, const int64_t* __res
         for (int k = 0; k < NR; ++k) v[qq * NR + k] = fma(ph, rv[k], v[qq * NR + k]);
       }
     }
-    block_sum<QB * NR>(v, lds);
-    if (threadIdx.x == 0)
-#pragma unroll
-      for (int qq = 0; qq < QB; ++qq)
-        if (q0 + qq < ns)
-#pragma unroll
-          for (int k = 0; k < NR; ++k)
-            bpart[(size_t)bdst[i0 + q0 + qq] * NR + k] = 0.25 * v[qq * NR + k];
-  }
+    const double sum = block_sum_spread<QB * NR>(v, lds);
+    if (mine) bpart[(size_t)bd * NR + tid % NR] = 0.25 * sum;
+    q0 += QB;
+  } while (q0 < ns);
 }
 
 // ---------------------------------------------------------------------------

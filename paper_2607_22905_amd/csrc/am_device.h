@@ -273,7 +273,11 @@ hipError_t launch_invert_diag(DeviceState& d, hipStream_t s);
 // z = A_i^{-1} r (+ prolongation with eta when eta != nullptr); dots when dot_out
 hipError_t launch_local_sweep(DeviceState& d, const double* r, double* z, const double* eta,
                               int nrhs, int mode, hipStream_t s);
-hipError_t launch_bpart(DeviceState& d, const double* r, int nrhs, hipStream_t s);
+hipError_t launch_bpart(DeviceState& d, double* r, int nr, hipStream_t s);
+// the same from the caller's vector src (its order, nrhs columns of stride ld),
+// which is also brought into d.r (nr columns, zeros beyond nrhs)
+hipError_t launch_bpart_in(DeviceState& d, const double* src, int64_t ld, int nrhs, int nr,
+                           hipStream_t s);
 
 // Whether the local kernel forms its own rows of eta = S^{-1} b: every
 // workgroup then reads max_ni rows of S^{-1} with its few waves, which pays

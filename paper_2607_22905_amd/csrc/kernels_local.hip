@@ -66,17 +66,34 @@ hipError_t launch_local_sweep(DeviceState& d, const double* r, double* z, const 
   }
 }
 
-hipError_t launch_bpart(DeviceState& d, const double* r, int nrhs, hipStream_t st) {
-  const dim3 g(d.m), b(256);
-  switch (nrhs) {
-    case 1: hipLaunchKernelGGL(k_bpart<1>, g, b, 0, st, d.n, d.sub_ptr, d.isub_ptr, d.mbf_off, d.mbf, d.bdst, r, d.bpart); break;
-    case 2: hipLaunchKernelGGL(k_bpart<2>, g, b, 0, st, d.n, d.sub_ptr, d.isub_ptr, d.mbf_off, d.mbf, d.bdst, r, d.bpart); break;
-    case 4: hipLaunchKernelGGL(k_bpart<4>, g, b, 0, st, d.n, d.sub_ptr, d.isub_ptr, d.mbf_off, d.mbf, d.bdst, r, d.bpart); break;
-    case 8: hipLaunchKernelGGL(k_bpart<8>, g, b, 0, st, d.n, d.sub_ptr, d.isub_ptr, d.mbf_off, d.mbf, d.bdst, r, d.bpart); break;
-    case 16: hipLaunchKernelGGL(k_bpart<16>, g, b, 0, st, d.n, d.sub_ptr, d.isub_ptr, d.mbf_off, d.mbf, d.bdst, r, d.bpart); break;
+template <int NR>
+static void bpart_t(DeviceState& d, const double* src, int64_t ld, int nrhs, double* r,
+                    hipStream_t st) {
+  auto kern = src ? &k_bpart<NR, true> : &k_bpart<NR, false>;
+  hipLaunchKernelGGL(kern, dim3(d.m), dim3(256), 0, st, d.n, d.sub_ptr, d.isub_ptr, d.mbf_off,
+                     d.mbf, d.bdst, d.dperm, src, ld, nrhs, r, d.bpart);
+}
+
+static hipError_t bpart(DeviceState& d, const double* src, int64_t ld, int nrhs, double* r, int nr,
+                        hipStream_t st) {
+  switch (nr) {
+    case 1: bpart_t<1>(d, src, ld, nrhs, r, st); break;
+    case 2: bpart_t<2>(d, src, ld, nrhs, r, st); break;
+    case 4: bpart_t<4>(d, src, ld, nrhs, r, st); break;
+    case 8: bpart_t<8>(d, src, ld, nrhs, r, st); break;
+    case 16: bpart_t<16>(d, src, ld, nrhs, r, st); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+hipError_t launch_bpart(DeviceState& d, double* r, int nr, hipStream_t st) {
+  return bpart(d, nullptr, 0, nr, r, nr, st);
+}
+
+hipError_t launch_bpart_in(DeviceState& d, const double* src, int64_t ld, int nrhs, int nr,
+                           hipStream_t st) {
+  return bpart(d, src, ld, nrhs, d.r, nr, st);
 }
 
 // The stop test of a PCG iteration as a launch of its own (one wave): used

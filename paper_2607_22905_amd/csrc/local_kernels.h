@@ -1157,15 +1157,18 @@ __global__ __launch_bounds__(64) void k_mbf(
   bwd_sweep<FT, C, 1>(N, NP, Lr + fac_off[s], col, pre, post);
 }
 
-template <int NR>
+template <int NR, bool GATHER>
 __global__ __launch_bounds__(256) void k_bpart(int64_t n, const int64_t* __restrict__ sub_ptr,
                                                const int64_t* __restrict__ isub_ptr,
                                                const int64_t* __restrict__ mbf_off,
                                                const double* __restrict__ mbf,
                                                const int64_t* __restrict__ bdst,
-                                               const double* __restrict__ r, double* bpart) {
-  __shared__ double lds[4 * 16];  // block sums of up to 16 values
-  bpart_sub<NR>(blockIdx.x, n, sub_ptr, isub_ptr, mbf_off, mbf, bdst, r, bpart, lds);
+                                               const int32_t* __restrict__ dperm,
+                                               const double* src, int64_t ld, int nrhs, double* r,
+                                               double* bpart) {
+  __shared__ double lds[4 * 32];  // block sums of up to 32 values
+  bpart_sub<NR, GATHER>(blockIdx.x, n, sub_ptr, isub_ptr, mbf_off, mbf, bdst, dperm, src, ld, nrhs,
+                        r, bpart, lds);
 }
 
 // ---------------------------------------------------------------------------
