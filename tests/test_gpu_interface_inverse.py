@@ -9,9 +9,11 @@ to the inverse."""
 import numpy as np
 import pytest
 
-import paper_2607_22905_amd as am
-from tests.test_gpu_block_inverse import _band_matrix
-from workloads import make_config
+torch = pytest.importorskip("torch")
+
+import paper_2607_22905_amd as am  # noqa: E402
+from tests.test_gpu_block_inverse import _band_matrix  # noqa: E402
+from workloads import make_config  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
