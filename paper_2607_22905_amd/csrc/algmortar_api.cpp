@@ -1620,25 +1620,17 @@ static am_status pcg_impl(am_handle h, const double* b, double* x, int32_t nrhs,
   HCHK(hipStreamSynchronize((hipStream_t)stream));
   hipStream_t st = h->own;
   const int nr = pow2_at_least(nrhs);
-  const int64_t nv = d.n * nr;
   {
     am_status ts = autotune_tiles(h, nr);
     if (ts != AM_OK) return ts;
     if (smooth && (ts = autotune_tiles(h->bj, nr)) != AM_OK) return fail(h, ts, h->bj->err);
   }
   HCHK(hipEventRecord(h->ev0, st));
-  HCHK(launch_permute_in(d.dperm, d.n, b, ld, d.r, nrhs, st));
-  HCHK(launch_permute_in(d.dperm, d.n, b, ld, h->bp, nrhs, st));
-  HCHK(launch_fill(d.x, nv, 0.0, st));
-  HCHK(launch_fill(d.z, nv, 0.0, st));
-  HCHK(launch_fill(d.q, nv, 0.0, st));
-  HCHK(launch_fill(d.p[0], nv, 0.0, st));
-  HCHK(launch_fill(d.p[1], nv, 0.0, st));
-  HCHK(launch_fill(d.eta, (int64_t)std::max<int32_t>(d.ldS, 1) * nr, 0.0, st));
   // the flexible beta where the preconditioner is not a fixed symmetric
   // operator: reduced-precision factors, an interface solve stopped by a
   // tolerance
-  HCHK(launch_pcg_init(d, nr, tol, maxit, (d.prec != AM_FP64 || d.ix.on) ? 1 : 0, st));
+  HCHK(launch_pcg_begin(d, b, ld, nrhs, h->bp, nr, tol, maxit,
+                        (d.prec != AM_FP64 || d.ix.on) ? 1 : 0, st));
   // The smoothed preconditioner runs the same chunks of iterations, its
   // iteration being smoothed_iteration; its first residual norm and stop
   // test come from the update launch in its initial form.

@@ -334,6 +334,9 @@ hipError_t launch_permute_in(const int32_t* dperm, int64_t n, const double* src,
 hipError_t launch_permute_out(const int32_t* dperm, int64_t n, const double* src, double* dst,
                               int64_t ld, int nrhs, hipStream_t s);
 hipError_t launch_fill(double* p, int64_t count, double v, hipStream_t s);
+// the vectors and scalars of a solve of b (the caller's order), bp: b in device order
+hipError_t launch_pcg_begin(DeviceState& d, const double* b, int64_t ld, int nrhs, double* bp,
+                            int nr, double tol, int maxit, int flexible, hipStream_t s);
 hipError_t launch_pcg_init(DeviceState& d, int nrhs, double tol, int maxit, int flexible,
                            hipStream_t s);
 hipError_t launch_pcg_iteration(DeviceState& d, int nrhs, int parity, hipStream_t s);

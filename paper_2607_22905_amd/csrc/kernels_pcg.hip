@@ -21,27 +21,35 @@
 
 namespace am {
 
+// Caller's vectors (its order, column k at k ld) to device order and back: a
+// thread takes up to four columns of a row, so that the lanes of a row with 8
+// or 16 columns write its line together.
 template <int NR>
 __global__ __launch_bounds__(256) void k_permute_in(const int32_t* __restrict__ dperm, int64_t n,
                                                     const double* __restrict__ src, int64_t ld,
                                                     int nrhs, double* __restrict__ dst) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  constexpr int KG = KGroup<NR>::v, TR = NR / KG;
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, i = t / TR;
+  const int k0 = (int)(t % TR) * KG;
   if (i >= n) return;
   const int64_t o = dperm[i];
 #pragma unroll
-  for (int k = 0; k < NR; ++k) dst[vix<NR>(n, i, k)] = k < nrhs ? src[k * ld + o] : 0.0;
+  for (int k = 0; k < KG; ++k)
+    dst[vix<NR>(n, i, k0 + k)] = k0 + k < nrhs ? src[(k0 + k) * ld + o] : 0.0;
 }
 
 template <int NR>
 __global__ __launch_bounds__(256) void k_permute_out(const int32_t* __restrict__ dperm, int64_t n,
                                                      const double* __restrict__ src, int nrhs,
                                                      double* __restrict__ dst, int64_t ld) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  constexpr int KG = KGroup<NR>::v, TR = NR / KG;
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, i = t / TR;
+  const int k0 = (int)(t % TR) * KG;
   if (i >= n) return;
   const int64_t o = dperm[i];
 #pragma unroll
-  for (int k = 0; k < NR; ++k)
-    if (k < nrhs) dst[k * ld + o] = src[vix<NR>(n, i, k)];
+  for (int k = 0; k < KG; ++k)
+    if (k0 + k < nrhs) dst[(k0 + k) * ld + o] = src[vix<NR>(n, i, k0 + k)];
 }
 
 __global__ __launch_bounds__(256) void k_fill(double* p, int64_t cnt, double v) {
@@ -49,9 +57,8 @@ __global__ __launch_bounds__(256) void k_fill(double* p, int64_t cnt, double v) 
   if (i < cnt) p[i] = v;
 }
 
-__global__ void k_init_scalars(PcgScalars* sc, PcgShared* sh, int nr, int nrhs, double tol2,
-                               int maxit, int flexible) {
-  const int k = threadIdx.x;
+__device__ __forceinline__ void init_scalars(int k, PcgScalars* sc, PcgShared* sh, int nr,
+                                             double tol2, int maxit, int flexible) {
   if (k < nr) {
     PcgScalars& S = sc[k];
     S.rzv[0] = S.rzv[1] = 0.0;
@@ -68,7 +75,42 @@ __global__ void k_init_scalars(PcgScalars* sc, PcgShared* sh, int nr, int nrhs, 
     sh->flexible = flexible;
     sh->all_done = 0;
   }
-  (void)nrhs;
+}
+
+__global__ void k_init_scalars(PcgScalars* sc, PcgShared* sh, int nr, double tol2, int maxit,
+                               int flexible) {
+  init_scalars(threadIdx.x, sc, sh, nr, tol2, maxit, flexible);
+}
+
+// The state of a solve in one launch (two permutations, six fills and the
+// scalars one by one: about 35 us before the first iteration): b in device
+// order as r and for the true residual, zeros elsewhere.
+template <int NR>
+__global__ __launch_bounds__(256) void k_pcg_begin(
+    const int32_t* __restrict__ dperm, int64_t n, const double* src, int64_t ld, int nrhs,
+    double* __restrict__ r, double* __restrict__ bp, double* __restrict__ x,
+    double* __restrict__ z, double* __restrict__ q, double* __restrict__ p0,
+    double* __restrict__ p1, double* __restrict__ eta, int64_t neta, PcgScalars* sc, PcgShared* sh,
+    double tol2, int maxit, int flexible) {
+  constexpr int KG = KGroup<NR>::v, TR = NR / KG;
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, i = t / TR;
+  const int k0 = (int)(t % TR) * KG;
+  if (blockIdx.x == 0) init_scalars(threadIdx.x, sc, sh, NR, tol2, maxit, flexible);
+  for (int64_t e = t; e < neta; e += (int64_t)gridDim.x * blockDim.x) eta[e] = 0.0;
+  if (i >= n) return;
+  const int64_t o = dperm[i];
+#pragma unroll
+  for (int k = 0; k < KG; ++k) {
+    const size_t d = vix<NR>(n, i, k0 + k);
+    x[d] = 0.0;
+    z[d] = 0.0;
+    q[d] = 0.0;
+    p0[d] = 0.0;
+    p1[d] = 0.0;
+    const double v = k0 + k < nrhs ? src[(k0 + k) * ld + o] : 0.0;
+    r[d] = v;
+    bp[d] = v;
+  }
 }
 
 // Right-hand sides per workgroup of the PCG kernels: a workgroup takes the
@@ -921,8 +963,8 @@ hipError_t launch_permute_in(const int32_t* dperm, int64_t n, const double* src,
                              double* dst, int nrhs, hipStream_t s) {
   int nr = 1;
   while (nr < nrhs) nr *= 2;
-  AM_NR_SWITCH(nr, hipLaunchKernelGGL(k_permute_in<NR>, dim3(nblk(n)), dim3(256), 0, s, dperm, n,
-                                      src, ld, nrhs, dst));
+  AM_NR_SWITCH(nr, hipLaunchKernelGGL(k_permute_in<NR>, dim3(nblk(n * (NR / KGroup<NR>::v))),
+                                      dim3(256), 0, s, dperm, n, src, ld, nrhs, dst));
   return hipGetLastError();
 }
 
@@ -930,8 +972,8 @@ hipError_t launch_permute_out(const int32_t* dperm, int64_t n, const double* src
                               int64_t ld, int nrhs, hipStream_t s) {
   int nr = 1;
   while (nr < nrhs) nr *= 2;
-  AM_NR_SWITCH(nr, hipLaunchKernelGGL(k_permute_out<NR>, dim3(nblk(n)), dim3(256), 0, s, dperm,
-                                       n, src, nrhs, dst, ld));
+  AM_NR_SWITCH(nr, hipLaunchKernelGGL(k_permute_out<NR>, dim3(nblk(n * (NR / KGroup<NR>::v))),
+                                      dim3(256), 0, s, dperm, n, src, nrhs, dst, ld));
   return hipGetLastError();
 }
 
@@ -943,8 +985,18 @@ hipError_t launch_fill(double* p, int64_t count, double v, hipStream_t s) {
 
 hipError_t launch_pcg_init(DeviceState& d, int nr, double tol, int maxit, int flexible,
                            hipStream_t s) {
-  hipLaunchKernelGGL(k_init_scalars, dim3(1), dim3(64), 0, s, d.sc, d.shared, nr, nr, tol * tol,
+  hipLaunchKernelGGL(k_init_scalars, dim3(1), dim3(64), 0, s, d.sc, d.shared, nr, tol * tol,
                      maxit, flexible);
+  return hipGetLastError();
+}
+
+hipError_t launch_pcg_begin(DeviceState& d, const double* b, int64_t ld, int nrhs, double* bp,
+                            int nr, double tol, int maxit, int flexible, hipStream_t s) {
+  const int64_t neta = (int64_t)std::max<int32_t>(d.ldS, 1) * nr;
+  AM_NR_SWITCH(nr, hipLaunchKernelGGL(k_pcg_begin<NR>, dim3(nblk(d.n * (NR / KGroup<NR>::v))),
+                                      dim3(256), 0, s, d.dperm, d.n, b, ld, nrhs, d.r, bp, d.x,
+                                      d.z, d.q, d.p[0], d.p[1], d.eta, neta, d.sc, d.shared,
+                                      tol * tol, maxit, flexible));
   return hipGetLastError();
 }
 
