@@ -11,6 +11,7 @@
 #include <functional>
 #include <mutex>
 #include <string>
+#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -56,12 +57,20 @@ class HostTeam {
       seats_ = nt - 1;
       ++epoch_;
     }
-    while ((int)pool_.size() < nt - 1) pool_.emplace_back([this] { serve(); });
+    struct Finish {  // also where work() throws here: the others still use it
+      HostTeam* t;
+      ~Finish() {
+        std::unique_lock<std::mutex> l(t->m_);
+        t->job_ = nullptr;  // a thread that wakes from now on finds nothing to do
+        t->done_.wait(l, [this] { return t->active_ == 0; });
+      }
+    } finish{this};
+    try {
+      while ((int)pool_.size() < nt - 1) pool_.emplace_back([this] { serve(); });
+    } catch (const std::system_error&) {  // no more threads: with those there are
+    }
     wake_.notify_all();
     work();
-    std::unique_lock<std::mutex> l(m_);
-    job_ = nullptr;  // a thread that wakes from now on finds nothing to do
-    done_.wait(l, [this] { return active_ == 0; });
     return true;
   }
 
