@@ -59,7 +59,8 @@ def traffic_record(prec, config, tile_choice):
     if not os.path.exists(path):
         return None
     rec = json.load(open(path))
-    src = open(os.path.join(ROOT, "paper_2607_22905_amd", "csrc", "local_kernels.h"), "rb").read()
+    csrc = os.path.join(ROOT, "paper_2607_22905_amd", "csrc")
+    src = b"".join(open(os.path.join(csrc, f), "rb").read() for f in ("local_kernels.h", "tri_kernels.h"))
     if rec.get("local_kernels_sha256") != hashlib.sha256(src).hexdigest():
         return None
     ent = rec.get("per_tile_choice", {}).get(str(tile_choice))
@@ -434,11 +435,11 @@ def main():
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
                      "traffic": traffic,
-                     "kernel": (("k_localt_mf + k_localt_mf2 (16 RHS on the matrix cores: tile sweeps, "
+                     "kernel": (("k_tri_mf + k_localt_mf2 (16 RHS on the matrix cores: local solves, "
                                  "reconstruction; one launch per window bucket)" if nrhs == 16 else
-                                 "k_localt (tile sweeps, fused interface solve, reconstruction)")
+                                 "k_tri_solve (local solves by block inverses, reconstruction)")
                                 if smooth is None else
-                                "k_localt on the smoothing blocks (block-Jacobi solves)"),
+                                "k_tri_solve on the smoothing blocks (block-Jacobi solves)"),
                      "avg_launch_us": k_ms * 1e3, "launches": k_launches,
                      "bytes_per_launch": k_bytes,
                      "timing": ("HIP events attached to the launches of a profiled solve (plain launches, "

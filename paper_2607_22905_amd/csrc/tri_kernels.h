@@ -659,9 +659,9 @@ __device__ __forceinline__ bool local_prologue(int mode, int ns, int64_t i0,
 // barrier and a round of partial sums per step: 1.0 us a step with four waves
 // against 0.45.)  Blocks further out than HT are read again on the way back.
 // x goes to LDS, and all threads form z = x + sum eta phat and the PCG dots
-// over the rows at the end.  128^3 (4096 boxes), FP64: 158 us for 0.74 GB, the
+// over the rows at the end.  128^3 (4096 boxes), FP64: 168 us for 0.79 GB (counters), the
 // loads of one workgroup beside the chain of the other on its CU (band tiles
-// read once per sweep, 32 barriers: 342 us for 2.1 GB); FP32 94 us; 64^3 21 us
+// read once per sweep, 32 barriers: 342 us for 2.1 GB); FP32 99 us; 64^3 21 us
 // (52 us with the interface rows formed inside).
 template <typename FT, int NT, int HT> constexpr int tri_waves() {
   constexpr int regs = (2 * HT + 1) * 4 * (int)sizeof(FT) + 16 * NT + 72;
