@@ -47,7 +47,7 @@ typedef enum {
   AM_ERR_ARG = -1,               /* bad pointer, size, pattern or partition */
   AM_ERR_NOT_SYMMETRIC = -2,     /* a_kl != a_lk (bitwise) */
   AM_ERR_POSITIVE_COUPLING = -3, /* an off-diagonal > 0: W must be negative */
-  AM_ERR_NOT_SPD = -4,           /* a Cholesky pivot <= 0 (A_i or S) */
+  AM_ERR_NOT_SPD = -4,           /* a pivot <= 0 (A_i or S) */
   AM_ERR_NO_CONVERGENCE = -5,    /* maxit reached; x holds the last iterate */
   AM_ERR_BREAKDOWN = -6,         /* (p,Ap) <= 0 or (r,z) <= 0 in PCG */
   AM_ERR_HIP = -7,               /* a HIP runtime call failed */
