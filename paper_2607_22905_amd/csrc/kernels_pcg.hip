@@ -197,6 +197,14 @@ __global__ __launch_bounds__(256) void k_spmv_p(int64_t n, int w, const int32_t*
     for (int c = 0; c < MAXW; ++c)
 #pragma unroll
       for (int k = 0; k < KG; ++k) acc[k] = fma(v[c], fma(beta[k], pc[c][k], zc[c][k]), acc[k]);
+    if constexpr (MAXW > 8)  // a row with more entries than are held in registers
+      for (int c = MAXW; c < w; ++c) {
+        const int64_t j = ec[(int64_t)c * n + i];
+        const double a = ev[(int64_t)c * n + i];
+#pragma unroll
+        for (int k = 0; k < KG; ++k)
+          acc[k] = fma(a, fma(beta[k], pold[vi(j, k)], z[vi(j, k)]), acc[k]);
+      }
 #pragma unroll
     for (int k = 0; k < KG; ++k) {
       const double pn = fma(beta[k], pi[k], zi[k]);
@@ -713,6 +721,13 @@ __global__ __launch_bounds__(kSpmvSubThreads) void k_spmv_sub(
 #pragma unroll
       for (int k = 0; k < KG; ++k) acc[k] = fma(vv[c], pv[k], acc[k]);
     }
+    if constexpr (MAXW > 8)  // (as in k_spmv_p)
+      for (int c = MAXW; c < w; ++c) {
+        const size_t o = (size_t)ec[(int64_t)c * n + base + r] * NT + k0;
+        const double a = ev[(int64_t)c * n + base + r];
+#pragma unroll
+        for (int k = 0; k < KG; ++k) acc[k] = fma(a, fma(beta[k], pold[o + k], z[o + k]), acc[k]);
+      }
     double pn[KG];
     if (r < NL) {
 #pragma unroll
@@ -931,6 +946,13 @@ __global__ __launch_bounds__(256) void k_true_res(int64_t n, int w, const int32_
       if (c < w)
 #pragma unroll
         for (int k = 0; k < NR; ++k) acc[k] = fma(-a[c], x[vix<NR>(n, col[c], k)], acc[k]);
+    if constexpr (MAXW > 8)  // (as in k_spmv_p)
+      for (int c = MAXW; c < w; ++c) {
+        const int64_t j = ec[(int64_t)c * n + i];
+        const double av = ev[(int64_t)c * n + i];
+#pragma unroll
+        for (int k = 0; k < NR; ++k) acc[k] = fma(-av, x[vix<NR>(n, j, k)], acc[k]);
+      }
 #pragma unroll
     for (int k = 0; k < NR; ++k) v[k] = fma(acc[k], acc[k], v[k]);
   }

@@ -66,6 +66,13 @@ __global__ __launch_bounds__(256) void k_sres(int64_t n, int w, const int32_t* _
       if (win) u += win[oc];
       acc = fma(-v[c], u, acc);
     }
+    if constexpr (MAXW > 8)  // a row with more entries than are held in registers
+      for (int c = MAXW; c < w; ++c) {
+        const size_t oc = vix<NT>(n, ec[(int64_t)c * n + i], k);
+        double u = zin[oc];
+        if (win) u += win[oc];
+        acc = fma(-ev[(int64_t)c * n + i], u, acc);
+      }
     if (zout) {
       double u = zin[o];
       if (win) u += win[o];
