@@ -758,8 +758,8 @@ static am_status setup_impl(const am_csr* A, const int32_t* part, int32_t nparts
   for (int32_t s2 = 0; s2 < st.m; ++s2) {
     const int32_t np = (int32_t)(lp.roff[s2 + 1] - lp.roff[s2]);
     desc[s2] = {st.sub_ptr[s2], lp.fac_off[s2], lp.roff[s2], lp.cpl_off[s2], mbf_off[s2],
-                st.isub_ptr[s2], (int32_t)(st.sub_ptr[s2 + 1] - st.sub_ptr[s2]), np / 64,
-                lp.cpl_k[s2], (int32_t)(st.isub_ptr[s2 + 1] - st.isub_ptr[s2])};
+                st.isub_ptr[s2], (int32_t)(st.sub_ptr[s2 + 1] - st.sub_ptr[s2]), 0, lp.cpl_k[s2],
+                (int32_t)(st.isub_ptr[s2 + 1] - st.isub_ptr[s2])};
     if (lp.wp[s2] == 64) d.max_np0 = std::max(d.max_np0, np);
   }
   SCHK(upload(al, &d.desc, desc, sm));

@@ -400,11 +400,13 @@ __device__ __forceinline__ void bpart_sub(int s, int64_t n, const int64_t* __res
 // pivot row goes through one of two LDS rows prow: one barrier per pivot,
 // taken by every thread of the workgroup, act or not (act: whether this group
 // of 256 has a block).  bad(k) is called by one thread for a pivot that is not
-// positive (taken as 1).  Bound by the chain of 64 barriers and divisions,
-// about 25 us.
-template <typename F>
+// positive (taken as 1).  each(k, pr, rd) is called by every thread of a group
+// with a block, before pivot k = 1 / rd is used: with K the inverse of the
+// unit lower triangular factor of the block, pr[j] is -K[k][j] for j < k.
+// Bound by the chain of 64 barriers and divisions, about 25 us.
+template <typename F, typename G>
 __device__ __forceinline__ void sweep_inverse_64(double (&x)[4][4], double (*prow)[64], int tid,
-                                                 bool act, F&& bad) {
+                                                 bool act, F&& bad, G&& each) {
   const int i0 = 4 * (tid / 16), j0 = 4 * (tid % 16);
   if (act && i0 == 0)
 #pragma unroll
@@ -420,6 +422,7 @@ __device__ __forceinline__ void sweep_inverse_64(double (&x)[4][4], double (*pro
         const bool no = !(d > 0.0) || !(d < 1.0e300);
         const double rd = no ? 1.0 : 1.0 / d;
         if (tid == 0 && no) bad(k);
+        each(k, pr, rd);
         double pi[4], pj[4];
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
@@ -442,6 +445,11 @@ __device__ __forceinline__ void sweep_inverse_64(double (&x)[4][4], double (*pro
       __syncthreads();
     }
   }
+}
+template <typename F>
+__device__ __forceinline__ void sweep_inverse_64(double (&x)[4][4], double (*prow)[64], int tid,
+                                                 bool act, F&& bad) {
+  sweep_inverse_64(x, prow, tid, act, bad, [](int, const double*, double) {});
 }
 
 }  // namespace am

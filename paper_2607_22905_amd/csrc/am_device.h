@@ -134,11 +134,12 @@ struct IxDevice {
 
 // One subdomain as the solve kernels read it (one 64-byte load instead of a
 // chain of them): first row (device position), factor / diagonal / coupling /
-// basis-function offsets, first basis-function slot, rows, 64-row blocks,
-// couplings per row and side, basis functions.
+// basis-function offsets, first basis-function slot, rows, whether its block
+// inverses are kept as triangular factors (set by k_tri_factor), couplings per
+// row and side, basis functions.
 struct SubDesc {
   int64_t base, fac, ro, cpl, mbf, i0;
-  int32_t N, NB, kc, ns;
+  int32_t N, tri, kc, ns;
 };
 
 struct DeviceState {

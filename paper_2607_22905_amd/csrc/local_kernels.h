@@ -1185,8 +1185,7 @@ hipError_t band_factor_t(DeviceState& d, hipStream_t st) {
                        d.sub_ptr, d.roff, d.cpl_off, d.cpl_k, d.prp, d.pci, d.pv, (IT*)d.cpl,
                        d.cidx);
     hipLaunchKernelGGL((k_tri_factor<FT>), dim3(nb0), dim3(512), 0, st, d.d_bucket_sub[0],
-                       d.sub_ptr, d.roff, d.fac_off, d.prp, d.pci, d.pv, (FT*)d.Lc, (IT*)d.invd,
-                       d.fail, d.plain);
+                       d.desc, d.prp, d.pci, d.pv, (FT*)d.Lc, (IT*)d.invd, d.fail, d.plain);
     if (d.Bc)
       hipLaunchKernelGGL((k_band_factor<FT, 64>), dim3(nb0), dim3(256), 0, st, d.d_bucket_sub[0],
                          d.sub_ptr, d.roff, d.band_off, d.prp, d.pci, d.pv, (FT*)d.Bc, (FT*)d.Br,

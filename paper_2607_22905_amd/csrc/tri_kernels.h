@@ -24,6 +24,19 @@
 // and the second sum is a Horner scheme of one-lane wave rotations, so a
 // wave's factor values never leave its registers.  The main diagonal is a
 // separate array (arithmetic type), as are the couplings.
+//
+// Triangular form (FP32 and BF16 factors).  The local operator that is applied
+// is congruent to diag(X_b), and rounding the entries of X_b can make it
+// indefinite: where a conductive body lies inside a subdomain, X_b is nearly
+// of rank one over that body, and its small eigenvalues are below the rounding
+// of the large entries.  k_tri_factor therefore bounds the change in every
+// block; a subdomain beyond the bound keeps X_b = K^T D K instead, K unit lower
+// triangular, D > 0 diagonal, in the same storage: the pair (i, j), i > j, of
+// the tile holds K[i][j], the main diagonal D.  That is definite whatever the
+// rounding, and y = X_b t is two triangular products,
+//   u = t + Ks t,   v = D u,   y = v + Ks^T v    (Ks: K without its diagonal).
+// In the first, lane l takes its element (c, l) as an entry of its own row if
+// l + c >= 64 and of the other row if not; in the second the other way round.
 #pragma once
 #include <type_traits>
 
@@ -114,8 +127,9 @@ template <typename FT, int ND> struct TriFrag {
 // Partial products of the diagonals in f with NT vectors: t (this lane's
 // values), tw: the wave's LDS copy, value (k, i) at tw[128 k + i], rows
 // repeated at i + 64.  On return a[k] adds to row l, h[k] to row
-// (l + c0 + 1) % 64.
-template <typename FT, int ND, int NT>
+// (l + c0 + 1) % 64.  PART: 0 the symmetric tile, 1 its strict lower triangle
+// (Ks), 2 the transpose of that.
+template <typename FT, int ND, int NT, int PART = 0>
 __device__ __forceinline__ void tri_partial(const TriFrag<FT, ND>& f, int c0, int lane,
                                             const typename TriAcc<FT>::T (&t)[NT],
                                             const typename TriAcc<FT>::T* tw,
@@ -126,10 +140,12 @@ __device__ __forceinline__ void tri_partial(const TriFrag<FT, ND>& f, int c0, in
 #pragma unroll
   for (int j = ND - 1; j >= 0; --j) {
     const AT d = f.get(j);
+    const bool own = (lane + c0 + j + 1 >= 64) == (PART == 1);
+    const AT da = PART == 0 || own ? d : (AT)0, dh = PART == 0 || !own ? d : (AT)0;
 #pragma unroll
     for (int k = 0; k < NT; ++k) {
-      a[k] = j == ND - 1 ? d * p[128 * k + j] : fma(d, p[128 * k + j], a[k]);
-      h[k] = j == ND - 1 ? d * t[k] : fma(d, t[k], wave_ror1(h[k]));
+      a[k] = j == ND - 1 ? da * p[128 * k + j] : fma(da, p[128 * k + j], a[k]);
+      h[k] = j == ND - 1 ? dh * t[k] : fma(dh, t[k], wave_ror1(h[k]));
     }
   }
 }
@@ -227,20 +243,42 @@ __global__ __launch_bounds__(256) void k_tri_couplings(
 }
 
 // ---------------------------------------------------------------------------
+// Largest change of a block inverse by the rounding of its entries that the
+// symmetric form is kept for.  With X~ = X + E the stored block, S = X^{-1}
+// and D = diag(S): S is an M-matrix, so D^{-1/2} S D^{-1/2} has its eigenvalues
+// below 2 and X >= D^{-1} / 2; where every row sum of D^{1/2} |E| D^{1/2} is at
+// most tau, -2 tau X <= E <= 2 tau X.  tau < 1/2 keeps X~ definite; the values
+// lie where iterations would be lost (8^3 boxes with a 4^3 body of the given
+// contrast in each, symmetric and triangular form: BF16 1e2 (row sums 0.28) 21
+// and 19 iterations, 1e3 (2.4) breakdown and 21; FP32 1e4 (4e-4) 12 and 12, 1e6
+// (0.05) 15 and 12, 1e8 breakdown and 20).  Gaussian and layered fields stay
+// below 0.05 (BF16) and 1e-6 (FP32).
+template <typename FT> struct TriTau { static constexpr double v = 1.0 / 1024; };
+template <> struct TriTau<bf16_t> { static constexpr double v = 1.0 / 4; };
+
+// v as stored in FT
+template <typename FT> __device__ __forceinline__ double tri_stored(double v) {
+  FT b;
+  st_fac(&b, v);
+  return (double)widen_lds(b);
+}
+
 // X_b of every block (set-up): one workgroup per subdomain, two groups of 256
 // threads eliminating from the two ends side by side, group 0 then the middle
 // block.  A thread keeps a 4 x 4 piece of its group's 64 x 64 block in
 // registers (sweep_inverse_64), FP64 throughout.  A pivot that is not positive
-// names the subdomain and row in fail.  Bound by the chain of 64 barriers per
+// names the subdomain and row in fail.  FP32 and BF16: where the rounding of a
+// block is beyond TriTau, the elimination is done again for the triangular
+// form.  Bound by the chain of 64 barriers per
 // block: 4096 boxes 2.6 ms (band Cholesky and its diagonal inverses 16 ms).
 template <typename FT>
 __global__ __launch_bounds__(512) void k_tri_factor(
-    const int32_t* __restrict__ subs, const int64_t* __restrict__ sub_ptr,
-    const int64_t* __restrict__ roff, const int64_t* __restrict__ fac_off,
+    const int32_t* __restrict__ subs, SubDesc* __restrict__ desc,
     const int64_t* __restrict__ prp, const int32_t* __restrict__ pci,
     const double* __restrict__ pv, FT* __restrict__ fac,
     typename TriAcc<FT>::T* __restrict__ dg, int32_t* __restrict__ fail, int plain) {
   using AT = typename TriAcc<FT>::T;
+  constexpr bool kRounded = sizeof(FT) < 8;
   constexpr int P = 65;
   __shared__ double M[2][64 * P];
   __shared__ double prow[2][2][64];
@@ -248,12 +286,12 @@ __global__ __launch_bounds__(512) void k_tri_factor(
   // [group][list][row] first CSR position and count
   __shared__ int64_t e0[2][2][64];
   __shared__ int32_t en[2][2][64];
+  __shared__ double dsq[2][64];  // square roots of the block's diagonal
+  __shared__ int far;            // a block is beyond TriTau
   const int s = subs[blockIdx.x];
-  const int64_t base = sub_ptr[s];
-  const int N = (int)(sub_ptr[s + 1] - base);
-  const int64_t ro = roff[s];
-  const int NB = (int)(roff[s + 1] - ro) / 64;
-  FT* fs = fac + fac_off[s];
+  const int64_t base = desc[s].base, ro = desc[s].ro;
+  const int N = desc[s].N, NB = (N + 63) / 64;
+  FT* fs = fac + desc[s].fac;
   const int g = threadIdx.x >> 8, tid = threadIdx.x & 255;
   const int i0 = 4 * (tid / 16), j0 = 4 * (tid % 16);
   const int h = NB / 2, len1 = NB - 1 - h;
@@ -292,91 +330,134 @@ __global__ __launch_bounds__(512) void k_tri_factor(
     }
   };
 
-  // blocks in elimination order: step k < h: group 0 block k, group 1 block
-  // NB - 1 - k; step h: the middle block
-  for (int step = 0; step <= h; ++step) {
-    const bool mid = step == h;
-    const bool act = mid ? g == 0 : (g == 0 || step < len1);
-    const int b = mid ? h : (g == 0 ? step : NB - 1 - step);
-    // CSR ranges of the block's rows in the neighbouring blocks (row c of the
-    // list: couplings to the eliminated neighbour on that side)
-    if (act && tid < 128) {
-      const int list = tid / 64, i = tid % 64, row = 64 * b + i;
-      int64_t first = 0;
-      int cnt = 0;
-      if (row < N) {
-        const int64_t lo = base + 64 * (int64_t)(list == 0 ? b - 1 : b + 1);
-        const int64_t hi = min(lo + 64, base + (int64_t)N);
-        if (lo >= base && lo < base + N)
-          for (int64_t p = prp[base + row]; p < prp[base + row + 1]; ++p) {
-            const int64_t c = pci[p];
-            if (c >= lo && c < hi) {
-              if (cnt == 0) first = p;
-              ++cnt;
+  if (threadIdx.x == 0) far = 0;
+  // the symmetric form (0), then where needed the triangular one (1)
+  for (int form = 0; form < 2; ++form) {
+    // blocks in elimination order: step k < h: group 0 block k, group 1 block
+    // NB - 1 - k; step h: the middle block
+    for (int step = 0; step <= h; ++step) {
+      const bool mid = step == h;
+      const bool act = mid ? g == 0 : (g == 0 || step < len1);
+      const int b = mid ? h : (g == 0 ? step : NB - 1 - step);
+      // CSR ranges of the block's rows in the neighbouring blocks (row c of the
+      // list: couplings to the eliminated neighbour on that side)
+      if (act && tid < 128) {
+        const int list = tid / 64, i = tid % 64, row = 64 * b + i;
+        int64_t first = 0;
+        int cnt = 0;
+        if (row < N) {
+          const int64_t lo = base + 64 * (int64_t)(list == 0 ? b - 1 : b + 1);
+          const int64_t hi = min(lo + 64, base + (int64_t)N);
+          if (lo >= base && lo < base + N)
+            for (int64_t p = prp[base + row]; p < prp[base + row + 1]; ++p) {
+              const int64_t c = pci[p];
+              if (c >= lo && c < hi) {
+                if (cnt == 0) first = p;
+                ++cnt;
+              }
             }
-          }
-      }
-      e0[g][list][i] = first;
-      en[g][list][i] = cnt;
-    }
-    __syncthreads();
-    double upd[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) upd[a][c] = 0.0;
-    if (act) {
-      if (g == 0 && step > 0) reduce(upd, M[0], 0, b - 1);
-      if (g == 1 && step > 0) reduce(upd, M[1], 1, b + 1);
-      if (mid && len1 > 0) reduce(upd, M[1], 1, b + 1);
-    }
-    __syncthreads();
-    if (act)
-      for (int t = tid; t < 64 * P; t += 256) Mg[t] = 0.0;
-    __syncthreads();
-    if (act && tid < 64) {
-      const int row = 64 * b + tid;
-      double dout = 0.0;
-      if (row < N) {
-        const int64_t lo = base + 64 * (int64_t)b;
-        for (int64_t p = prp[base + row]; p < prp[base + row + 1]; ++p) {
-          const int64_t c = pci[p];
-          const double v = pv[p];
-          if (c >= base && c < base + N) {
-            if (c >= lo && c < lo + 64) Mg[tid * P + (int)(c - lo)] = v;
-          } else {
-            dout += v;
-          }
         }
-        if (!plain) Mg[tid * P + tid] -= dout;
-      } else {
-        Mg[tid * P + tid] = 1.0;
+        e0[g][list][i] = first;
+        en[g][list][i] = cnt;
       }
-    }
-    __syncthreads();
-    double x[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) x[a][c] = act ? Mg[(i0 + a) * P + j0 + c] - upd[a][c] : 0.0;
-    sweep_inverse_64(x, prow[g], tid, act, [&](int k) {
-      if (atomicCAS(fail, -1, s) == -1) fail[1] = 64 * b + k;
-    });
-    // x = -X_b
-    if (act)
+      __syncthreads();
+      double upd[4][4];
 #pragma unroll
       for (int a = 0; a < 4; ++a)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) Mg[(i0 + a) * P + j0 + c] = -x[a][c];
-    __syncthreads();
-    if (act) {
-      FT* ft = fs + (size_t)b * kTriElems;
-      for (int t = tid; t < kTriElems; t += 256) {
-        const int c = t / 64 + 1, l = t % 64;
-        const double v = Mg[l * P + ((l + c) & 63)];
-        st_fac(ft + tri_at<FT>(c, l), c == 32 ? 0.5 * v : v);
+        for (int c = 0; c < 4; ++c) upd[a][c] = 0.0;
+      if (act) {
+        if (g == 0 && step > 0) reduce(upd, M[0], 0, b - 1);
+        if (g == 1 && step > 0) reduce(upd, M[1], 1, b + 1);
+        if (mid && len1 > 0) reduce(upd, M[1], 1, b + 1);
       }
-      if (tid < 64) dg[ro + 64 * b + tid] = (AT)Mg[tid * P + tid];
+      __syncthreads();
+      if (act)
+        for (int t = tid; t < 64 * P; t += 256) Mg[t] = 0.0;
+      __syncthreads();
+      if (act && tid < 64) {
+        const int row = 64 * b + tid;
+        double dout = 0.0;
+        if (row < N) {
+          const int64_t lo = base + 64 * (int64_t)b;
+          for (int64_t p = prp[base + row]; p < prp[base + row + 1]; ++p) {
+            const int64_t c = pci[p];
+            const double v = pv[p];
+            if (c >= base && c < base + N) {
+              if (c >= lo && c < lo + 64) Mg[tid * P + (int)(c - lo)] = v;
+            } else {
+              dout += v;
+            }
+          }
+          if (!plain) Mg[tid * P + tid] -= dout;
+        } else {
+          Mg[tid * P + tid] = 1.0;
+        }
+      }
+      __syncthreads();
+      double x[4][4];
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) x[a][c] = act ? Mg[(i0 + a) * P + j0 + c] - upd[a][c] : 0.0;
+      if (kRounded && act && i0 == j0)
+#pragma unroll
+        for (int a = 0; a < 4; ++a) dsq[g][i0 + a] = sqrt(x[a][a]);
+      FT* ft = fs + (size_t)b * kTriElems;
+      sweep_inverse_64(
+          x, prow[g], tid, act,
+          [&](int k) {
+            if (atomicCAS(fail, -1, s) == -1) fail[1] = 64 * b + k;
+          },
+          [&](int k, const double* pr, double rd) {
+            if constexpr (kRounded) {
+              if (form == 0) return;
+              if (tid < k) {  // K[k][tid], where the pair (k, tid) is kept
+                const double v = -pr[tid];
+                const int c = k - tid;
+                if (c <= 32) st_fac(ft + tri_at<FT>(c, tid), c == 32 ? 0.5 * v : v);
+                if (c >= 32) st_fac(ft + tri_at<FT>(64 - c, k), c == 32 ? 0.5 * v : v);
+              }
+              if (tid == k) dg[ro + 64 * b + k] = (AT)rd;
+            }
+          });
+      // x = -X_b
+      if (kRounded && act && form == 0) {
+        bool over = false;
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+          double sum = 0.0;  // of the row's |E| over the sixteen threads of its row
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            const double v = -x[a][c];
+            const double t = i0 + a == j0 + c ? (double)(AT)v : tri_stored<FT>(v);
+            sum = fma(fabs(t - v), dsq[g][j0 + c], sum);
+          }
+          sum = add_ror<1>(add_ror<2>(add_ror<4>(add_ror<8>(sum))));
+          over |= !(sum * dsq[g][i0 + a] <= TriTau<FT>::v);  // (not a number: over)
+        }
+        if (over) far = 1;
+      }
+      if (act)
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) Mg[(i0 + a) * P + j0 + c] = -x[a][c];
+      __syncthreads();
+      if (act && form == 0) {
+        for (int t = tid; t < kTriElems; t += 256) {
+          const int c = t / 64 + 1, l = t % 64;
+          const double v = Mg[l * P + ((l + c) & 63)];
+          st_fac(ft + tri_at<FT>(c, l), c == 32 ? 0.5 * v : v);
+        }
+        if (tid < 64) dg[ro + 64 * b + tid] = (AT)Mg[tid * P + tid];
+      }
+    }
+    if constexpr (!kRounded) return;
+    __syncthreads();
+    if (form == 1 || !far) {
+      if (threadIdx.x == 0) desc[s].tri = form;
+      return;
     }
   }
 }
@@ -386,6 +467,7 @@ __global__ __launch_bounds__(512) void k_tri_factor(
 template <typename FT> struct TriSub {
   using AT = typename TriAcc<FT>::T;
   int N, NP, NB, h, len1, d, kc;  // d: steps group 1 waits at the start
+  bool tri;                       // the triangular form
   const FT* fac;
   const AT* dg;
   const AT* cpl;
@@ -398,12 +480,13 @@ __device__ __forceinline__ TriSub<FT> tri_sub(const SubDesc& e, const FT* fac,
                                               const uint8_t* cidx) {
   TriSub<FT> t;
   t.N = e.N;
-  t.NB = e.NB;
-  t.NP = 64 * e.NB;
+  t.NB = (e.N + 63) / 64;
+  t.NP = 64 * t.NB;
   t.h = t.NB / 2;
   t.len1 = t.NB - 1 - t.h;
   t.d = t.h - t.len1;
   t.kc = e.kc;
+  t.tri = sizeof(FT) < 8 && e.tri;
   t.fac = fac + e.fac;
   t.dg = dg + e.ro;
   t.cpl = cpl + e.cpl;
@@ -704,9 +787,12 @@ __global__ __launch_bounds__(128, (tri_waves<FT, NT, HT>())) void k_tri_solve(
   AT* tw = tw_all[g];
 
   // step k of a half (k = 0 the outermost block); off steps are streamed
-  const int off = max(0, T.h - HT);
-  const int r_lo = 64 * off;              // first row held on chip
-  const int r_n = min(T.NP - r_lo, RR);   // rows held on chip
+  // (the triangular form streams all but the middle block: two products a
+  // block in two places of the code)
+  const int held = T.tri ? 0 : HT;
+  const int off = max(0, T.h - held);
+  const int r_lo = 64 * off;  // first row held on chip
+  const int r_n = min(T.NP - r_lo, (2 * held + 1) * 64);  // rows held on chip
   auto blk = [&](int k) AM_INLINE { return g == 0 ? k : T.NB - 1 - (k - T.d); };
   auto active = [&](int k) AM_INLINE { return g == 0 || k >= T.d; };
   // list of a row's couplings to the block that comes before it on the way to
@@ -839,6 +925,31 @@ __global__ __launch_bounds__(128, (tri_waves<FT, NT, HT>())) void k_tri_solve(
     for (int k = 0; k < NT; ++k) y[k] = dgv * t[k];
     tri_full<FT, NT>(f, lane, tp, tw, y);
   };
+  // the same of a streamed block, in either form
+  auto product_streamed = [&](const TriFrag<FT, 32>& f, int b, const AT (&t)[NT],
+                              AT (&y)[NT]) AM_INLINE {
+    if constexpr (sizeof(FT) < 8) {
+      if (T.tri) {
+        AT tp[NT], v[NT], a[NT], h[NT];
+#pragma unroll
+        for (int k = 0; k < NT; ++k) tp[k] = operand(t[k]);
+        put(tp);
+        tri_partial<FT, 32, NT, 1>(f, 0, lane, tp, tw, a, h);
+        const AT dgv = T.dg[64 * b + lane];
+#pragma unroll
+        for (int k = 0; k < NT; ++k) {
+          v[k] = dgv * (t[k] + (a[k] + wave_ror1(h[k])));
+          tp[k] = operand(v[k]);
+        }
+        put(tp);
+        tri_partial<FT, 32, NT, 2>(f, 0, lane, tp, tw, a, h);
+#pragma unroll
+        for (int k = 0; k < NT; ++k) y[k] = v[k] + (a[k] + wave_ror1(h[k]));
+        return;
+      }
+    }
+    product(f, b, t, y);
+  };
 
   AT y[NT], t[NT];
 #pragma unroll
@@ -852,7 +963,7 @@ __global__ __launch_bounds__(128, (tri_waves<FT, NT, HT>())) void k_tri_solve(
     rhs(b, t);
     if (k > first) couple(b, LF, (AT)-1, y, t);
     ahead(k + 1 < T.h ? blk(k + 1) : T.h, LF);
-    product(f, b, t, y);
+    product_streamed(f, b, t, y);
     if (64 * b + lane < T.N)
 #pragma unroll
       for (int c = 0; c < NT; ++c) out[(size_t)(base + 64 * b + lane) * NT + c] = (double)y[c];
@@ -911,22 +1022,42 @@ __global__ __launch_bounds__(128, (tri_waves<FT, NT, HT>())) void k_tri_solve(
     for (int k = 0; k < NT; ++k) tp[k] = operand(t[k]);
     put(tp);
     if (g == 0 ? T.h > 0 : T.len1 > 0) ahead(blk(T.h - 1), LB);
-    tri_partial<FT, 16, NT>(Dm, 16 * g, lane, tp, tw, a, h);
-    if (g == 0) {
-      const AT dgv = ds[64 * T.h + lane - r_lo];
+    const AT dgv = ds[64 * T.h + lane - r_lo];
+    // a wave's 16 diagonals and the main one (times d t), added up over both
+    auto meet = [&](AT d) AM_INLINE {
 #pragma unroll
-      for (int k = 0; k < NT; ++k) a[k] = fma(dgv, t[k], a[k]);
+      for (int k = 0; k < NT; ++k) {
+        if (g == 0) a[k] = fma(d, t[k], a[k]);
+        ex[g][1][64 * k + lane] = a[k];
+        ex[g][2][64 * k + ((lane + 16 * g + 1) & 63)] = h[k];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < NT; ++k)
+        y[k] = (ex[0][1][64 * k + lane] + ex[1][1][64 * k + lane]) +
+               (ex[0][2][64 * k + lane] + ex[1][2][64 * k + lane]);
+    };
+    bool done = false;
+    if constexpr (sizeof(FT) < 8) {
+      if (T.tri) {  // uniform over the workgroup
+        done = true;
+        tri_partial<FT, 16, NT, 1>(Dm, 16 * g, lane, tp, tw, a, h);
+        meet((AT)1);
+#pragma unroll
+        for (int k = 0; k < NT; ++k) {
+          t[k] = dgv * y[k];
+          tp[k] = operand(t[k]);
+        }
+        put(tp);
+        tri_partial<FT, 16, NT, 2>(Dm, 16 * g, lane, tp, tw, a, h);
+        __syncthreads();  // the sums of the first product are read
+        meet((AT)1);
+      }
     }
-#pragma unroll
-    for (int k = 0; k < NT; ++k) {
-      ex[g][1][64 * k + lane] = a[k];
-      ex[g][2][64 * k + ((lane + 16 * g + 1) & 63)] = h[k];
+    if (!done) {
+      tri_partial<FT, 16, NT>(Dm, 16 * g, lane, tp, tw, a, h);
+      meet(dgv);
     }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < NT; ++k)
-      y[k] = (ex[0][1][64 * k + lane] + ex[1][1][64 * k + lane]) +
-             (ex[0][2][64 * k + lane] + ex[1][2][64 * k + lane]);
     if (g == 0)
 #pragma unroll
       for (int k = 0; k < NT; ++k) rs[k * RR + 64 * T.h - r_lo + lane] = y[k];
@@ -1020,7 +1151,7 @@ __global__ __launch_bounds__(128, (tri_waves<FT, NT, HT>())) void k_tri_solve(
     for (int c = 0; c < NT; ++c) t[c] = (AT)0;
     couple(b, LB, (AT)1, y, t);
     if (k > first) ahead(blk(k - 1), LB);
-    product(f, b, t, y);
+    product_streamed(f, b, t, y);
 #pragma unroll
     for (int c = 0; c < NT; ++c) y[c] = wv[c] - y[c];
     if (in) {
@@ -1318,15 +1449,51 @@ __global__ __launch_bounds__(256, 2) void k_tri_mf(
         }
     }
     if (q + 1 < nstep && active(q + 1) && (act || q > 0)) fetch(q + 1);
+    // entry (i, j) of the tile (its pair of rows), and the product with vb
+    auto entry = [&](int u, int c, int m) AM_INLINE {
+      const int i = 32 * w + 16 * u + li, j = c + m * lk, o = (j - i) & 63;
+      return o <= 32 ? tl[o * TP + i] : tl[(64 - o) * TP + j];
+    };
+    auto operand = [&](int c, int m) AM_INLINE { return vb[g][(c + m * lk) * 16 + li]; };
+    V acc[2];
+    if constexpr (sizeof(FT) < 8) {
+      if (T.tri) {  // uniform over the workgroup: u = t + Ks t, v = D u
+        if (act) {
+          tri_mf_pass<BFOP, V, AT>(
+              acc,
+              [&](int u, int c, int m) {
+                return c + m * lk < 32 * w + 16 * u + li ? entry(u, c, m) : (AT)0;
+              },
+              operand);
+#pragma unroll
+          for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+              acc[u][v] = tl[drow(u, v)] * (vb[g][drow(u, v) * 16 + li] + acc[u][v]);
+        }
+        __syncthreads();
+        if (act)
+#pragma unroll
+          for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) vb[g][drow(u, v) * 16 + li] = acc[u][v];
+        __syncthreads();
+      }
+    }
     if (act) {
-      V acc[2];
-      tri_mf_pass<BFOP, V, AT>(
-          acc,
-          [&](int u, int c, int m) {
-            const int i = 32 * w + 16 * u + li, j = c + m * lk, o = (j - i) & 63;
-            return o <= 32 ? tl[o * TP + i] : tl[(64 - o) * TP + j];
-          },
-          [&](int c, int m) { return vb[g][(c + m * lk) * 16 + li]; });
+      if (sizeof(FT) < 8 && T.tri) {  // v + Ks^T v
+        const V add[2] = {acc[0], acc[1]};
+        tri_mf_pass<BFOP, V, AT>(
+            acc,
+            [&](int u, int c, int m) {
+              return c + m * lk > 32 * w + 16 * u + li ? entry(u, c, m) : (AT)0;
+            },
+            operand);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) acc[u] += add[u];
+      } else {
+        tri_mf_pass<BFOP, V, AT>(acc, entry, operand);
+      }
 #pragma unroll
       for (int u = 0; u < 2; ++u)
 #pragma unroll
