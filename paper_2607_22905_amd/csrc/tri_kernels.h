@@ -1240,6 +1240,8 @@ __device__ __forceinline__ void tri_mf_pass(V (&acc)[2], AF&& afn, BF&& bfn) {
 // for the way back (a 512-row subdomain's 16 columns are 64 KB; beside the
 // tiles they would leave room for one workgroup per CU instead of two).  Both
 // groups form the middle block's x themselves: no exchange on the way back.
+// z = x + sum eta phat is FP64 for every factor type (v_mfma_f64_16x16x4f64; x
+// changes its result layout through LDS).
 // Bound by the LDS and memory latencies of a step (about 5 us with two
 // workgroups on the CU, 0.5 of it the product): 1721 subdomains of 200-800
 // cells, 16 columns, FP64: 347 us (band tiles, four products a step: 458).
@@ -1297,6 +1299,8 @@ __global__ __launch_bounds__(256, 2) void k_tri_mf(
   };
   // result layout: element v of strip u
   auto drow = [&](int u, int v) AM_INLINE { return 32 * w + 16 * u + MfAcc<AT>::row(lk, v); };
+  // the same of the reconstruction, FP64 for every factor type
+  auto zrow = [&](int u, int v) AM_INLINE { return 32 * w + 16 * u + MfAcc<double>::row(lk, v); };
   // the subdomain's rows: uniform bases, 32-bit lane offsets; loads use a
   // clamped offset (always in bounds), the values of rows outside are zeroed
   const double* rsub = rin + (size_t)base * NT;
@@ -1429,23 +1433,22 @@ __global__ __launch_bounds__(256, 2) void k_tri_mf(
     const bool post = act && (q > T.h || (mid && g == 0));  // z of this block
     // r for the dots and the first 16 slots' basis functions, in flight
     // during the product: A[row][slot 4 c + lk] of z += phat eta
-    double rp[8];
-    AT pa[2][4];
+    double rp[8], pa[2][4];
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         rp[4 * u + v] = 0.0;
-        pa[u][v] = (AT)0;
+        pa[u][v] = 0.0;
       }
     if (post) {  // uniform
 #pragma unroll
       for (int u = 0; u < 2; ++u)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          if (mode == 2) rp[4 * u + v] = rsub[row_off(64 * b + drow(u, v))];
+          if (mode == 2) rp[4 * u + v] = rsub[row_off(64 * b + zrow(u, v))];
           if (4 * v < ns)
-            pa[u][v] = (AT)P[min(4 * v + lk, ns - 1) * T.N + min(64 * b + 32 * w + 16 * u + li, T.N - 1)];
+            pa[u][v] = P[min(4 * v + lk, ns - 1) * T.N + min(64 * b + 32 * w + 16 * u + li, T.N - 1)];
         }
     }
     if (q + 1 < nstep && active(q + 1) && (act || q > 0)) fetch(q + 1);
@@ -1504,30 +1507,38 @@ __global__ __launch_bounds__(256, 2) void k_tri_mf(
           if (q < T.h && row < T.N && colok) osub[row * NT + li] = (double)acc[u][v];
         }
       if (post) {
+        tri_wave_sync();  // x of the wave's own rows, in the layout of z
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
+          am_mf_d4 z;
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            if constexpr (sizeof(AT) == 8)
+              z[v] = acc[u][v];
+            else
+              z[v] = (double)yb[g][zrow(u, v) * 16 + li];
+          }
           const int ra = min(64 * b + 32 * w + 16 * u + li, T.N - 1);
           for (int c0 = 0; c0 < ns; c0 += 16) {  // slots in chunks of 4 x 4
             if (c0 > 0)
 #pragma unroll
-              for (int c = 0; c < 4; ++c) pa[u][c] = (AT)P[min(c0 + 4 * c + lk, ns - 1) * T.N + ra];
+              for (int c = 0; c < 4; ++c) pa[u][c] = P[min(c0 + 4 * c + lk, ns - 1) * T.N + ra];
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
               if (c0 + 4 * c >= ns) break;  // uniform
               const int qq = c0 + 4 * c + lk;
-              const AT ev = (qq < ns && colok) ? (AT)eta_s[qq * NT + li] : AT(0);
-              acc[u] = mf4(qq < ns ? pa[u][c] : (AT)0, ev, acc[u]);
+              const double ev = (qq < ns && colok) ? eta_s[qq * NT + li] : 0.0;
+              z = mf4(qq < ns ? pa[u][c] : 0.0, ev, z);
             }
           }
 #pragma unroll
           for (int v = 0; v < 4; ++v) {
-            const int row = 64 * b + drow(u, v);
+            const int row = 64 * b + zrow(u, v);
             if (row < T.N && colok) {
               const int o = row * NT + li;
-              const double zv = (double)acc[u][v];
-              osub[o] = zv;
-              rz = fma(rp[4 * u + v], zv, rz);
-              if (flexible) qz = fma(qsub[o], zv, qz);
+              osub[o] = z[v];
+              rz = fma(rp[4 * u + v], z[v], rz);
+              if (flexible) qz = fma(qsub[o], z[v], qz);
             }
           }
         }
