@@ -1494,6 +1494,18 @@ __global__ __launch_bounds__(256, 2) void k_tri_mf(
             operand);
 #pragma unroll
         for (int u = 0; u < 2; ++u) acc[u] += add[u];
+      } else if constexpr (BFOP) {  // the main diagonal in FP32, on unrounded values
+        tri_mf_pass<BFOP, V, AT>(
+            acc,
+            [&](int u, int c, int m) {
+              return c + m * lk != 32 * w + 16 * u + li ? entry(u, c, m) : (AT)0;
+            },
+            operand);
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            acc[u][v] = fma(tl[drow(u, v)], vb[g][drow(u, v) * 16 + li], acc[u][v]);
       } else {
         tri_mf_pass<BFOP, V, AT>(acc, entry, operand);
       }

@@ -63,3 +63,22 @@ def test_reconstruction_is_fp64(nrhs, separate):
         assert tol < 1e-9
         assert np.abs(Z[k] / z - 1.0).max() <= tol, k
     h.close()
+
+
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_bf16_products(case):
+    """BF16 x BF16 products: 16 columns (matrix cores) and one (vector units)
+    round the same operands and keep the diagonals and what they multiply in
+    FP32; the products are exact in FP32.  Sums in another order differ by some
+    1e-7, which moves an operand of three in 1e5 over a rounding boundary, by
+    2^-8: 1e-5 in the norm.  A rounded diagonal would show as 5e-4 and more."""
+    sizes, offsets = CASES[case]
+    A, D, part = _band_matrix(sizes, offsets, 60 + case)
+    h = am.AlgMortar(A, part, len(sizes), prec="bf16", max_nrhs=16, separate_iface=True,
+                     bf16_products=True)
+    R = _gpu(np.random.default_rng(case).standard_normal((16, A.n)))
+    Z = h.apply(R).cpu().numpy()
+    for k in range(16):
+        z = h.apply(R[k].contiguous()).cpu().numpy()
+        assert np.linalg.norm(Z[k] - z) <= 1e-4 * np.linalg.norm(z), k
+    h.close()
