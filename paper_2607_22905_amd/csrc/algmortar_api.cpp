@@ -433,11 +433,18 @@ static hipError_t interface_inverse(DeviceState& d, hipStream_t st) {
   return he;
 }
 
-// Set-up arrays of the window-64 band factors of the FP32 / BF16 forms (see
-// DeviceState::Bc), in one allocation t that the caller frees; zeroed as the
-// band kernel writes inside the band only.
-static hipError_t band_alloc(DeviceState& d, const LocalPlan& lp, void** t, hipStream_t st) {
+// Memory for the basis functions of window-64 subdomains during a
+// factorization, in one allocation t that the caller frees.  FP64: the vectors
+// of long subdomains (DeviceState::mbf_tmp).  FP32 / BF16: the band factors
+// (DeviceState::Bc), zeroed as the band kernel writes inside the band only.
+static hipError_t basis_alloc(DeviceState& d, const LocalPlan& lp, void** t, hipStream_t st) {
   if (d.bucket_sub[0].empty()) return hipSuccess;
+  if (d.prec == AM_FP64) {
+    if (d.long_pairs == 0) return hipSuccess;
+    const hipError_t e = hipMalloc(t, sizeof(double) * (size_t)d.long_pairs * d.max_np0);
+    d.mbf_tmp = (double*)*t;
+    return e;
+  }
   const size_t bytes = (size_t)lp.band_off.back() * (d.prec == AM_FP32 ? 4 : 2);
   hipError_t e = hipMalloc(t, 2 * bytes + (size_t)lp.roff.back() * 4);
   if (e != hipSuccess) return e;
@@ -684,6 +691,13 @@ static am_status setup_impl(const am_csr* A, const int32_t* part, int32_t nparts
   for (int bk = 0; bk < 2; ++bk) d.bucket_pair[bk].clear();
   for (int64_t pi = 0; pi < npair; ++pi)
     d.bucket_pair[lp.wp[pair_sub[pi]] == 64 ? 0 : 1].push_back((int32_t)pi);
+  d.long_pairs = (int32_t)(d.bucket_pair[0].end() -
+                           std::stable_partition(d.bucket_pair[0].begin(), d.bucket_pair[0].end(),
+                                                 [&](int32_t pi) {
+                                                   const int32_t s2 = pair_sub[pi];
+                                                   return lp.roff[s2 + 1] - lp.roff[s2] <=
+                                                          mbf_onchip_rows();
+                                                 }));
   std::vector<int64_t> mbf_off(st.m + 1, 0);
   for (int32_t s2 = 0; s2 < st.m; ++s2)
     mbf_off[s2 + 1] = mbf_off[s2] + (st.isub_ptr[s2 + 1] - st.isub_ptr[s2]) *
@@ -798,14 +812,12 @@ static am_status setup_impl(const am_csr* A, const int32_t* part, int32_t nparts
   d.cpl = cv;
   d.cpl_kmax = lp.cpl_kmax;
   d.max_ni = lp.max_ni;
-  // FP32 / BF16: band factors of the window-64 subdomains, for their basis
-  // functions (set-up only)
-  struct Band {  // (freed after a failed set-up has destroyed the handle, too)
+  struct Basis {  // (freed after a failed set-up has destroyed the handle, too)
     void* t = nullptr;
-    ~Band() { (void)hipFree(t); }
-  } band;
+    ~Basis() { (void)hipFree(t); }
+  } basis;
   if (d.prec != AM_FP64 && !plain) SCHK(upload(al, &d.band_off, lp.band_off, sm));
-  if (d.prec != AM_FP64 && !plain) SCHK(band_alloc(d, lp, &band.t, sm));
+  if (!plain) SCHK(basis_alloc(d, lp, &basis.t, sm));
   // the band factors (window 128) are written inside their band only; the
   // row layout exists for them alone
   if (!d.bucket_sub[1].empty()) {
@@ -898,7 +910,7 @@ static am_status setup_impl(const am_csr* A, const int32_t* part, int32_t nparts
       d.allocs.erase(it);
       break;
     }
-  d.Lr = d.Bc = d.Br = d.Bd = nullptr;
+  d.Lr = d.Bc = d.Br = d.Bd = d.mbf_tmp = nullptr;
   mark("checks and frees", nullptr);
   for (const auto& ph : phases) std::fprintf(stderr, "algmortar set-up: %-24s %9.2f ms\n", ph.first, ph.second);
   *out = h;
@@ -1203,8 +1215,8 @@ am_status algmortar_update_values(am_handle h, const am_csr* A, void* stream) {
   const size_t nfac = (size_t)h->lp.fac_off[h->st.m];
   void* Lr = nullptr;
   hipError_t he = hipSuccess;
-  void* band = nullptr;
-  if (d.prec != AM_FP64) he = band_alloc(d, h->lp, &band, st);
+  void* basis = nullptr;
+  he = basis_alloc(d, h->lp, &basis, st);
   if (he == hipSuccess && !d.bucket_sub[1].empty()) {
     he = hipMalloc(&Lr, nfac * esz);
     d.Lr = Lr;
@@ -1220,8 +1232,8 @@ am_status algmortar_update_values(am_handle h, const am_csr* A, void* stream) {
   const hipError_t he3 = hipStreamSynchronize(st);
   if (he == hipSuccess) he = he3;
   (void)hipFree(Lr);
-  (void)hipFree(band);
-  d.Lr = d.Bc = d.Br = d.Bd = nullptr;
+  (void)hipFree(basis);
+  d.Lr = d.Bc = d.Br = d.Bd = d.mbf_tmp = nullptr;
   HCHK(he);
   int32_t fl[4];
   HCHK(hipMemcpy(fl, d.fail, sizeof(fl), hipMemcpyDeviceToHost));

@@ -206,6 +206,11 @@ struct DeviceState {
   int32_t* d_bucket_sub[2] = {nullptr, nullptr};
   std::vector<int32_t> bucket_pair[2]; // host: (subdomain, slot) pairs per window width
   int32_t* d_bucket_pair[2] = {nullptr, nullptr};
+  // the last pairs of bucket 0 are those of subdomains whose vector does not
+  // fit the LDS of the basis-function kernel (FP64): max_np0 doubles for each,
+  // during set-up only
+  int32_t long_pairs = 0;
+  double* mbf_tmp = nullptr;
   int32_t* fail = nullptr;     // [4]: failing subdomain and pivot of A_i; failing row of S (device)
 
   // mortar structure
@@ -266,6 +271,9 @@ double* static_scratch_ptr(int device);
 // ---- launchers (kernels_local.hip) ----
 hipError_t launch_band_factor(DeviceState& d, hipStream_t s);
 hipError_t launch_mbf(DeviceState& d, hipStream_t s);
+// padded rows of a window-64 subdomain up to which the basis-function kernel
+// keeps its vector on chip
+int mbf_onchip_rows();
 inline int tile_slot(int nrhs) { return nrhs <= 1 ? 0 : nrhs <= 2 ? 1 : nrhs <= 4 ? 2 : nrhs <= 8 ? 3 : 4; }
 // number of local-kernel wave layouts the autotuner times for nrhs
 int tile_candidates(const DeviceState& d, int nrhs);

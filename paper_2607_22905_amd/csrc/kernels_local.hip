@@ -33,6 +33,8 @@ hipError_t launch_mbf(DeviceState& d, hipStream_t st) {
   }
 }
 
+int mbf_onchip_rows() { return kMbfRows; }
+
 hipError_t launch_invert_diag(DeviceState& d, hipStream_t st) {
   switch (d.prec) {
     case AM_FP64: return invert_diag_t<double>(d, st);

@@ -22,6 +22,7 @@
 // per row between the two sweeps.  Padding rows have a zero factor and
 // dinv = 1.
 #pragma once
+#include <algorithm>
 #include <type_traits>
 
 #include "am_common.h"
@@ -1204,13 +1205,16 @@ hipError_t mbf_t(DeviceState& d, hipStream_t st) {
   const int nb0 = (int)d.bucket_pair[0].size(), nb1 = (int)d.bucket_pair[1].size();
   if (nb0) {
     if constexpr (sizeof(FT) == 8) {
-      // the vector of a subdomain of up to 4096 rows in LDS
-      const bool chip = d.max_np0 <= 4096;
-      auto kern = chip ? &k_tri_mbf<true> : &k_tri_mbf<false>;
-      hipLaunchKernelGGL(kern, dim3(nb0), dim3(64), chip ? d.max_np0 * sizeof(double) : 0, st,
-                         d.d_bucket_pair[0], d.mbf_pair_sub, d.mbf_pair_q, d.desc, (const FT*)d.Lc,
-                         (const IT*)d.invd, (const IT*)d.cpl, d.cidx, d.prp, d.pci, d.pv, d.mbf,
-                         d.bw_ptr, d.bw_row, d.bw_val, d.plain);
+      auto go = [&](auto kern, const int32_t* pairs, int nb, size_t lds) {
+        if (nb > 0)
+          hipLaunchKernelGGL(kern, dim3(nb), dim3(64), lds, st, pairs, d.mbf_pair_sub,
+                             d.mbf_pair_q, d.desc, (const FT*)d.Lc, (const IT*)d.invd,
+                             (const IT*)d.cpl, d.cidx, d.prp, d.pci, d.pv, d.mbf, d.bw_ptr,
+                             d.bw_row, d.bw_val, d.plain, d.mbf_tmp, d.max_np0);
+      };
+      const int on = nb0 - d.long_pairs;
+      go(&k_tri_mbf<true>, d.d_bucket_pair[0], on, std::min(d.max_np0, kMbfRows) * sizeof(double));
+      go(&k_tri_mbf<false>, d.d_bucket_pair[0] + on, d.long_pairs, 0);
     } else {
       // reduced precision: the basis functions define the coarse space, and
       // those of the band sweeps in FT arithmetic are kept

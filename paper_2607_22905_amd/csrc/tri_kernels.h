@@ -496,13 +496,15 @@ __device__ __forceinline__ TriSub<FT> tri_sub(const SubDesc& e, const FT* fac,
 
 // Multiscale basis functions (set-up): one wave per (subdomain, slot), the
 // right-hand side -B_s psi_n scattered from the boundary weights, then the
-// block elimination one block after the other in the vector v (LDS; the
-// output column itself, ONCHIP = false, for a subdomain too long for it).
+// block elimination one block after the other in the vector v (LDS; for a
+// subdomain of more than kMbfRows rows, ONCHIP = false, memory of the set-up:
+// tmp, ldt a workgroup).
 // The interface matrix S is made of 1 - phat at the interfaces, which
 // cancels where phat is near 1, so phat is improved once by the correction
 // for its residual b - A_s phat, accumulated in twice the working precision
 // (the applied z of a 100-cell chain with interfaces on every cell: error
 // 4e-13 with S from unrefined values, 4e-14 so).
+constexpr int kMbfRows = 4096;  // 32 KB
 template <bool ONCHIP>
 __global__ __launch_bounds__(64) void k_tri_mbf(
     const int32_t* __restrict__ pairs, const int32_t* __restrict__ pair_sub,
@@ -511,7 +513,8 @@ __global__ __launch_bounds__(64) void k_tri_mbf(
     const double* __restrict__ cpl, const uint8_t* __restrict__ cidx,
     const int64_t* __restrict__ prp, const int32_t* __restrict__ pci,
     const double* __restrict__ pv, double* mbf, const int64_t* __restrict__ bw_ptr,
-    const int32_t* __restrict__ bw_row, const double* __restrict__ bw_val, int plain) {
+    const int32_t* __restrict__ bw_row, const double* __restrict__ bw_val, int plain,
+    double* tmp, int ldt) {
   __shared__ double tw[128];
   __shared__ double yw[64];
   __shared__ double hw[64];
@@ -521,7 +524,7 @@ __global__ __launch_bounds__(64) void k_tri_mbf(
   const SubDesc e = desc[s];
   const TriSub<double> T = tri_sub(e, fac, dg, cpl, cidx);
   double* col = mbf + e.mbf + (size_t)q * T.N;
-  double* v = ONCHIP ? dyn : col;
+  double* v = ONCHIP ? dyn : tmp + (size_t)blockIdx.x * ldt;
   const int lane = threadIdx.x;
   auto scatter = [&]() {
     for (int row = lane; row < T.N; row += 64) v[row] = 0.0;
@@ -607,44 +610,40 @@ __global__ __launch_bounds__(64) void k_tri_mbf(
   };
   scatter();
   solve();
-  if constexpr (ONCHIP) {
-    for (int row = lane; row < T.N; row += 64) col[row] = v[row];
-    __syncthreads();
-    scatter();
-    {
-      for (int row = lane; row < T.N; row += 64) {
-        double hi = v[row], lo = 0.0;
-        auto add = [&](double a) {  // (hi, lo) += a
+  for (int row = lane; row < T.N; row += 64) col[row] = v[row];
+  __syncthreads();
+  scatter();
+  for (int row = lane; row < T.N; row += 64) {
+    double hi = v[row], lo = 0.0;
+    auto add = [&](double a) {  // (hi, lo) += a
 #pragma clang fp contract(off)
-          const double u = hi + a, w = u - hi;
-          lo += (hi - (u - w)) + (a - w);
-          hi = u;
-        };
-        auto sub = [&](double a, double x) {  // (hi, lo) -= a x
+      const double u = hi + a, w = u - hi;
+      lo += (hi - (u - w)) + (a - w);
+      hi = u;
+    };
+    auto sub = [&](double a, double x) {  // (hi, lo) -= a x
 #pragma clang fp contract(off)
-          const double m = a * x;
-          add(-m);
-          lo -= fma(a, x, -m);
-        };
-        double dout = 0.0, diag = 0.0;
-        for (int64_t p = prp[e.base + row]; p < prp[e.base + row + 1]; ++p) {
-          const int64_t c = (int64_t)pci[p] - e.base;
-          const double a = pv[p];
-          if (c < 0 || c >= T.N)
-            dout += a;
-          else if (c == row)
-            diag = a;
-          else
-            sub(a, col[c]);
-        }
-        sub(plain ? diag : diag - dout, col[row]);
-        v[row] = hi + lo;
-      }
-      __syncthreads();
-      solve();
-      for (int row = lane; row < T.N; row += 64) col[row] += v[row];
+      const double m = a * x;
+      add(-m);
+      lo -= fma(a, x, -m);
+    };
+    double dout = 0.0, diag = 0.0;
+    for (int64_t p = prp[e.base + row]; p < prp[e.base + row + 1]; ++p) {
+      const int64_t c = (int64_t)pci[p] - e.base;
+      const double a = pv[p];
+      if (c < 0 || c >= T.N)
+        dout += a;
+      else if (c == row)
+        diag = a;
+      else
+        sub(a, col[c]);
     }
+    sub(plain ? diag : diag - dout, col[row]);
+    v[row] = hi + lo;
   }
+  __syncthreads();
+  solve();
+  for (int row = lane; row < T.N; row += 64) col[row] += v[row];
 }
 
 // ---------------------------------------------------------------------------
