@@ -203,6 +203,9 @@ __device__ __forceinline__ void tri_full(const TriFrag<FT, 32>& f, int lane,
 // row i of block b, list 0 holds its entries in block b - 1, list 1 those in
 // block b + 1; value (list, k, row) at cpl[(list kc + k) NP + row], the
 // column's row within its block in the byte array; unused places are zero.
+// (An entry beyond the neighbouring blocks was an explicit zero when the order
+// of the rows was chosen.  New values may have given it one since; it is not
+// part of the local operator, here as in the factors and basis functions.)
 template <typename FT>
 __global__ __launch_bounds__(256) void k_tri_couplings(
     const int32_t* __restrict__ subs, const int64_t* __restrict__ sub_ptr,
@@ -226,7 +229,7 @@ __global__ __launch_bounds__(256) void k_tri_couplings(
         const int64_t c = (int64_t)pci[p] - base;
         if (c < 0 || c >= N) continue;
         const int cb = (int)c / 64;
-        if (cb == b) continue;
+        if (cb == b || cb < b - 1 || cb > b + 1) continue;
         const int list = cb < b ? 0 : 1;
         const int at = (list * kc + cnt[list]) * NP + row;
         cv[at] = (AT)pv[p];
@@ -635,7 +638,7 @@ __global__ __launch_bounds__(64) void k_tri_mbf(
         dout += a;
       else if (c == row)
         diag = a;
-      else
+      else if (abs((int)c / 64 - row / 64) <= 1)  // (see k_tri_couplings)
         sub(a, col[c]);
     }
     sub(plain ? diag : diag - dout, col[row]);
