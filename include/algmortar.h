@@ -313,7 +313,9 @@ am_status algmortar_sizes(am_handle h, int64_t* n, int64_t* nparts, int64_t* n_i
                           int64_t* n_edges);
 
 /* Copy the interface matrix S (dense FP64, n_iface x n_iface, row-major,
- * symmetrised) or its inverse to a host buffer.  which: 0 = S, 1 = S^{-1}. */
+ * symmetrised) or its inverse to a host buffer.  which: 0 = S, 1 = S^{-1} (in
+ * the dissection form, which does not keep it, what the interface solve makes
+ * of the unit vectors, symmetrised; takes device memory for it meanwhile). */
 am_status algmortar_export_interface(am_handle h, int32_t which, double* out);
 
 /* Copy the MBF values of basis function `iface` on subdomain `sub` (one of

@@ -1830,17 +1830,17 @@ am_status algmortar_export_interface(am_handle h, int32_t which, double* out) {
   DeviceState& d = h->d;
   if (d.NL == 0) return AM_OK;
   HCHK(hipSetDevice(d.device));
-  const int64_t nS = (int64_t)d.ldS * d.ldS;
-  if (which == 1 && d.nd.on) {  // not kept by the dissection form: formed here
+  if (which == 1 && d.nd.on) {  // not kept by the dissection form: its action on the unit vectors
+    const size_t bytes = sizeof(double) * (size_t)d.NL * d.NL;
     double* t = nullptr;
-    HCHK(hipMalloc((void**)&t, (size_t)(3 * nS + 8192) * sizeof(double)));
-    hipError_t he = dense_inverse(d, d.S, t + nS, t + 2 * nS, t + 3 * nS, t, h->own);
-    if (he == hipSuccess) he = hipStreamSynchronize(h->own);
-    if (he == hipSuccess)
-      he = hipMemcpy2D(out, sizeof(double) * d.NL, t, sizeof(double) * d.ldS, sizeof(double) * d.NL,
-                       d.NL, hipMemcpyDeviceToHost);
+    HCHK(hipMalloc((void**)&t, bytes));
+    hipError_t he = nd_operator(d, t, h->own);
+    if (he == hipSuccess) he = hipMemcpy(out, t, bytes, hipMemcpyDeviceToHost);
     (void)hipFree(t);
     HCHK(he);
+    for (int64_t i = 0; i < d.NL; ++i)
+      for (int64_t j = 0; j < i; ++j)
+        out[i * d.NL + j] = out[j * d.NL + i] = 0.5 * (out[i * d.NL + j] + out[j * d.NL + i]);
     return AM_OK;
   }
   const double* src = which == 0 ? d.S : d.Sinv;

@@ -325,6 +325,8 @@ int64_t nd_max_rows(int nr_max);
 // eta = S^{-1} b by the nested-dissection block elimination (same contract
 // as launch_iface_gemv)
 hipError_t launch_nd_solve(DeviceState& d, int nrhs, int pcg, int init, hipStream_t s);
+// X = S^{-1}, n_iface x n_iface, as that solve applies it (export)
+hipError_t nd_operator(const DeviceState& d, double* X, hipStream_t s);
 // set-up: block inverses, C^{-1} and coupling values from d.S (see
 // kernels_nd.hip); scratch of nd_scratch(d.nd) doubles
 int64_t nd_scratch(const NdDevice& nd);

@@ -311,6 +311,57 @@ hipError_t launch_nd_solve(DeviceState& d, int nr, int pcg, int init, hipStream_
   return hipGetLastError();
 }
 
+// ---- the operator that the solve applies, for export -------------------------
+
+// unit right-hand sides: column k is 1 at ND position p0 + k
+__global__ __launch_bounds__(256) void k_nd_units(int64_t count, int nr, int64_t p0,
+                                                  double* __restrict__ bpart) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t < count) bpart[t] = t / nr == 2 * (p0 + t % nr) ? 1.0 : 0.0;
+}
+
+// row ord[p0 + k] of X from column k of eta
+__global__ __launch_bounds__(256) void k_nd_take(int64_t NL, int nr, int64_t p0,
+                                                 const int32_t* __restrict__ ord,
+                                                 const double* __restrict__ eta,
+                                                 double* __restrict__ X) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t k = t / NL, r = t % NL;
+  if (k < nr && p0 + k < NL) X[(size_t)ord[p0 + k] * NL + r] = eta[r * nr + k];
+}
+
+// X = S^{-1} (NL x NL) as the interface solve applies it, a batch of unit
+// right-hand sides at a time, on vectors of its own (applications of the
+// handle may be running).  Synchronizes st.
+hipError_t nd_operator(const DeviceState& d0, double* X, hipStream_t st) {
+  DeviceState d = d0;
+  const int nr = d.max_nrhs;
+  const int64_t n_b = 2 * d.NL * nr, n_e = (int64_t)d.ldS * nr,
+                n_y = std::max<int64_t>(d.nd.nrows, 1) * nr,
+                n_t = (int64_t)std::max<int32_t>(d.nd.R, 1) * nr,
+                n_p = (int64_t)d.nd.P * std::max<int32_t>(d.nd.ldC, 1) * nr;
+  double* t = nullptr;
+  hipError_t e = hipMalloc((void**)&t, sizeof(double) * (size_t)(n_b + n_e + n_y + n_t + n_p));
+  if (e != hipSuccess) return e;
+  d.bpart = t;
+  d.eta = d.bpart + n_b;
+  d.nd.y1 = d.eta + n_e;
+  d.nd.eta2 = d.nd.y1 + n_y;
+  d.nd.ypart = d.nd.eta2 + n_t;
+  for (int64_t p0 = 0; p0 < d.NL && e == hipSuccess; p0 += nr) {
+    hipLaunchKernelGGL(k_nd_units, dim3((unsigned)((n_b + 255) / 256)), dim3(256), 0, st, n_b, nr,
+                       p0, d.bpart);
+    e = launch_nd_solve(d, nr, 0, 0, st);
+    if (e == hipSuccess)
+      hipLaunchKernelGGL(k_nd_take, dim3((unsigned)((d.NL * nr + 255) / 256)), dim3(256), 0, st,
+                         d.NL, nr, p0, d.nd.ord, d.eta, X);
+  }
+  if (e == hipSuccess) e = hipGetLastError();
+  const hipError_t e2 = hipStreamSynchronize(st);
+  (void)hipFree(t);
+  return e != hipSuccess ? e : e2;
+}
+
 // ---- set-up ----------------------------------------------------------------
 
 // block z of S, padded with the identity to T[z] tiles a side
