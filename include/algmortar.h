@@ -326,9 +326,9 @@ am_status algmortar_export_mbf(am_handle h, int64_t iface, int32_t sub, double* 
 /* Measurement: `reps` back-to-back launches of one apply kernel on the
  * handle's internal stream, bracketed by HIP events (the buffers hold the
  * last call's data).  kernel: 0 = local solves + reconstruction (the band
- * sweeps of Algorithm 2), 1 = interface solve eta = S^{-1} b (row-part
- * products and their sum; AM_ERR_ARG on a handle whose interface solve runs
- * inside the local kernel),
+ * sweeps of Algorithm 2), 1 = interface solve eta = S^{-1} b (its launches;
+ * AM_ERR_ARG where the local kernel forms eta for this number of right-hand
+ * sides: small interface systems, few columns),
  * 2 = interface partial right-hand sides, 3 = the PCG SpMV (p update, A p,
  * (p, Ap)), 4 = the PCG x/r update with the interface partials, 5 = the
  * block solves of the smoother set by algmortar_set_smoother (kernel 0 on the

@@ -1883,13 +1883,14 @@ am_status algmortar_time_kernel(am_handle h, int32_t kernel, int32_t nrhs, int32
     if (ts == AM_OK) ts = algmortar_time_kernel(h->bj, 0, nrhs, reps, avg_ms, bytes);
     return ts == AM_OK ? AM_OK : fail(h, ts, h->bj->err);
   }
-  if (kernel == 1 && (h->d.fuse_eta || (!h->d.nd.on && !h->d.ix.on && h->d.ypart == nullptr)))
-    return fail(h, AM_ERR_ARG,
-                "the interface solve of this handle runs inside the local kernel (kernel 0)");
   DeviceState& d = h->d;
   const Structure& st = h->st;
   const LocalPlan& lp = h->lp;
   const int nr = pow2_at_least(nrhs);
+  if (kernel == 1 &&
+      (d.fuse_eta ? eta_inline(d, nr) : !d.nd.on && !d.ix.on && d.ypart == nullptr))
+    return fail(h, AM_ERR_ARG,
+                "the interface solve of this handle runs inside the local kernel (kernel 0)");
   const double esz = d.prec == AM_FP64 ? 8 : (d.prec == AM_FP32 ? 4 : 2);
   const double isz = d.prec == AM_FP64 ? 8 : 4;
   double by = 0.0;
@@ -1936,6 +1937,9 @@ am_status algmortar_time_kernel(am_handle h, int32_t kernel, int32_t nrhs, int32
     }
     const double vec = (double)d.NL * 8.0 * nr;
     by = blocks + 5.0 * vec + ix.maxit * (12.0 * ix.w * d.NL + blocks + 9.0 * vec);
+  } else if (kernel == 1 && d.fuse_eta) {
+    // S^{-1} once, the interface slots, eta (k_eta_dense)
+    by = (double)d.NL * d.NL * 8.0 + 3.0 * d.NL * 8.0 * nr;
   } else if (kernel == 1) {
     // S^{-1} once, the interface slots, the part sums written and read, eta
     by = (double)d.NL * d.NL * 8.0 + 3.0 * d.NL * 8.0 * nr +
