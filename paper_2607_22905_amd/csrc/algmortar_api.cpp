@@ -951,6 +951,11 @@ static bool single_layout(const DeviceState& d, int nr) {
   return nr == 16 || (nr == 1 && d.bf16_ops && d.bucket_sub[1].empty());
 }
 
+// The set of layouts that an index in a cache file stands for: another number
+// whenever a candidate changes its meaning (1: band tiles for every window; 2:
+// block inverses for window 64).
+static constexpr int kLayouts = 2;
+
 static am_status autotune_tiles(am_handle h, int nr) {
   DeviceState& d = h->d;
   const int slot = tile_slot(nr);
@@ -972,14 +977,16 @@ static am_status autotune_tiles(am_handle h, int nr) {
   }
   // ALGMORTAR_AUTOTUNE_CACHE=file keeps the choices across processes: a
   // line "key choice" per tuned case, the key describing what the layouts
-  // are timed on (sizes, window buckets, factor precision, interface form,
-  // right-hand sides); a case found there is not timed again
+  // are timed on (the set of layouts, kLayouts; sizes, window buckets, longest
+  // subdomains, factor precision, interface form, right-hand sides); a case
+  // found there is not timed again
   const char* cache = std::getenv("ALGMORTAR_AUTOTUNE_CACHE");
   std::string key;
   if (cache && *cache) {
-    key = "n" + std::to_string(d.n) + "_m" + std::to_string(d.m) + "_nl" + std::to_string(d.NL) +
+    key = "v" + std::to_string(kLayouts) + "_n" + std::to_string(d.n) + "_m" + std::to_string(d.m) + "_nl" + std::to_string(d.NL) +
           "_b" + std::to_string(d.bucket_sub[0].size()) + "x" + std::to_string(d.bucket_sub[1].size()) +
-          "_p" + std::to_string(d.prec) + "_f" + std::to_string(d.fuse_eta) + "_pl" +
+          "_np" + std::to_string(d.max_np0) + "x" + std::to_string(d.max_np) +
+          "_p" + std::to_string(d.prec) + "_f" + std::to_string(d.fuse_eta + eta_inline(d, nr)) + "_pl" +
           std::to_string(d.plain) + "_nr" + std::to_string(nr) + "_c" + std::to_string(nc);
     if (FILE* f = std::fopen(cache, "r")) {
       char k[256];
