@@ -810,7 +810,6 @@ static am_status setup_impl(const am_csr* A, const int32_t* part, int32_t nparts
   d.Lc = Lc;
   d.invd = iv;
   d.cpl = cv;
-  d.cpl_kmax = lp.cpl_kmax;
   d.max_ni = lp.max_ni;
   struct Basis {  // (freed after a failed set-up has destroyed the handle, too)
     void* t = nullptr;

@@ -193,7 +193,6 @@ struct DeviceState {
   // (window 128); double for FP64, float otherwise
   void* invd = nullptr;
   // couplings between a window-64 subdomain's neighbouring blocks
-  int32_t cpl_kmax = 0;        // most per row and side
   int32_t max_ni = 0;          // most basis functions on a subdomain
   int32_t max_np0 = 0;         // largest padded row count in window 64
   SubDesc* desc = nullptr;     // [m]

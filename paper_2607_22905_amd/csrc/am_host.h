@@ -171,6 +171,15 @@ uint64_t splitmix64(uint64_t x);
 // Band layout of the local factors.  Inside every subdomain the device uses
 // an ordering (identity or reverse Cuthill-McKee, whichever has the smaller
 // bandwidth) and a window width Wp = 64 * ceil(bandwidth / 64).
+// Whether the block-inverse kernels (window 64) take a subdomain of np padded
+// rows, kc couplings of a row per side and ni basis functions: they index its
+// couplings, basis functions and 16 columns of a vector with 32 bits.
+inline bool tri_indexable(int64_t np, int64_t kc, int64_t ni) {
+  constexpr int64_t lim = INT32_MAX;
+  return np <= lim / 16 && kc <= lim / (2 * std::max<int64_t>(np, 1)) &&
+         ni <= lim / std::max<int64_t>(np, 1);
+}
+
 struct LocalPlan {
   std::vector<int32_t> dperm;      // [n] device order: dperm[new] = old
   std::vector<int32_t> dpos;       // [n] inverse: dpos[old] = new
@@ -180,11 +189,10 @@ struct LocalPlan {
   // packed block inverses), 128 per row (window 128, band)
   std::vector<int64_t> fac_off;
   std::vector<int64_t> band_off;   // [m+1] element offsets of the band factors = padded rows * wp
-  // window 64: most couplings of a row to the block before or after its own,
-  // and [m+1] element offsets of the coupling lists (2 * cpl_k * padded rows)
+  // window 64: most couplings of a row to the block before or after its own
+  // (window 128: 0), and [m+1] element offsets of the coupling lists (2 * cpl_k * padded rows)
   std::vector<int32_t> cpl_k;
   std::vector<int64_t> cpl_off;
-  int32_t cpl_kmax = 0;
   int32_t max_wp = 64;
   int32_t max_ni = 0;              // max |I_i|
   int32_t max_sub = 0;             // max subdomain size

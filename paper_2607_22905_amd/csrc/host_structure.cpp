@@ -501,7 +501,6 @@ am_status plan_local(const HostCSR& A, const Structure& st, LocalPlan& lp, std::
   lp.band_off.assign(st.m + 1, 0);
   lp.cpl_k.assign(st.m, 0);
   lp.cpl_off.assign(st.m + 1, 0);
-  lp.cpl_kmax = 0;
   lp.max_wp = 64;
   lp.max_ni = 0;
   lp.max_sub = 0;
@@ -558,16 +557,20 @@ am_status plan_local(const HostCSR& A, const Structure& st, LocalPlan& lp, std::
             " > 128 (the band kernels support windows up to 128)";
       return AM_ERR_UNSUPPORTED;
     }
+    const int64_t np = ((int64_t)ns + 63) / 64 * 64;
+    const int64_t ni = st.isub_ptr[s + 1] - st.isub_ptr[s];
+    if (wp == 64 && !tri_indexable(np, lp.cpl_k[s], ni)) {  // the band kernels index with 64 bits
+      wp = 128;
+      lp.cpl_k[s] = 0;
+    }
     lp.wp[s] = wp;
     lp.max_wp = std::max(lp.max_wp, wp);
     lp.max_sub = std::max(lp.max_sub, ns);
-    lp.max_ni = std::max<int32_t>(lp.max_ni, (int32_t)(st.isub_ptr[s + 1] - st.isub_ptr[s]));
-    const int64_t np = ((int64_t)ns + 63) / 64 * 64;
+    lp.max_ni = std::max<int32_t>(lp.max_ni, (int32_t)ni);
     lp.roff[s + 1] = lp.roff[s] + np;
     lp.fac_off[s + 1] = lp.fac_off[s] + (wp == 64 ? np * 32 : np * wp);
     lp.band_off[s + 1] = lp.band_off[s] + np * wp;
     lp.cpl_off[s + 1] = lp.cpl_off[s] + 2 * np * lp.cpl_k[s];
-    lp.cpl_kmax = std::max(lp.cpl_kmax, lp.cpl_k[s]);
   }
   return AM_OK;
 }
