@@ -1327,15 +1327,18 @@ hipError_t localt_shape(DeviceState& d, const double* r, double* z, const double
         // up to nine blocks whole), 1 two (more workgroups per CU, the outer
         // tiles read twice), 2 six (up to thirteen blocks)
         constexpr int HT = I == 1 ? 2 : I == 2 ? 6 : 4;
+        const TriArgs<FT> again{d.desc, (const FT*)d.Lc, (const IT*)d.invd, (const IT*)d.cpl, d.cidx, r, z,
+                                mode, d.isub_list, d.mbf, eta, d.q, d.red.pd, off, inl, d.Sinv,
+                                (int)d.NL, d.ldS, d.bpart, d.red.pb, d.m, init, d.sc, d.shared};
         // one right-hand side with BF16 x BF16 products, where every
         // subdomain is in this bucket
         if constexpr (NT == 1 && kBf && I == 0) {
           if (!inl && d.bf16_ops && nb1 == 0) {
-            go(k_tri_solve<FT, 1, HT, true>, 128, 0);
+            go(k_tri_solve<FT, 1, HT, true>, 128, 0, again);
             return;
           }
         }
-        go(k_tri_solve<FT, NT, HT>, 128, 0);
+        go(k_tri_solve<FT, NT, HT>, 128, 0, again);
       }
       return;
     }

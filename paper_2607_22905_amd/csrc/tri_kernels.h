@@ -752,6 +752,28 @@ template <typename FT, int NT, int HT> constexpr int tri_waves() {
   constexpr int regs = (2 * HT + 1) * 4 * (int)sizeof(FT) + 16 * NT + 72;
   return regs <= 128 ? 4 : regs <= 256 ? 2 : 1;
 }
+// The arguments of k_tri_solve once more, for the body of the triangular form
+// (aligned: a gap keeps the loads of both from being merged).
+template <typename FT> struct alignas(64) TriArgs {
+  const SubDesc* desc;
+  const FT* fac;
+  const typename TriAcc<FT>::T *dg, *cpl;
+  const uint8_t* cidx;
+  const double* rin;
+  double* out;
+  int mode;
+  const int32_t* isub_list;
+  const double *mbf, *eta, *qv;
+  double* partial;
+  unsigned blk_off;
+  int fuse_eta;
+  const double* Sinv;
+  int NL, ldS;
+  const double *bpart, *pb;
+  int npb, init;
+  PcgScalars* sc;
+  PcgShared* sh;
+};
 template <typename FT, int NT, int HT, bool BFOP = false>
 __global__ __launch_bounds__(128, (tri_waves<FT, NT, HT>())) void k_tri_solve(
     const int32_t* __restrict__ subs, const SubDesc* __restrict__ desc,
@@ -761,11 +783,10 @@ __global__ __launch_bounds__(128, (tri_waves<FT, NT, HT>())) void k_tri_solve(
     const double* __restrict__ mbf, const double* __restrict__ eta, const double* __restrict__ qv,
     double* __restrict__ partial, unsigned blk_off, int fuse_eta, const double* __restrict__ Sinv,
     int NL, int ldS, const double* __restrict__ bpart, const double* __restrict__ pb, int npb,
-    int init, PcgScalars* sc, PcgShared* sh) {
+    int init, PcgScalars* sc, PcgShared* sh, TriArgs<FT> again) {
   using AT = typename TriAcc<FT>::T;
   constexpr int NTHR = 128;
   constexpr int RR = (2 * HT + 1) * 64;  // rows held on chip
-  constexpr int NS = HT + 1;             // rows per thread of those, rounded up
   __shared__ AT tw_all[2][NT * 128];
   __shared__ AT ex[2][3][NT * 64];  // what a half hands to the other at the middle
   __shared__ AT rs[RR * NT];        // r; then w, then x of the blocks already done
@@ -780,158 +801,169 @@ __global__ __launch_bounds__(128, (tri_waves<FT, NT, HT>())) void k_tri_solve(
   // a solve that has stopped (with the fused interface solve workgroup 0 of
   // this launch may be writing the flag: the stop test below decides)
   if (mode == 2 && !fuse_eta && all_done(sh)) return;
-  const int64_t base = e.base, i0 = e.i0;
-  const TriSub<FT> T = tri_sub(e, fac, dg, cpl, cidx);
-  const int lane = threadIdx.x & 63;
-  const int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int ns = mode >= 1 ? e.ns : 0;
-  const double* P = mbf + e.mbf;
-  AT* tw = tw_all[g];
+  // The triangular form has a body of its own, which streams all blocks but the
+  // middle one, and arguments of its own: scalar loads with a use in both
+  // bodies would stay before the branch, more of them than there are registers.
+  // (The FP32 kernel at 128^3: with a branch around each product 8% slower,
+  // with shared arguments 6%, so as without the form.)
+  auto solve = [&](auto form, const SubDesc& e, const FT* fac, const AT* dg, const AT* cpl, const uint8_t* cidx,
+                   const double* rin, double* out, int mode, const int32_t* isub_list,
+                   const double* mbf, const double* eta, const double* qv, double* partial,
+                   unsigned blk_off, int fuse_eta, const double* Sinv, int NL, int ldS,
+                   const double* bpart, const double* pb, int npb, int init, PcgScalars* sc,
+                   PcgShared* sh) AM_INLINE {
+    constexpr bool TRI = decltype(form)::value;
+    constexpr int HE = TRI ? 0 : HT;        // blocks of a half that are held
+    constexpr int RH = (2 * HE + 1) * 64;   // rows held on chip
+    constexpr int NS = HE + 1;              // rows per thread of those, rounded up
+    const int64_t base = e.base, i0 = e.i0;
+    const TriSub<FT> T = tri_sub(e, fac, dg, cpl, cidx);
+    const int lane = threadIdx.x & 63;
+    const int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int ns = mode >= 1 ? e.ns : 0;
+    const double* P = mbf + e.mbf;
+    AT* tw = tw_all[g];
 
-  // step k of a half (k = 0 the outermost block); off steps are streamed
-  // (the triangular form streams all but the middle block: two products a
-  // block in two places of the code)
-  const int held = T.tri ? 0 : HT;
-  const int off = max(0, T.h - held);
-  const int r_lo = 64 * off;  // first row held on chip
-  const int r_n = min(T.NP - r_lo, (2 * held + 1) * 64);  // rows held on chip
-  auto blk = [&](int k) AM_INLINE { return g == 0 ? k : T.NB - 1 - (k - T.d); };
-  auto active = [&](int k) AM_INLINE { return g == 0 || k >= T.d; };
-  // list of a row's couplings to the block that comes before it on the way to
-  // the middle (F) and after it (B)
-  const int LF = g == 0 ? 0 : 1, LB = 1 - LF;
+    // step k of a half (k = 0 the outermost block); off steps are streamed
+    const int off = max(0, T.h - HE);
+    const int r_lo = 64 * off;             // first row held on chip
+    const int r_n = min(T.NP - r_lo, RH);  // rows held on chip
+    auto blk = [&](int k) AM_INLINE { return g == 0 ? k : T.NB - 1 - (k - T.d); };
+    auto active = [&](int k) AM_INLINE { return g == 0 || k >= T.d; };
+    // list of a row's couplings to the block that comes before it on the way to
+    // the middle (F) and after it (B)
+    const int LF = g == 0 ? 0 : 1, LB = 1 - LF;
 
-  // ---- loads: what goes to LDS, then the tiles (in the order of their use:
-  // a wait for an early load does not wait for the later ones) ----
-  AT rv[NS][NT], dv[NS];
+    // ---- loads: what goes to LDS, then the tiles (in the order of their use:
+    // a wait for an early load does not wait for the later ones) ----
+    AT rv[NS][NT], dv[NS];
 #pragma unroll
-  for (int u = 0; u < NS; ++u) {
-    const int t = u * NTHR + threadIdx.x, row = r_lo + t;
+    for (int u = 0; u < NS; ++u) {
+      const int t = u * NTHR + threadIdx.x, row = r_lo + t;
 #pragma unroll
-    for (int k = 0; k < NT; ++k)
-      rv[u][k] = (t < r_n && row < T.N) ? (AT)rin[(size_t)(base + row) * NT + k] : (AT)0;
-    dv[u] = t < r_n ? T.dg[row] : (AT)0;
-  }
-  int eid = 0;  // basis function of the thread's first interface value
-  if (!fuse_eta && (int)threadIdx.x < ns * NT) eid = isub_list[i0 + threadIdx.x / NT];
-  // the tiles: two steps ahead of their use (the first two here); all of
-  // them at once flood the memory system, and no workgroup gets its first
-  // tile before the others have got their last.  No branch around the loads:
-  // waits at the joins would put them one after the other; a half with fewer
-  // blocks loads its last one again.
-  TriFrag<FT, 32> D[HT];
-  TriFrag<FT, 16> Dm;
-  auto fetch_tile = [&](auto jc) AM_INLINE {
-    constexpr int j = decltype(jc)::value;
-    if constexpr (j < HT) {
-      const int k = min(off + j, T.h - 1);
-      D[j].load(T.fac + (size_t)(k >= 0 && active(k) ? blk(k) : T.h) * kTriElems, 0, lane);
-    } else if constexpr (j == HT) {
-      Dm.load(T.fac + (size_t)T.h * kTriElems, 16 * g, lane);
+      for (int k = 0; k < NT; ++k)
+        rv[u][k] = (t < r_n && row < T.N) ? (AT)rin[(size_t)(base + row) * NT + k] : (AT)0;
+      dv[u] = t < r_n ? T.dg[row] : (AT)0;
     }
-  };
-  fetch_tile(std::integral_constant<int, 0>{});
-  fetch_tile(std::integral_constant<int, 1>{});
-#pragma unroll
-  for (int u = 0; u < NS; ++u) {
-    const int t = u * NTHR + threadIdx.x;
-    if (t < r_n) {
-#pragma unroll
-      for (int k = 0; k < NT; ++k) rs[k * RR + t] = rv[u][k];
-      ds[t] = dv[u];
-    }
-  }
-  double ev = 0.0;
-  if (!fuse_eta && (int)threadIdx.x < ns * NT) ev = eta[(size_t)eid * NT + threadIdx.x % NT];
-  __syncthreads();
-
-  // row values of block b for this lane, and v += sign * (couplings of list
-  // `list`) . (the neighbour's values y)
-  auto rhs = [&](int b, AT (&v)[NT]) AM_INLINE {
-    const int t = 64 * b + lane - r_lo;
-#pragma unroll
-    for (int k = 0; k < NT; ++k) {
-      if (64 * b >= r_lo && 64 * b < r_lo + r_n)  // uniform
-        v[k] = rs[k * RR + t];
-      else
-        v[k] = 64 * b + lane < T.N ? (AT)rin[(size_t)(base + 64 * b + lane) * NT + k] : (AT)0;
-    }
-  };
-  // the next step's couplings (this lane's row, places 0 .. KA-1), requested
-  // a product ahead and before the tile that is requested with them
-  constexpr int KA = 5;  // boxes have one place, bisection parts three to five
-  AT cv[KA];
-  int ci[KA];
-  auto ahead = [&](int b, int list) AM_INLINE {
-    if (T.kc == 0) return;
-    const int at = list * T.kc * T.NP + 64 * b + lane;
-    cv[0] = T.cpl[at];
-    ci[0] = T.cidx[at];
-    if (T.kc > 1)
-#pragma unroll
-      for (int k = 1; k < KA; ++k) {
-        const int ak = at + min(k, T.kc - 1) * T.NP;
-        cv[k] = T.cpl[ak];
-        ci[k] = T.cidx[ak];
+    int eid = 0;  // basis function of the thread's first interface value
+    if (!fuse_eta && (int)threadIdx.x < ns * NT) eid = isub_list[i0 + threadIdx.x / NT];
+    // the tiles: two steps ahead of their use (the first two here); all of
+    // them at once flood the memory system, and no workgroup gets its first
+    // tile before the others have got their last.  No branch around the loads:
+    // waits at the joins would put them one after the other; a half with fewer
+    // blocks loads its last one again.
+    TriFrag<FT, 32> D[HE > 0 ? HE : 1];
+    TriFrag<FT, 16> Dm;
+    auto fetch_tile = [&](auto jc) AM_INLINE {
+      constexpr int j = decltype(jc)::value;
+      if constexpr (j < HE) {
+        const int k = min(off + j, T.h - 1);
+        D[j].load(T.fac + (size_t)(k >= 0 && active(k) ? blk(k) : T.h) * kTriElems, 0, lane);
+      } else if constexpr (j == HE) {
+        Dm.load(T.fac + (size_t)T.h * kTriElems, 16 * g, lane);
       }
-  };
-  auto couple = [&](int b, int list, AT sign, const AT (&y)[NT], AT (&v)[NT]) AM_INLINE {
-    if (T.kc == 0) return;
-    if constexpr (NT > 1) {
-      tri_wave_sync();
-#pragma unroll
-      for (int c = 0; c < NT; ++c) tw[128 * c + lane] = y[c];
-      tri_wave_sync();
-    }
-    auto add = [&](AT w, int i) AM_INLINE {
-#pragma unroll
-      for (int c = 0; c < NT; ++c)
-        v[c] = fma(w, NT > 1 ? tw[128 * c + i] : lane_value(y[c], i), v[c]);
     };
-    add(sign * cv[0], ci[0]);
-    if (T.kc > 1) {
+    fetch_tile(std::integral_constant<int, 0>{});
+    fetch_tile(std::integral_constant<int, 1>{});
 #pragma unroll
-      for (int k = 1; k < KA; ++k) add(k < T.kc ? sign * cv[k] : (AT)0, ci[k]);
-      for (int k = KA; k < T.kc; ++k) {
-        const int at = (list * T.kc + k) * T.NP + 64 * b + lane;
-        add(sign * T.cpl[at], T.cidx[at]);
+    for (int u = 0; u < NS; ++u) {
+      const int t = u * NTHR + threadIdx.x;
+      if (t < r_n) {
+#pragma unroll
+        for (int k = 0; k < NT; ++k) rs[k * RR + t] = rv[u][k];
+        ds[t] = dv[u];
       }
     }
-  };
-  // a product's vector operand: rounded to BF16 on request (the stored
-  // diagonals are BF16 then, so their products are exact in FP32)
-  auto operand = [&](AT v) AM_INLINE -> AT {
-    if constexpr (BFOP)
-      return __builtin_bit_cast(float, (uint32_t)(uint16_t)am_bf16_rne(v) << 16);
-    else
-      return v;
-  };
-  auto put = [&](const AT (&v)[NT]) AM_INLINE {  // t where the product reads it, twice
-    tri_wave_sync();
+    double ev = 0.0;
+    if (!fuse_eta && (int)threadIdx.x < ns * NT) ev = eta[(size_t)eid * NT + threadIdx.x % NT];
+    __syncthreads();
+
+    // row values of block b for this lane, and v += sign * (couplings of list
+    // `list`) . (the neighbour's values y)
+    auto rhs = [&](int b, AT (&v)[NT]) AM_INLINE {
+      const int t = 64 * b + lane - r_lo;
 #pragma unroll
-    for (int k = 0; k < NT; ++k) {
-      tw[128 * k + lane] = v[k];
-      tw[128 * k + lane + 64] = v[k];
-    }
-    tri_wave_sync();
-  };
-  // y = X_b t, the tile in f
-  auto product = [&](const TriFrag<FT, 32>& f, int b, const AT (&t)[NT], AT (&y)[NT]) AM_INLINE {
-    AT tp[NT];
+      for (int k = 0; k < NT; ++k) {
+        if (64 * b >= r_lo && 64 * b < r_lo + r_n)  // uniform
+          v[k] = rs[k * RR + t];
+        else
+          v[k] = 64 * b + lane < T.N ? (AT)rin[(size_t)(base + 64 * b + lane) * NT + k] : (AT)0;
+      }
+    };
+    // the next step's couplings (this lane's row, places 0 .. KA-1), requested
+    // a product ahead and before the tile that is requested with them
+    constexpr int KA = 5;  // boxes have one place, bisection parts three to five
+    AT cv[KA];
+    int ci[KA];
+    auto ahead = [&](int b, int list) AM_INLINE {
+      if (T.kc == 0) return;
+      const int at = list * T.kc * T.NP + 64 * b + lane;
+      cv[0] = T.cpl[at];
+      ci[0] = T.cidx[at];
+      if (T.kc > 1)
 #pragma unroll
-    for (int k = 0; k < NT; ++k) tp[k] = operand(t[k]);
-    put(tp);
-    const int i = 64 * b + lane - r_lo;
-    const AT dgv = (64 * b >= r_lo && 64 * b < r_lo + r_n) ? ds[i] : T.dg[64 * b + lane];
+        for (int k = 1; k < KA; ++k) {
+          const int ak = at + min(k, T.kc - 1) * T.NP;
+          cv[k] = T.cpl[ak];
+          ci[k] = T.cidx[ak];
+        }
+    };
+    auto couple = [&](int b, int list, AT sign, const AT (&y)[NT], AT (&v)[NT]) AM_INLINE {
+      if (T.kc == 0) return;
+      if constexpr (NT > 1) {
+        tri_wave_sync();
 #pragma unroll
-    for (int k = 0; k < NT; ++k) y[k] = dgv * t[k];
-    tri_full<FT, NT>(f, lane, tp, tw, y);
-  };
-  // the same of a streamed block, in either form
-  auto product_streamed = [&](const TriFrag<FT, 32>& f, int b, const AT (&t)[NT],
-                              AT (&y)[NT]) AM_INLINE {
-    if constexpr (sizeof(FT) < 8) {
-      if (T.tri) {
+        for (int c = 0; c < NT; ++c) tw[128 * c + lane] = y[c];
+        tri_wave_sync();
+      }
+      auto add = [&](AT w, int i) AM_INLINE {
+#pragma unroll
+        for (int c = 0; c < NT; ++c)
+          v[c] = fma(w, NT > 1 ? tw[128 * c + i] : lane_value(y[c], i), v[c]);
+      };
+      add(sign * cv[0], ci[0]);
+      if (T.kc > 1) {
+#pragma unroll
+        for (int k = 1; k < KA; ++k) add(k < T.kc ? sign * cv[k] : (AT)0, ci[k]);
+        for (int k = KA; k < T.kc; ++k) {
+          const int at = (list * T.kc + k) * T.NP + 64 * b + lane;
+          add(sign * T.cpl[at], T.cidx[at]);
+        }
+      }
+    };
+    // a product's vector operand: rounded to BF16 on request (the stored
+    // diagonals are BF16 then, so their products are exact in FP32)
+    auto operand = [&](AT v) AM_INLINE -> AT {
+      if constexpr (BFOP)
+        return __builtin_bit_cast(float, (uint32_t)(uint16_t)am_bf16_rne(v) << 16);
+      else
+        return v;
+    };
+    auto put = [&](const AT (&v)[NT]) AM_INLINE {  // t where the product reads it, twice
+      tri_wave_sync();
+#pragma unroll
+      for (int k = 0; k < NT; ++k) {
+        tw[128 * k + lane] = v[k];
+        tw[128 * k + lane + 64] = v[k];
+      }
+      tri_wave_sync();
+    };
+    // y = X_b t, the tile in f
+    auto product = [&](const TriFrag<FT, 32>& f, int b, const AT (&t)[NT], AT (&y)[NT]) AM_INLINE {
+      AT tp[NT];
+#pragma unroll
+      for (int k = 0; k < NT; ++k) tp[k] = operand(t[k]);
+      put(tp);
+      const int i = 64 * b + lane - r_lo;
+      const AT dgv = (64 * b >= r_lo && 64 * b < r_lo + r_n) ? ds[i] : T.dg[64 * b + lane];
+#pragma unroll
+      for (int k = 0; k < NT; ++k) y[k] = dgv * t[k];
+      tri_full<FT, NT>(f, lane, tp, tw, y);
+    };
+    // the same of a streamed block, in either form
+    auto product_streamed = [&](const TriFrag<FT, 32>& f, int b, const AT (&t)[NT],
+                                AT (&y)[NT]) AM_INLINE {
+      if constexpr (TRI) {
         AT tp[NT], v[NT], a[NT], h[NT];
 #pragma unroll
         for (int k = 0; k < NT; ++k) tp[k] = operand(t[k]);
@@ -947,252 +979,266 @@ __global__ __launch_bounds__(128, (tri_waves<FT, NT, HT>())) void k_tri_solve(
         tri_partial<FT, 32, NT, 2>(f, 0, lane, tp, tw, a, h);
 #pragma unroll
         for (int k = 0; k < NT; ++k) y[k] = v[k] + (a[k] + wave_ror1(h[k]));
-        return;
+      } else {
+        product(f, b, t, y);
       }
-    }
-    product(f, b, t, y);
-  };
+    };
 
-  AT y[NT], t[NT];
+    AT y[NT], t[NT];
 #pragma unroll
-  for (int k = 0; k < NT; ++k) y[k] = (AT)0;
-  // ---- elimination towards the middle: streamed blocks, then resident ----
-  const int first = g == 0 ? 0 : T.d;
-  for (int k = first; k < off; ++k) {
-    const int b = blk(k);
-    TriFrag<FT, 32> f;
-    f.load(T.fac + (size_t)b * kTriElems, 0, lane);
-    rhs(b, t);
-    if (k > first) couple(b, LF, (AT)-1, y, t);
-    ahead(k + 1 < T.h ? blk(k + 1) : T.h, LF);
-    product_streamed(f, b, t, y);
-    if (64 * b + lane < T.N)
+    for (int k = 0; k < NT; ++k) y[k] = (AT)0;
+    // ---- elimination towards the middle: streamed blocks, then resident ----
+    const int first = g == 0 ? 0 : T.d;
+    for (int k = first; k < off; ++k) {
+      const int b = blk(k);
+      TriFrag<FT, 32> f;
+      f.load(T.fac + (size_t)b * kTriElems, 0, lane);
+      rhs(b, t);
+      if (k > first) couple(b, LF, (AT)-1, y, t);
+      ahead(k + 1 < T.h ? blk(k + 1) : T.h, LF);
+      product_streamed(f, b, t, y);
+      if (64 * b + lane < T.N)
 #pragma unroll
-      for (int c = 0; c < NT; ++c) out[(size_t)(base + 64 * b + lane) * NT + c] = (double)y[c];
-  }
-  auto inward = [&](auto jc) AM_INLINE {
-    constexpr int j = decltype(jc)::value;
-    if constexpr (j < HT) {
-      const int k = off + j;
-      const bool act = k < T.h && k >= first;  // uniform
-      const int b = act ? blk(k) : 0;
-      if (act) {
-        rhs(b, t);
-        if (k > first) couple(b, LF, (AT)-1, y, t);
-        ahead(k + 1 < T.h ? blk(k + 1) : T.h, LF);
-      }
-      fetch_tile(std::integral_constant<int, j + 2>{});
-      if (act) {
-        product(D[j], b, t, y);
-#pragma unroll
-        for (int c = 0; c < NT; ++c) rs[c * RR + 64 * b - r_lo + lane] = y[c];
-      }
+        for (int c = 0; c < NT; ++c) out[(size_t)(base + 64 * b + lane) * NT + c] = (double)y[c];
     }
-  };
-  static_assert(HT <= 6, "steps written out");
-  inward(std::integral_constant<int, 0>{});
-  inward(std::integral_constant<int, 1>{});
-  inward(std::integral_constant<int, 2>{});
-  inward(std::integral_constant<int, 3>{});
-  inward(std::integral_constant<int, 4>{});
-  inward(std::integral_constant<int, 5>{});
-  // the fused interface solve and its stop test here: its loads would queue
-  // behind the tiles at the start (64^3: 6 us before the first step)
-  if (fuse_eta && local_prologue<NT, 2>(mode, ns, i0, isub_list, Sinv, NL, ldS, bpart, pb, npb, init,
-                                        sc, sh, etap, eta_s, &stop_s))
-    return;
-  // ---- middle block: both waves ----
-  {
-    AT cm[NT];
+    auto inward = [&](auto jc) AM_INLINE {
+      constexpr int j = decltype(jc)::value;
+      if constexpr (j < HE) {
+        const int k = off + j;
+        const bool act = k < T.h && k >= first;  // uniform
+        const int b = act ? blk(k) : 0;
+        if (act) {
+          rhs(b, t);
+          if (k > first) couple(b, LF, (AT)-1, y, t);
+          ahead(k + 1 < T.h ? blk(k + 1) : T.h, LF);
+        }
+        fetch_tile(std::integral_constant<int, j + 2>{});
+        if (act) {
+          product(D[j], b, t, y);
 #pragma unroll
-    for (int c = 0; c < NT; ++c) cm[c] = (AT)0;
-    if (g == 0 ? T.h > 0 : T.len1 > 0) couple(T.h, LF, (AT)1, y, cm);
-#pragma unroll
-    for (int c = 0; c < NT; ++c) ex[g][0][64 * c + lane] = cm[c];
-    if (!fuse_eta) {
-      if ((int)threadIdx.x < ns * NT) eta_s[threadIdx.x] = ev;
-      for (int q = NTHR + threadIdx.x; q < ns * NT; q += NTHR)
-        eta_s[q] = eta[(size_t)isub_list[i0 + q / NT] * NT + q % NT];
-    }
-    rhs(T.h, t);
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < NT; ++c)
-      t[c] = (t[c] - ex[0][0][64 * c + lane]) - ex[1][0][64 * c + lane];
-    AT tp[NT], a[NT], h[NT];
-#pragma unroll
-    for (int k = 0; k < NT; ++k) tp[k] = operand(t[k]);
-    put(tp);
-    if (g == 0 ? T.h > 0 : T.len1 > 0) ahead(blk(T.h - 1), LB);
-    const AT dgv = ds[64 * T.h + lane - r_lo];
-    // a wave's 16 diagonals and the main one (times d t), added up over both
-    auto meet = [&](AT d) AM_INLINE {
-#pragma unroll
-      for (int k = 0; k < NT; ++k) {
-        if (g == 0) a[k] = fma(d, t[k], a[k]);
-        ex[g][1][64 * k + lane] = a[k];
-        ex[g][2][64 * k + ((lane + 16 * g + 1) & 63)] = h[k];
+          for (int c = 0; c < NT; ++c) rs[c * RR + 64 * b - r_lo + lane] = y[c];
+        }
       }
+    };
+    static_assert(HE <= 6, "steps written out");
+    inward(std::integral_constant<int, 0>{});
+    inward(std::integral_constant<int, 1>{});
+    inward(std::integral_constant<int, 2>{});
+    inward(std::integral_constant<int, 3>{});
+    inward(std::integral_constant<int, 4>{});
+    inward(std::integral_constant<int, 5>{});
+    // the fused interface solve and its stop test here: its loads would queue
+    // behind the tiles at the start (64^3: 6 us before the first step)
+    if (fuse_eta && local_prologue<NT, 2>(mode, ns, i0, isub_list, Sinv, NL, ldS, bpart, pb, npb, init,
+                                          sc, sh, etap, eta_s, &stop_s))
+      return;
+    // ---- middle block: both waves ----
+    {
+      AT cm[NT];
+#pragma unroll
+      for (int c = 0; c < NT; ++c) cm[c] = (AT)0;
+      if (g == 0 ? T.h > 0 : T.len1 > 0) couple(T.h, LF, (AT)1, y, cm);
+#pragma unroll
+      for (int c = 0; c < NT; ++c) ex[g][0][64 * c + lane] = cm[c];
+      if (!fuse_eta) {
+        if ((int)threadIdx.x < ns * NT) eta_s[threadIdx.x] = ev;
+        for (int q = NTHR + threadIdx.x; q < ns * NT; q += NTHR)
+          eta_s[q] = eta[(size_t)isub_list[i0 + q / NT] * NT + q % NT];
+      }
+      rhs(T.h, t);
       __syncthreads();
 #pragma unroll
-      for (int k = 0; k < NT; ++k)
-        y[k] = (ex[0][1][64 * k + lane] + ex[1][1][64 * k + lane]) +
-               (ex[0][2][64 * k + lane] + ex[1][2][64 * k + lane]);
-    };
-    bool done = false;
-    if constexpr (sizeof(FT) < 8) {
-      if (T.tri) {  // uniform over the workgroup
-        done = true;
-        tri_partial<FT, 16, NT, 1>(Dm, 16 * g, lane, tp, tw, a, h);
-        meet((AT)1);
+      for (int c = 0; c < NT; ++c)
+        t[c] = (t[c] - ex[0][0][64 * c + lane]) - ex[1][0][64 * c + lane];
+      AT tp[NT], a[NT], h[NT];
+#pragma unroll
+      for (int k = 0; k < NT; ++k) tp[k] = operand(t[k]);
+      put(tp);
+      if (g == 0 ? T.h > 0 : T.len1 > 0) ahead(blk(T.h - 1), LB);
+      // both waves' 16 diagonals and the main one, added up
+      auto meet = [&]() AM_INLINE {
 #pragma unroll
         for (int k = 0; k < NT; ++k) {
-          t[k] = dgv * y[k];
+          ex[g][1][64 * k + lane] = a[k];
+          ex[g][2][64 * k + ((lane + 16 * g + 1) & 63)] = h[k];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < NT; ++k)
+          y[k] = (ex[0][1][64 * k + lane] + ex[1][1][64 * k + lane]) +
+                 (ex[0][2][64 * k + lane] + ex[1][2][64 * k + lane]);
+      };
+      if constexpr (TRI) {
+        tri_partial<FT, 16, NT, 1>(Dm, 16 * g, lane, tp, tw, a, h);
+        if (g == 0)
+#pragma unroll
+          for (int k = 0; k < NT; ++k) a[k] += t[k];
+        meet();
+#pragma unroll
+        for (int k = 0; k < NT; ++k) {
+          t[k] = ds[64 * T.h + lane - r_lo] * y[k];
           tp[k] = operand(t[k]);
         }
         put(tp);
         tri_partial<FT, 16, NT, 2>(Dm, 16 * g, lane, tp, tw, a, h);
+        if (g == 0)
+#pragma unroll
+          for (int k = 0; k < NT; ++k) a[k] += t[k];
         __syncthreads();  // the sums of the first product are read
-        meet((AT)1);
+      } else {
+        tri_partial<FT, 16, NT>(Dm, 16 * g, lane, tp, tw, a, h);
+        if (g == 0) {
+          const AT dgv = ds[64 * T.h + lane - r_lo];
+#pragma unroll
+          for (int k = 0; k < NT; ++k) a[k] = fma(dgv, t[k], a[k]);
+        }
       }
+      meet();
+      if (g == 0)
+#pragma unroll
+        for (int k = 0; k < NT; ++k) rs[k * RR + 64 * T.h - r_lo + lane] = y[k];
     }
-    if (!done) {
-      tri_partial<FT, 16, NT>(Dm, 16 * g, lane, tp, tw, a, h);
-      meet(dgv);
-    }
-    if (g == 0)
+    // ---- back outwards ----
+    double rz[NT], qz[NT];
 #pragma unroll
-      for (int k = 0; k < NT; ++k) rs[k * RR + 64 * T.h - r_lo + lane] = y[k];
-  }
-  // ---- back outwards ----
-  double rz[NT], qz[NT];
+    for (int k = 0; k < NT; ++k) rz[k] = qz[k] = 0.0;
+    // (q, z) enters the flexible beta only
+    const int flexible = mode == 2 ? sh->flexible : 0;
+    // z of a row from its x and its share of the dots; the row's basis functions
+    // (six: a box's faces) and vector values are loaded before
+    struct RowIn {
+      double p[6], r[NT], q[NT];
+    };
+    auto load_in = [&](int row, RowIn& in) AM_INLINE {
 #pragma unroll
-  for (int k = 0; k < NT; ++k) rz[k] = qz[k] = 0.0;
-  // (q, z) enters the flexible beta only
-  const int flexible = mode == 2 ? sh->flexible : 0;
-  // z of a row from its x and its share of the dots; the row's basis functions
-  // (six: a box's faces) and vector values are loaded before
-  struct RowIn {
-    double p[6], r[NT], q[NT];
-  };
-  auto load_in = [&](int row, RowIn& in) AM_INLINE {
+      for (int u = 0; u < 6; ++u) in.p[u] = u < ns ? P[(size_t)u * T.N + row] : 0.0;
 #pragma unroll
-    for (int u = 0; u < 6; ++u) in.p[u] = u < ns ? P[(size_t)u * T.N + row] : 0.0;
+      for (int k = 0; k < NT; ++k) {
+        const size_t o = (size_t)(base + row) * NT + k;
+        in.r[k] = mode == 2 ? rin[o] : 0.0;
+        in.q[k] = flexible ? qv[o] : 0.0;
+      }
+    };
+    auto finish = [&](int row, const AT (&x)[NT], const RowIn& in) AM_INLINE {
+      double z[NT];
 #pragma unroll
-    for (int k = 0; k < NT; ++k) {
-      const size_t o = (size_t)(base + row) * NT + k;
-      in.r[k] = mode == 2 ? rin[o] : 0.0;
-      in.q[k] = flexible ? qv[o] : 0.0;
-    }
-  };
-  auto finish = [&](int row, const AT (&x)[NT], const RowIn& in) AM_INLINE {
-    double z[NT];
-#pragma unroll
-    for (int k = 0; k < NT; ++k) z[k] = (double)x[k];
-#pragma unroll
-    for (int u = 0; u < 6; ++u)
-      if (u < ns)
-#pragma unroll
-        for (int k = 0; k < NT; ++k) z[k] = fma(in.p[u], eta_s[u * NT + k], z[k]);
-    for (int q0 = 6; q0 < ns; q0 += 6) {
-      double pq[6];
-#pragma unroll
-      for (int u = 0; u < 6; ++u) pq[u] = P[(size_t)min(q0 + u, ns - 1) * T.N + row];
+      for (int k = 0; k < NT; ++k) z[k] = (double)x[k];
 #pragma unroll
       for (int u = 0; u < 6; ++u)
-        if (q0 + u < ns)
+        if (u < ns)
 #pragma unroll
-          for (int k = 0; k < NT; ++k) z[k] = fma(pq[u], eta_s[(q0 + u) * NT + k], z[k]);
-    }
+          for (int k = 0; k < NT; ++k) z[k] = fma(in.p[u], eta_s[u * NT + k], z[k]);
+      for (int q0 = 6; q0 < ns; q0 += 6) {
+        double pq[6];
 #pragma unroll
-    for (int k = 0; k < NT; ++k) {
-      rz[k] = fma(in.r[k], z[k], rz[k]);
-      qz[k] = fma(in.q[k], z[k], qz[k]);
-      out[(size_t)(base + row) * NT + k] = z[k];
-    }
-  };
-  // the resident rows are finished RB at a time with their loads together;
-  // the first ones' loads go out before the way back (after it, their round
-  // trip stands alone at the end of the workgroup)
-  const int rows = min(r_n, T.N - r_lo);
-  constexpr int RB = NT == 1 ? 4 : NT == 2 ? 2 : 1;
-  RowIn ri[RB];
-  auto load_first = [&]() AM_INLINE {
+        for (int u = 0; u < 6; ++u) pq[u] = P[(size_t)min(q0 + u, ns - 1) * T.N + row];
 #pragma unroll
-    for (int u = 0; u < RB; ++u) load_in(r_lo + min((int)threadIdx.x + NTHR * u, rows - 1), ri[u]);
-  };
-  constexpr bool kEarly = NT == 1 && HT == 4;  // (elsewhere the registers don't allow it)
-  if constexpr (kEarly) load_first();
+        for (int u = 0; u < 6; ++u)
+          if (q0 + u < ns)
 #pragma unroll
-  for (int j = HT - 1; j >= 0; --j) {
-    const int k = off + j;
-    if (k >= T.h || k < first) continue;  // uniform
-    const int b = blk(k);
-    AT wv[NT];
-    rhs(b, wv);
+            for (int k = 0; k < NT; ++k) z[k] = fma(pq[u], eta_s[(q0 + u) * NT + k], z[k]);
+      }
 #pragma unroll
-    for (int c = 0; c < NT; ++c) t[c] = (AT)0;
-    couple(b, LB, (AT)1, y, t);
-    if (k > first) ahead(blk(k - 1), LB);
-    product(D[j], b, t, y);
+      for (int k = 0; k < NT; ++k) {
+        rz[k] = fma(in.r[k], z[k], rz[k]);
+        qz[k] = fma(in.q[k], z[k], qz[k]);
+        out[(size_t)(base + row) * NT + k] = z[k];
+      }
+    };
+    // the resident rows are finished RB at a time with their loads together;
+    // the first ones' loads go out before the way back (after it, their round
+    // trip stands alone at the end of the workgroup)
+    const int rows = min(r_n, T.N - r_lo);
+    constexpr int RB = NT == 1 ? 4 : NT == 2 ? 2 : 1;
+    RowIn ri[RB];
+    auto load_first = [&]() AM_INLINE {
 #pragma unroll
-    for (int c = 0; c < NT; ++c) {
-      y[c] = wv[c] - y[c];
-      rs[c * RR + 64 * b - r_lo + lane] = y[c];
-    }
-  }
-  for (int k = off - 1; k >= first; --k) {
-    const int b = blk(k);
-    TriFrag<FT, 32> f;
-    f.load(T.fac + (size_t)b * kTriElems, 0, lane);
-    const bool in = 64 * b + lane < T.N;
-    AT wv[NT];
+      for (int u = 0; u < RB; ++u) load_in(r_lo + min((int)threadIdx.x + NTHR * u, rows - 1), ri[u]);
+    };
+    constexpr bool kEarly = NT == 1 && HE == 4;  // (elsewhere the registers don't allow it)
+    if constexpr (kEarly) load_first();
 #pragma unroll
-    for (int c = 0; c < NT; ++c) wv[c] = in ? (AT)out[(size_t)(base + 64 * b + lane) * NT + c] : (AT)0;
+    for (int j = HE - 1; j >= 0; --j) {
+      const int k = off + j;
+      if (k >= T.h || k < first) continue;  // uniform
+      const int b = blk(k);
+      AT wv[NT];
+      rhs(b, wv);
 #pragma unroll
-    for (int c = 0; c < NT; ++c) t[c] = (AT)0;
-    couple(b, LB, (AT)1, y, t);
-    if (k > first) ahead(blk(k - 1), LB);
-    product_streamed(f, b, t, y);
+      for (int c = 0; c < NT; ++c) t[c] = (AT)0;
+      couple(b, LB, (AT)1, y, t);
+      if (k > first) ahead(blk(k - 1), LB);
+      product(D[j], b, t, y);
 #pragma unroll
-    for (int c = 0; c < NT; ++c) y[c] = wv[c] - y[c];
-    if (in) {
-      RowIn ri;
-      load_in(64 * b + lane, ri);
-      finish(64 * b + lane, y, ri);
-    }
-  }
-  if constexpr (!kEarly) load_first();
-  __syncthreads();
-  for (int i0r = 0; i0r < rows; i0r += RB * NTHR) {
-    if (i0r > 0)
-#pragma unroll
-      for (int u = 0; u < RB; ++u) load_in(r_lo + min(i0r + (int)threadIdx.x + NTHR * u, rows - 1), ri[u]);
-#pragma unroll
-    for (int u = 0; u < RB; ++u) {
-      const int i = i0r + threadIdx.x + NTHR * u;
-      if (i < rows) {
-        AT x[NT];
-#pragma unroll
-        for (int k = 0; k < NT; ++k) x[k] = rs[k * RR + i];
-        finish(r_lo + i, x, ri[u]);
+      for (int c = 0; c < NT; ++c) {
+        y[c] = wv[c] - y[c];
+        rs[c * RR + 64 * b - r_lo + lane] = y[c];
       }
     }
-  }
-  if (mode != 2) return;
+    for (int k = off - 1; k >= first; --k) {
+      const int b = blk(k);
+      TriFrag<FT, 32> f;
+      f.load(T.fac + (size_t)b * kTriElems, 0, lane);
+      const bool in = 64 * b + lane < T.N;
+      AT wv[NT];
 #pragma unroll
-  for (int k = 0; k < NT; ++k) {
-    const double a = wave_sum(rz[k]);
-    const double b2 = wave_sum(qz[k]);
-    if (lane == 0) {
-      dots[g][k] = a;
-      dots[g][NT + k] = b2;
+      for (int c = 0; c < NT; ++c) wv[c] = in ? (AT)out[(size_t)(base + 64 * b + lane) * NT + c] : (AT)0;
+#pragma unroll
+      for (int c = 0; c < NT; ++c) t[c] = (AT)0;
+      couple(b, LB, (AT)1, y, t);
+      if (k > first) ahead(blk(k - 1), LB);
+      product_streamed(f, b, t, y);
+#pragma unroll
+      for (int c = 0; c < NT; ++c) y[c] = wv[c] - y[c];
+      if (in) {
+        RowIn ri;
+        load_in(64 * b + lane, ri);
+        finish(64 * b + lane, y, ri);
+      }
+    }
+    if constexpr (!kEarly) load_first();
+    __syncthreads();
+    for (int i0r = 0; i0r < rows; i0r += RB * NTHR) {
+      if (i0r > 0)
+#pragma unroll
+        for (int u = 0; u < RB; ++u) load_in(r_lo + min(i0r + (int)threadIdx.x + NTHR * u, rows - 1), ri[u]);
+#pragma unroll
+      for (int u = 0; u < RB; ++u) {
+        const int i = i0r + threadIdx.x + NTHR * u;
+        if (i < rows) {
+          AT x[NT];
+#pragma unroll
+          for (int k = 0; k < NT; ++k) x[k] = rs[k * RR + i];
+          finish(r_lo + i, x, ri[u]);
+        }
+      }
+    }
+    if (mode != 2) return;
+#pragma unroll
+    for (int k = 0; k < NT; ++k) {
+      const double a = wave_sum(rz[k]);
+      const double b2 = wave_sum(qz[k]);
+      if (lane == 0) {
+        dots[g][k] = a;
+        dots[g][NT + k] = b2;
+      }
+    }
+    __syncthreads();
+    if (threadIdx.x < 2 * NT)
+      partial[(size_t)(blk_off + blockIdx.x) * 2 * NT + threadIdx.x] =
+          dots[0][threadIdx.x] + dots[1][threadIdx.x];
+  };
+  if constexpr (sizeof(FT) < 8) {
+    if (__builtin_expect(e.tri, 0)) {  // uniform over the workgroup
+      const TriArgs<FT>& a = again;
+      solve(std::true_type{}, a.desc[s], a.fac, a.dg, a.cpl, a.cidx, a.rin, a.out, a.mode, a.isub_list, a.mbf,
+            a.eta, a.qv, a.partial, a.blk_off, a.fuse_eta, a.Sinv, a.NL, a.ldS, a.bpart, a.pb,
+            a.npb, a.init, a.sc, a.sh);
+      return;
     }
   }
-  __syncthreads();
-  if (threadIdx.x < 2 * NT)
-    partial[(size_t)(blk_off + blockIdx.x) * 2 * NT + threadIdx.x] =
-        dots[0][threadIdx.x] + dots[1][threadIdx.x];
+  solve(std::false_type{}, e, fac, dg, cpl, cidx, rin, out, mode, isub_list, mbf, eta, qv, partial,
+        blk_off, fuse_eta, Sinv, NL, ldS, bpart, pb, npb, init, sc, sh);
 }
 
 // Two 16-row strips of the product, sharing the vector operand (operands as in
