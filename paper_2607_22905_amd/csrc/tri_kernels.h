@@ -251,11 +251,14 @@ __global__ __launch_bounds__(256) void k_tri_couplings(
 // and D = diag(S): S is an M-matrix, so D^{-1/2} S D^{-1/2} has its eigenvalues
 // below 2 and X >= D^{-1} / 2; where every row sum of D^{1/2} |E| D^{1/2} is at
 // most tau, -2 tau X <= E <= 2 tau X.  tau < 1/2 keeps X~ definite; the values
-// lie where iterations would be lost (8^3 boxes with a 4^3 body of the given
-// contrast in each, symmetric and triangular form: BF16 1e2 (row sums 0.28) 21
-// and 19 iterations, 1e3 (2.4) breakdown and 21; FP32 1e4 (4e-4) 12 and 12, 1e6
-// (0.05) 15 and 12, 1e8 breakdown and 20).  Gaussian and layered fields stay
-// below 0.05 (BF16) and 1e-6 (FP32).
+// lie where the symmetric form begins to need more iterations than the
+// triangular one, whose products take longer (an iteration 46 -> 58 us): 8^3
+// boxes with a 4^3 body in each, 64^3 cells, by contrast: row sums, iterations
+// of the triangular and of the symmetric form.  BF16: 100: 0.25, 23, 23; 1e4:
+// 21, 35, breakdown.  FP32: 1e4: 4e-4, 18, 18; 1e6: 0.05, 30, 34 (8 columns);
+// 1e8: 5, 20, breakdown.  (Below, both are as good as their FP32 arithmetic.)
+// Gaussian and layered fields stay below 0.23 (BF16; in 3-D 0.05) and 4e-6
+// (FP32).
 template <typename FT> struct TriTau { static constexpr double v = 1.0 / 1024; };
 template <> struct TriTau<bf16_t> { static constexpr double v = 1.0 / 4; };
 

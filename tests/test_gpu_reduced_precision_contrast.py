@@ -57,14 +57,15 @@ def _gpu(x):
     return torch.as_tensor(x, dtype=torch.float64, device="cuda:0")
 
 
-@pytest.mark.parametrize("nrhs,kw", [(1, {}), (1, {"separate_iface": True, "bf16_products": True}),
-                                     (2, {}), (4, {}), (8, {}), (16, {}),
-                                     (16, {"separate_iface": True, "bf16_products": True})])
-@pytest.mark.parametrize("case", list(LIMITS), ids=lambda c: "%s-%s-%.0e" % c)
+PRODUCTS = {"separate_iface": True, "bf16_products": True}  # an option of the BF16 form
+FORMS = [(c, nrhs, {}) for c in LIMITS for nrhs in (1, 2, 4, 8, 16)] + \
+        [(c, nrhs, PRODUCTS) for c in LIMITS for nrhs in (1, 16) if c[1] == "bf16"]
+
+
+@pytest.mark.parametrize("case,nrhs,kw", FORMS, ids=["%s-%s-%.0e-%d%s" % (*c, n, "-products" if k else "")
+                                                     for c, n, k in FORMS])
 def test_solve(case, nrhs, kw):
     kind, prec, contrast = case
-    if kw and prec != "bf16":
-        pytest.skip("an option of the BF16 form")
     P, part, m = _body(kind, contrast)
     h = am.AlgMortar(P.A, part, m, prec=prec, max_nrhs=nrhs, **kw)
     B = np.random.default_rng(nrhs).standard_normal((nrhs, P.n))
