@@ -5,7 +5,7 @@
 Workload (default): the 128^3 TPFA system with K = exp(GRF, sigma 1, ell 8),
 4096 subdomains of 8^3 cells, one right-hand side, PCG to relative residual
 1e-8 with x0 = 0 (FP64 everywhere).  A step is one full PCG solve (every
-iteration: SpMV, dots, axpys and the AlgMortar apply -- local tile sweeps,
+iteration: SpMV, dots, axpys and the AlgMortar apply -- local solves,
 interface right-hand side, interface solve, reconstruction).  The set-up
 (partition, local factors, basis functions, interface matrix and its
 inverse) runs once before the timed region, as the factors are reused
@@ -18,7 +18,7 @@ residuals stay FP64), reported under "precision_forms" with their solve
 rates, iteration counts and speedups over FP64.
 
 Prints one JSON line with the metric, the roofline of the dominant kernel
-(the local tile sweeps + reconstruction) and the CPU oracle baseline.
+(the local solves + reconstruction) and the CPU oracle baseline.
 """
 import argparse
 import hashlib

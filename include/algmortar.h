@@ -71,7 +71,8 @@ typedef struct {
 
 /* Precision of the local factors and local solves.  FP64 is the method as
  * written; FP32 and BF16 (bf16 storage, fp32 arithmetic) are the reduced-
- * precision forms.  The interface solve, PCG vectors, dots and residuals are
+ * precision forms, whose local operators stay positive definite at any
+ * contrast of the coefficients.  The interface solve, PCG vectors, dots and residuals are
  * always FP64. */
 typedef enum { AM_FP64 = 0, AM_FP32 = 1, AM_BF16 = 2 } am_prec;
 
@@ -113,8 +114,9 @@ typedef struct {
  * FP32 accumulation (16 right-hand sides: v_mfma_f32_16x16x16bf16_1k on the
  * matrix cores; one: the vector units, where such a product is exact in
  * FP32), instead of the default FP32 x FP32 products of the widened factors.
- * The diagonals of the block inverses stay FP32 and multiply the unrounded
- * vectors.  The preconditioner then carries 8-bit block vectors into every
+ * The diagonals of the block inverses (and of the triangular factors that take
+ * their place where rounding would spoil an inverse) stay FP32 and multiply the
+ * unrounded vectors.  The preconditioner then carries 8-bit block vectors into every
  * factor product; the outer PCG is the flexible one, as for every reduced
  * precision.  Ignored in every other case. */
 #define AM_FLAG_BF16_PRODUCTS 16u
@@ -245,8 +247,8 @@ am_status algmortar_set_inexact(am_handle h, double rtol, int32_t maxit);
  *   z = 0;  nu times z += B^{-1} (r - A z);  z += Mcal^{-1} (r - A z);
  *   nu times z += B^{-1} (r - A z)
  * with B = blockdiag(A[K, K]) over the blocks K of `blocks`, each block
- * solved exactly (band Cholesky of the block as it is, in the handle's factor
- * precision; the paper names block Jacobi and the number of blocks only).
+ * solved exactly (the block as it is, by the same kernels and in the same
+ * factor precision as the subdomains; the paper names block Jacobi and the number of blocks only).
  * blocks: host int32[n], ids in [0, nblocks), none empty (typically unions of
  * several subdomains; each block's bandwidth in ascending index order or RCM
  * order must be at most 128).  steps: nu in [0, 1000]; 0 removes the smoother.
@@ -325,8 +327,8 @@ am_status algmortar_export_mbf(am_handle h, int64_t iface, int32_t sub, double* 
 
 /* Measurement: `reps` back-to-back launches of one apply kernel on the
  * handle's internal stream, bracketed by HIP events (the buffers hold the
- * last call's data).  kernel: 0 = local solves + reconstruction (the band
- * sweeps of Algorithm 2), 1 = interface solve eta = S^{-1} b (its launches;
+ * last call's data).  kernel: 0 = local solves + reconstruction (the local
+ * part of Algorithm 2), 1 = interface solve eta = S^{-1} b (its launches;
  * AM_ERR_ARG where the local kernel forms eta for this number of right-hand
  * sides: small interface systems, few columns),
  * 2 = interface partial right-hand sides, 3 = the PCG SpMV (p update, A p,

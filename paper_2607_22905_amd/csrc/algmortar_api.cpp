@@ -940,10 +940,11 @@ static am_status check_vec_args(am_handle h, const void* a, const void* b, int32
 // work vectors of this handle) and keeps the fastest for the handle's later
 // applies and solves.  Runs once per right-hand-side count, outside any graph
 // capture.
-// The local kernel has a single layout: 16 right-hand sides with the
-// interface solve as its own launches, or one right-hand side with BF16 x
-// BF16 products where every subdomain is in the window-64 bucket (the
-// matrix-core kernels in both cases).
+// The local kernel has a single layout: 16 right-hand sides on the matrix cores
+// (every subdomain in the window-64 bucket, or eta formed by its own launches,
+// as the window-128 matrix-core kernel needs), or one right-hand side with BF16
+// x BF16 products where every subdomain is in the window-64 bucket (k_tri_solve
+// in its first layout).
 static bool single_layout(const DeviceState& d, int nr) {
   if (nr == 16 && d.bucket_sub[1].empty()) return true;
   if (eta_inline(d, nr)) return false;
@@ -960,7 +961,7 @@ static am_status autotune_tiles(am_handle h, int nr) {
   const int slot = tile_slot(nr);
   if (d.tile_cand[slot] >= 0) return AM_OK;
   const int nc = tile_candidates(d, nr);
-  // the matrix-core kernels have one layout: nothing to choose
+  // nothing to choose
   if (single_layout(d, nr)) {
     d.tile_cand[slot] = 0;
     return AM_OK;

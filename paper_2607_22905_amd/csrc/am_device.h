@@ -151,7 +151,7 @@ struct DeviceState {
   int32_t ldS = 0;  // padded interface dimension (multiple of kTile)
   int32_t fuse_eta = 0;  // small dense S^{-1}: eta in one launch, or in the local kernel (eta_inline)
   int32_t plain = 0;     // factors are the plain diagonal blocks A_ii (block Jacobi)
-  int32_t bf16_ops = 0;  // 16-RHS matrix-core sweeps: BF16 x BF16 products (AM_FLAG_BF16_PRODUCTS)
+  int32_t bf16_ops = 0;  // 1 and 16 columns: BF16 x BF16 products (AM_FLAG_BF16_PRODUCTS)
   int32_t max_nrhs = 1;
   int32_t max_np = 0;       // largest padded subdomain row count
   // wave layout of the tile kernel chosen by the autotuner per right-hand-side
@@ -181,7 +181,8 @@ struct DeviceState {
   int32_t* wp = nullptr;       // [m]
   int64_t* roff = nullptr;     // [m+1] padded row offsets of the factor blocks
   int64_t* fac_off = nullptr;  // [m+1] element offsets of the factor blocks
-  // window 64: packed block inverses (tri_kernels.h); window 128: band factor,
+  // window 64: packed block inverses or their triangular factors
+  // (tri_kernels.h); window 128: band factor,
   // column layout (precision dependent)
   void* Lc = nullptr;
   void* Lr = nullptr;          // band factor, row layout (window 128, set-up only; freed after)
@@ -189,7 +190,8 @@ struct DeviceState {
   // subdomains, from which their basis functions are solved (LocalPlan::band_off)
   void *Bc = nullptr, *Br = nullptr, *Bd = nullptr;
   int64_t* band_off = nullptr;
-  // per padded row: diagonal of the block inverses (window 64), 1/L_jj^2
+  // per padded row: diagonal of the block inverses, D of the triangular
+  // factors (window 64), 1/L_jj^2
   // (window 128); double for FP64, float otherwise
   void* invd = nullptr;
   // couplings between a window-64 subdomain's neighbouring blocks
@@ -385,7 +387,7 @@ hipError_t launch_place_values(DeviceState& d, const ValueMaps& vm, const double
 
 // ---- block-Jacobi smoothing (kernels_smooth.hip) ----
 struct SmoothDevice {
-  DeviceState* bj = nullptr;        // band factors of the plain diagonal blocks
+  DeviceState* bj = nullptr;        // factors of the plain diagonal blocks
   int32_t steps = 0;                // steps before and after the correction
   const int32_t* to_bj = nullptr;   // [n] AlgMortar position of each block-Jacobi position
   const int32_t* to_am = nullptr;   // [n] block-Jacobi position of each AlgMortar position

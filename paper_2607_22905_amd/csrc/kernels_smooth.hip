@@ -1,6 +1,6 @@
 // Block-Jacobi pre- and post-smoothing around the AlgMortar correction
 // (Sec. 5.4), for gfx950.  The smoother's block solves run on a second set
-// of band factors, those of the plain diagonal blocks A[K, K] of a coarser
+// of factors, those of the plain diagonal blocks A[K, K] of a coarser
 // partition, laid out in that partition's own device order; the AlgMortar
 // correction runs in the AlgMortar device order.  Vectors cross between the
 // two orders by gathers.  One application z = M^{-1} r, from z = 0:

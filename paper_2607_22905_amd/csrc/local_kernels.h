@@ -1216,8 +1216,11 @@ hipError_t mbf_t(DeviceState& d, hipStream_t st) {
       go(&k_tri_mbf<true>, d.d_bucket_pair[0], on, std::min(d.max_np0, kMbfRows) * sizeof(double));
       go(&k_tri_mbf<false>, d.d_bucket_pair[0] + on, d.long_pairs, 0);
     } else {
-      // reduced precision: the basis functions define the coarse space, and
-      // those of the band sweeps in FT arithmetic are kept
+      // reduced precision: from a band factor of their own, in FT.  Functions
+      // solved with the block inverses are closer to the FP64 ones (the
+      // application then by 10 to 60 times), but they are another coarse
+      // space, with which solves end some 1e-9 from where they ended with
+      // these; the second factorization is the price of the same results.
       hipLaunchKernelGGL((k_mbf<FT, 1>), dim3(nb0), dim3(64), 0, st, d.d_bucket_pair[0],
                          d.mbf_pair_sub, d.mbf_pair_q, d.sub_ptr, d.roff, d.band_off,
                          (const FT*)d.Bc, (const FT*)d.Br, (const IT*)d.Bd, d.mbf_off, d.mbf,

@@ -1292,7 +1292,8 @@ __device__ __forceinline__ void tri_mf_pass(V (&acc)[2], AF&& afn, BF&& bfn) {
 // tiles they would leave room for one workgroup per CU instead of two).  Both
 // groups form the middle block's x themselves: no exchange on the way back.
 // z = x + sum eta phat is FP64 for every factor type (v_mfma_f64_16x16x4f64; x
-// changes its result layout through LDS).
+// changes its result layout through LDS).  A subdomain in the triangular form
+// takes two products and two more barriers a step.
 // Bound by the LDS and memory latencies of a step (about 5 us with two
 // workgroups on the CU, 0.5 of it the product): 1721 subdomains of 200-800
 // cells, 16 columns, FP64: 347 us (band tiles, four products a step: 458).
